@@ -170,7 +170,7 @@ __device__ __forceinline__ void solve2(float g1x, float g1y, float g2x, float g2
 }
 
 template <int K, int BLOCK, bool ACC>
-__device__ __forceinline__ void adjoint_agent(int s, const AdjArgs &a, const GridMeta &g,
+__device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a, const GridMeta &g,
                                               float4 *lines, int tid)
 {
     const dev::SceneP &p = a.p;
@@ -224,8 +224,9 @@ __device__ __forceinline__ void adjoint_agent(int s, const AdjArgs &a, const Gri
         fail = nh;
         rec.kind = dev::kCentre;
     }
-    if (fail < mt)
-        dev::lp3<true, BLOCK, ACC>(src, mt, fail, vmax, prx, pry, p.eps, vx, vy, &rec);
+    dev::wave_lp3<true, K, BLOCK, ACC>(src, tid, live && fail < mt, mt, fail, vmax, prx, pry, p.eps,
+                                       vx, vy, &rec);
+    if (!live) return;
 
     // -- cotangent of the new velocity: v' directly and through p' = p + v' dt --
     const float gpx = a.gpx1[i], gpy = a.gpy1[i];
@@ -479,9 +480,9 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(AdjArgs a)
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;
     const int s = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + tid;
-    if (s >= a.n) return;
     const GridMeta g = *a.meta;
-    adjoint_agent<K, BLOCK, ACC>(s, a, g, lines, tid);
+    // every lane of the last wavefront takes part (LP3 is solved by quads)
+    adjoint_agent<K, BLOCK, ACC>(s < a.n, min(s, a.n - 1), a, g, lines, tid);
 }
 
 // Edges by target: count and rank.

@@ -170,21 +170,20 @@ struct BatchArgs {
     float *guess;  // per-agent K-th neighbour distance kept between steps
 };
 
+// The agent at cell-order position s (all lanes of the wavefront call it; one
+// past the last agent takes part without an agent of its own).
 template <int K, int BLOCK, bool ACC>
 __device__ __forceinline__ void batch_agent(const BatchArgs &a, int s, int first, float4 *lines,
                                             int tid)
 {
+    const bool live = s < a.n;
+    s = min(s, a.n - 1);
     const int sc = scene_from(a.off, a.S, first, s);
     const GridMeta g = a.meta[sc];
     const dev::SceneP p = dev::scene_params(a.prm[sc]);
-    // LP3's sub-problem boundaries cached in spare LDS columns: the batch's
-    // scenes keep many lanes in LP3 (3.37 -> 3.25 ms per step on the
-    // 512-scene batch, the same results bit for bit); on the dense crossing,
-    // where LP3 is a small share, the plain kernel is faster without it
-    dev::step_agent<K, BLOCK, ACC, false, true>(s, g, p, a.in, a.out, a.start, a.s0, a.s1, lines,
-                                                tid, a.guess);
+    dev::step_agent<K, BLOCK, ACC>(live, s, g, p, a.in, a.out, a.start, a.s0, a.s1, lines, tid,
+                                   a.guess);
 }
-
 
 // Persistent step: wavefronts pop 64-agent tiles, first from their XCD's
 // queue (a contiguous eighth of the tiles), then from the others.
@@ -208,7 +207,7 @@ __global__ __launch_bounds__(BLOCK) void k_step_batched(BatchArgs a)
             const int s = (lo + t) * kTile + lane;
             // the tile's first scene, searched once (a wavefront-uniform index)
             const int first = scene_of(a.off, a.S, (lo + t) * kTile);
-            if (s < a.n) batch_agent<K, BLOCK, ACC>(a, s, first, lines, tid);
+            batch_agent<K, BLOCK, ACC>(a, s, first, lines, tid);
         }
     }
 }
@@ -220,8 +219,7 @@ __global__ __launch_bounds__(BLOCK) void k_step_batched_flat(BatchArgs a)
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;
     const int s0 = xcd_tile(blockIdx.x, gridDim.x) * BLOCK;
-    const int s = s0 + tid;
-    if (s < a.n) batch_agent<K, BLOCK, ACC>(a, s, scene_of(a.off, a.S, s0), lines, tid);
+    batch_agent<K, BLOCK, ACC>(a, s0 + tid, scene_of(a.off, a.S, s0), lines, tid);
 }
 
 // Workgroups of k_step_batched that fit the device at once (cached per

@@ -66,8 +66,6 @@ struct LpVec<double> {
 };
 
 
-
-
 // Squared distance in double from FP32 positions, each operation rounded
 // separately (no fused multiply-add): the neighbour order is defined on it.
 __device__ __forceinline__ double nb_key(float xi, float yi, float xj, float yj)
@@ -812,7 +810,10 @@ struct ProjLines {
     // it is not a constraint (its components are then meaningless).
     __device__ __forceinline__ bool get(int j, float4 &out) const
     {
-        const float4 lj = ls.line(j);
+        return make(j, ls.line(j), out);
+    }
+    __device__ __forceinline__ bool make(int j, float4 lj, float4 &out) const
+    {
         if (ACC && j < ls.nh) {
             out = lj;
             return true;
@@ -871,58 +872,6 @@ struct ProjLinesD {
     }
 };
 
-// The boundaries of one least-penetration sub-problem, cached in the LDS
-// column of a lane of the same wavefront that runs no LP3 (its half-planes
-// are not read again once its LP2 is done): lp3 computes the boundaries
-// j < i of line i once, and the lp1 calls of the sub-problem read them
-// instead of recomputing every one at each re-solve.  A cached boundary is
-// the value ProjLines computes (multiply-adds are fused within an expression
-// only, so it has the bits of one computed where it is used), so the result
-// is the same bit for bit with or without a column; a lane without one (a
-// wavefront with more lanes in LP3 than not) computes on demand.
-template <int BLOCK, bool ACC>
-struct CachedProj {
-    const ProjLines<BLOCK, ACC> &pl;
-    const float4 *L;  // the workgroup's [slot][BLOCK] array
-    int col;          // cache column, or -1
-    uint32_t valid;   // bit j: boundary j is a constraint
-    __device__ __forceinline__ bool get(int j, float4 &out) const
-    {
-        if (col >= 0) {
-            out = L[j * BLOCK + col];
-            return (valid >> j) & 1u;
-        }
-        return pl.get(j, out);
-    }
-};
-
-// The cache column of this lane for lp3 (CachedProj): the r-th lane of the
-// wavefront that needs LP3 (in lane order) takes the column of the r-th lane
-// that does not; -1 without one.  Every active lane of the wavefront calls
-// it, after its LP2.  Only for callers whose lanes read none of their own
-// half-planes after LP2: the step does not, the adjoint's recomputation does
-// (its VJP reads the lines of the active set) and so takes no cache.
-template <int BLOCK>
-__device__ __forceinline__ int lp3_cache_column(bool need, int tid)
-{
-    const uint64_t needm = __ballot(need);
-    uint64_t spare = __ballot(!need);
-    const int lane = tid & (kWave - 1);
-    int col = -1;
-    if (need) {
-        int r = __popcll(needm & ((1ull << lane) - 1ull));
-        if (r < __popcll(spare)) {
-            for (; r > 0; --r) spare &= spare - 1ull;
-            col = (tid - lane) + __builtin_ctzll(spare);
-        }
-    }
-    // the owners' last reads of those columns (their LP2) stay before the
-    // cache writes of other lanes
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    return col;
-}
-
 // The constraints that define an LP result (its active set), recorded by
 // the adjoint's recomputation of the step.  LP2 results: kFree (v = v_pref),
 // kDisc (v_pref scaled onto the speed circle), kLine (projection of v_pref
@@ -968,25 +917,21 @@ struct FeasSlack<double> {
 };
 
 // One-dimensional sub-problem on line li (index i): the parameter interval
-// inside the speed disc and on the permitted side of every valid line j < i.
-// mode 0: closest point to (ox, oy); mode 1: extreme along unit (ox, oy), or,
-// when the line is orthogonal to it, the point closest to (tx, ty).
-// `how` reports what fixed the result: 0 projection, 1 / 2 the lower / upper
-// end of the interval (bounded by line `src`, or by the disc when src < 0),
-// 3 the tie projection.
-template <class S, class Src>
-__device__ __forceinline__ bool lp1(const Src &src, int i, typename LpVec<S>::T li, S vmax,
-                                    int mode, S ox, S oy, S tx, S ty, S eps, S &x, S &y, int &how,
-                                    int &bound)
+// inside the speed disc (lp1_disc) and on the permitted side of every valid
+// line j < i (lp1_cut), then the point of it that the objective takes
+// (lp1_point).  The parts are shared by the form that walks the lines in one
+// lane and the one that spreads them over four.
+//
+// The line meets the speed circle at t^2 + 2 dot t + c = 0, c = |q|^2 -
+// v_max^2.  c is formed in double (exact products), so its sign -- whether
+// q itself lies in the disc -- is exact; the root near q is taken as c
+// over the other root, which has no cancellation, so q stays inside the
+// interval exactly when it lies in the disc (the f = 0 lines of an agent
+// pass through its own velocity, which the grid build puts inside the
+// disc: that apex is then a feasible point, as it is exactly).
+template <class S, class V4>
+__device__ __forceinline__ bool lp1_disc(V4 li, S vmax, S &tl, S &tr)
 {
-    using V4 = typename LpVec<S>::T;
-    // The line meets the speed circle at t^2 + 2 dot t + c = 0, c = |q|^2 -
-    // v_max^2.  c is formed in double (exact products), so its sign -- whether
-    // q itself lies in the disc -- is exact; the root near q is taken as c
-    // over the other root, which has no cancellation, so q stays inside the
-    // interval exactly when it lies in the disc (the f = 0 lines of an agent
-    // pass through its own velocity, which the grid build puts inside the
-    // disc: that apex is then a feasible point, as it is exactly).
     const S dot = li.x * li.z + li.y * li.w;
     const double cd = (double)li.x * (double)li.x + (double)li.y * (double)li.y -
                       (double)vmax * (double)vmax;
@@ -996,42 +941,45 @@ __device__ __forceinline__ bool lp1(const Src &src, int i, typename LpVec<S>::T 
     const S sq = lp_sqrt(disc);
     const S far = dot > (S)0 ? -dot - sq : -dot + sq;
     const S near = far != (S)0 ? c / far : (S)0;
-    S tl = lp_min(far, near), tr = lp_max(far, near);
-    int sl = -1, sr = -1;
-    // Branch-free over j: the lanes of a wavefront meet different cases
-    // (parallel, lower or upper bound) at the same j, so every case is a
-    // select.  The interval only shrinks, so a failure at some j is a
-    // failure at the end: it is recorded in `ok` instead of returning.
-    // An interval empty by less than the scalar type resolves at this
-    // velocity scale (FeasSlack v_max) counts as one point: a feasible set
-    // that thin --
-    // several lines through one vertex, an apex on the speed circle -- is
-    // empty or not by rounding alone, and the point found then violates a
-    // constraint by no more than that.
-    const S slack = vmax * FeasSlack<S>::v;
-    // Lines parallel within eps are one line when line i is offset to j's
-    // forbidden side by no more than 2^-20 v_max (far below what the FP32
-    // positions resolve), else disjoint; the same offset in either precision
-    // and in the FP64 reference.
-    const S pslack = vmax * (S)0x1p-20;
-    bool ok = true;
-    for (int j = 0; j < i; ++j) {
-        V4 lj;
-        const bool valid = src.get(j, lj);
-        const S a = det2(lj.z, lj.w, li.z, li.w);
-        const S b = det2(lj.z, lj.w, li.x - lj.x, li.y - lj.y);
-        const bool par = lp_abs(a) <= eps;
-        const S t = -b / a;
-        const bool cut = valid && !par;
-        const bool lo = cut && a > (S)0 && t > tl;
-        const bool hi = cut && !(a > (S)0) && t < tr;
-        tl = lo ? t : tl;
-        sl = lo ? j : sl;
-        tr = hi ? t : tr;
-        sr = hi ? j : sr;
-        ok = ok && !(valid && par && b < -pslack) && !(tl > tr + slack);
-    }
-    if (!ok) return false;
+    tl = lp_min(far, near);
+    tr = lp_max(far, near);
+    return true;
+}
+
+// Line j's cut of the interval [tl, tr] (whose ends lines sl and sr set).
+// Branch-free: the lanes of a wavefront meet different cases (parallel,
+// lower or upper bound) at the same j, so every case is a select.  Lines
+// parallel within eps are one line when line i is offset to j's forbidden
+// side by no more than 2^-20 v_max (far below what the FP32 positions
+// resolve), else disjoint (`apart`); the same offset in either precision and
+// in the FP64 reference.
+template <class S, class V4>
+__device__ __forceinline__ void lp1_cut(int j, V4 lj, bool valid, V4 li, S eps, S pslack, S &tl,
+                                        S &tr, int &sl, int &sr, bool &apart)
+{
+    const S a = det2(lj.z, lj.w, li.z, li.w);
+    const S b = det2(lj.z, lj.w, li.x - lj.x, li.y - lj.y);
+    const bool par = lp_abs(a) <= eps;
+    const S t = -b / a;
+    const bool cut = valid && !par;
+    const bool lo = cut && a > (S)0 && t > tl;
+    const bool hi = cut && !(a > (S)0) && t < tr;
+    tl = lo ? t : tl;
+    sl = lo ? j : sl;
+    tr = hi ? t : tr;
+    sr = hi ? j : sr;
+    apart = apart || (valid && par && b < -pslack);
+}
+
+// mode 0: closest point to (ox, oy); mode 1: extreme along unit (ox, oy), or,
+// when the line is orthogonal to it, the point closest to (tx, ty).
+// `how` reports what fixed the result: 0 projection, 1 / 2 the lower / upper
+// end of the interval (bounded by line `src`, or by the disc when src < 0),
+// 3 the tie projection.
+template <class S, class V4>
+__device__ __forceinline__ void lp1_point(V4 li, int mode, S ox, S oy, S tx, S ty, S eps, S tl,
+                                          S tr, int sl, int sr, S &x, S &y, int &how, int &bound)
+{
     S t;
     if (mode == 0) {
         t = li.z * (ox - li.x) + li.w * (oy - li.y);
@@ -1057,6 +1005,34 @@ __device__ __forceinline__ bool lp1(const Src &src, int i, typename LpVec<S>::T 
     bound = how == 1 ? sl : (how == 2 ? sr : -1);
     x = li.x + t * li.z;
     y = li.y + t * li.w;
+}
+
+template <class S, class Src>
+__device__ __forceinline__ bool lp1(const Src &src, int i, typename LpVec<S>::T li, S vmax,
+                                    int mode, S ox, S oy, S tx, S ty, S eps, S &x, S &y, int &how,
+                                    int &bound)
+{
+    using V4 = typename LpVec<S>::T;
+    S tl, tr;
+    if (!lp1_disc<S>(li, vmax, tl, tr)) return false;
+    int sl = -1, sr = -1;
+    // An interval empty by less than the scalar type resolves at this
+    // velocity scale (FeasSlack v_max) counts as one point: a feasible set
+    // that thin --
+    // several lines through one vertex, an apex on the speed circle -- is
+    // empty or not by rounding alone, and the point found then violates a
+    // constraint by no more than that.  The interval only shrinks, so a
+    // failure at some j is a failure at the end.
+    const S slack = vmax * FeasSlack<S>::v;
+    const S pslack = vmax * (S)0x1p-20;
+    bool apart = false;
+    for (int j = 0; j < i; ++j) {
+        V4 lj;
+        const bool valid = src.get(j, lj);
+        lp1_cut<S>(j, lj, valid, li, eps, pslack, tl, tr, sl, sr, apart);
+    }
+    if (apart || tl > tr + slack) return false;
+    lp1_point<S>(li, mode, ox, oy, tx, ty, eps, tl, tr, sl, sr, x, y, how, bound);
     return true;
 }
 
@@ -1119,14 +1095,11 @@ __device__ __forceinline__ int lp2(const Src &src, int m, S vmax, int mode, S ox
 // region where no earlier line penetrates more than line i, as deep into line
 // i's permitted side as possible.  With ACC the first nh lines are hard: never
 // relaxed, they bound every re-solve as they are.
-// `col`: a cache column for the sub-problems' boundaries (lp3_cache_column;
-// only without hard lines), or -1.
 template <bool REC, int BLOCK, bool ACC = false>
 __device__ __forceinline__ void lp3(const LdsLines<BLOCK, ACC> &ls, int m, int fail, float vmax,
                                     float tx, float ty, float eps, float &vx, float &vy,
-                                    ActiveSet *rec, int col = -1)
+                                    ActiveSet *rec)
 {
-    static_assert(ORCA_K_MAX <= 32, "the cache's validity bits are one 32-bit word");
     float level = 0.0f;
     float x = vx, y = vy;
     const int nhard = ACC ? ls.nh : 0;
@@ -1147,19 +1120,9 @@ __device__ __forceinline__ void lp3(const LdsLines<BLOCK, ACC> &ls, int m, int f
         }
         if (i >= m) break;
         ProjLines<BLOCK, ACC> src{ls, li, det2(li.z, li.w, li.x, li.y), eps};
-        uint32_t valid = 0;
-        if (!ACC && col >= 0) {
-            float4 *C = const_cast<float4 *>(ls.L);
-            for (int j = 0; j < i; ++j) {
-                float4 b;
-                valid |= (src.get(j, b) ? 1u : 0u) << j;
-                C[j * BLOCK + col] = b;
-            }
-        }
-        const CachedProj<BLOCK, ACC> cs{src, ls.L, ACC ? -1 : col, valid};
         float nx = x, ny = y;
         ActiveSet inner;
-        bool solved = lp2<REC, float>(cs, i, vmax, 1, -li.w, li.z, tx, ty, eps, nx, ny,
+        bool solved = lp2<REC, float>(src, i, vmax, 1, -li.w, li.z, tx, ty, eps, nx, ny,
                                       &inner) == i;
         if (!solved) {
             // failed in FP32 only: solve it again in double (ProjLinesD)
@@ -1184,6 +1147,286 @@ __device__ __forceinline__ void lp3(const LdsLines<BLOCK, ACC> &ls, int m, int f
     }
     vx = x;
     vy = y;
+}
+
+// ---------------------------------------------------------------------------
+// Least penetration (Sec. 3), by a group of lanes per agent: from LP2's
+// partial result at line `fail`, each later line i whose penetration exceeds
+// the current level re-solves v in the region where no earlier line penetrates
+// more than line i, as deep into line i's permitted side as possible.  Hard
+// lines are never relaxed; they bound every re-solve as they are.
+//
+// What bounds it is the serial walk over lines inside lines inside lines, and
+// the lanes that wait for it: a wavefront has few lanes in LP3 (a quarter in a
+// dense crossing, an eighth in a mixed crowd), so a walk by the lane itself
+// runs at that share of the SIMD.  Here the failed agents of the wavefront, 16
+// at a time, are taken over by its 16 groups of G = 4 lanes: lane c of a group
+// holds lines c, c + G, c + 2 G, ... of its agent, so the boundaries, the test
+// for the next violated line and the cuts of an interval each take a fourth
+// of the walk (one pass over the lane's registers and two DPP steps), and each
+// boundary is formed once for a sub-problem.
+// The result is the serial one bit for bit: the first violated line is the
+// least index over the group, an interval's ends are an exact maximum and
+// minimum (the first line that attains one is kept, as in the walk), and
+// every value is formed by the same expressions.
+//
+// Against the walk per lane, whole steps: 1M dense crossing (24 % of agents in
+// LP3) 452 -> 394 us, 66,560 mixed (12 %) 148 -> 96 us, 4,999 mixed 121 -> 92
+// us, 512 scenes (44 %) 4.03 -> 3.56 ms.  G = 8 and 16: 407 and 452 us on the
+// crossing against 384 us; with hard lines, up to ten more per agent, 8 is the
+// best (200,003 capped: 240, 208 and 226 us at 4, 8 and 16; 278 us by the walk).
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
+
+// Reductions over the G lanes of a group (4, 8 or 16), the result in each:
+// lanes 1,0,3,2 and 2,3,0,1 of each quad, then the lanes of each half row and
+// of each row in reverse.
+template <int G, class F>
+__device__ __forceinline__ int group_reduce(int v, F f)
+{
+    v = f(v, dpp<0xB1>(v));
+    v = f(v, dpp<0x4E>(v));
+    if (G >= 8) v = f(v, dpp<0x141>(v));
+    if (G >= 16) v = f(v, dpp<0x140>(v));
+    return v;
+}
+template <int G>
+__device__ __forceinline__ int group_min(int v)
+{
+    return group_reduce<G>(v, [](int a, int b) { return min(a, b); });
+}
+template <int G>
+__device__ __forceinline__ bool group_any(bool p)
+{
+    return group_reduce<G>(p ? 1 : 0, [](int a, int b) { return a | b; }) != 0;
+}
+template <int G>
+__device__ __forceinline__ float group_max(float v)
+{
+    return __int_as_float(group_reduce<G>(__float_as_int(v), [](int a, int b) {
+        return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b)));
+    }));
+}
+template <int G>
+__device__ __forceinline__ float group_min(float v)
+{
+    return __int_as_float(group_reduce<G>(__float_as_int(v), [](int a, int b) {
+        return __float_as_int(fminf(__int_as_float(a), __int_as_float(b)));
+    }));
+}
+
+// Line k of the group's (the same k in its lanes), from register k / G of
+// lane k % G.
+template <int G, int NL>
+__device__ __forceinline__ float4 group_line(const float4 (&l)[NL], int k)
+{
+    float4 v = l[0];
+#pragma unroll
+    for (int r = 1; r < NL; ++r) {
+        const bool is = k / G == r;
+        v = make_float4(is ? l[r].x : v.x, is ? l[r].y : v.y, is ? l[r].z : v.z,
+                        is ? l[r].w : v.w);
+    }
+    return make_float4(__shfl(v.x, k % G, G), __shfl(v.y, k % G, G), __shfl(v.z, k % G, G),
+                       __shfl(v.w, k % G, G));
+}
+
+// LP3 of one agent by the group this lane belongs to (c = its lane there); all
+// arguments are the same in the group's lanes.  ls reads the agent's lines.  NL:
+// lines per lane.
+template <bool REC, int BLOCK, bool ACC, int G, int NL>
+__device__ __forceinline__ void group_lp3(const LdsLines<BLOCK, ACC> &ls, int c, int m, int fail,
+                                         float vmax, float tx, float ty, float eps, float &vx,
+                                         float &vy, ActiveSet *rec)
+{
+    float level = 0.0f;
+    float x = vx, y = vy;
+    const int nhard = ACC ? ls.nh : 0;
+    // a line is re-solved only when it exceeds the level by more than FP32
+    // resolves in a penetration (about 2^-20 v_max): at a point where several
+    // lines are penetrated equally, FP32 rounding alone would otherwise
+    // decide whether a later tied line triggers a re-solve, and the re-solve
+    // then jumps to another vertex of the tie
+    const float tol = vmax * FeasSlack<float>::v;
+    const float slack = vmax * FeasSlack<float>::v;
+    const float pslack = vmax * 0x1p-20f;
+    float4 ln[NL];
+#pragma unroll
+    for (int r = 0; r < NL; ++r) ln[r] = ls.line(min(c + G * r, m - 1));
+    int i = fail > nhard ? fail : nhard;
+    for (;;) {
+        // the next line above the level
+        int first = m;
+#pragma unroll
+        for (int r = NL - 1; r >= 0; --r) {
+            const int j = c + G * r;
+            const bool above = det2(ln[r].z, ln[r].w, ln[r].x - x, ln[r].y - y) > level + tol;
+            first = j >= i && j < m && above ? j : first;
+        }
+        i = group_min<G>(first);
+        if (i >= m) break;
+        const float4 li = ls.line(i);
+        const ProjLines<BLOCK, ACC> src{ls, li, det2(li.z, li.w, li.x, li.y), eps};
+        float4 bd[NL];
+        uint32_t valid = 0;
+#pragma unroll
+        for (int r = 0; r < NL; ++r) {
+            const int j = c + G * r;
+            if (G * r < i) {  // the same in the whole group
+                const bool is = src.make(j, ln[r], bd[r]) && j < i;
+                valid |= (is ? 1u : 0u) << r;
+            }
+        }
+        // LP2 over the boundaries, objective: deepest into line i
+        const float ox = -li.w, oy = li.z;
+        float nx = ox * vmax, ny = oy * vmax;
+        ActiveSet inner{kDir, -1, -1, -1};
+        bool solved = true;
+        for (int k = 0;;) {
+            int next = i;
+#pragma unroll
+            for (int r = NL - 1; r >= 0; --r) {
+                const int j = c + G * r;
+                if (G * r < i) {
+                    const bool out = det2(bd[r].z, bd[r].w, bd[r].x - nx, bd[r].y - ny) > 0.0f;
+                    next = ((valid >> r) & 1u) && j >= k && out ? j : next;
+                }
+            }
+            k = group_min<G>(next);
+            if (k >= i) break;
+            const float4 lk = group_line<G>(bd, k);
+            float tl, tr;
+            solved = lp1_disc<float>(lk, vmax, tl, tr);
+            if (!solved) break;
+            const float tl0 = tl, tr0 = tr;
+            int sl = -1, sr = -1;
+            bool apart = false;
+#pragma unroll
+            for (int r = 0; r < NL; ++r) {
+                const int j = c + G * r;
+                if (G * r < k)
+                    lp1_cut<float>(j, bd[r], ((valid >> r) & 1u) && j < k, lk, eps, pslack, tl, tr,
+                                   sl, sr, apart);
+            }
+            if (REC) {
+                // the first line that sets each end
+                const float gl = group_max<G>(tl), gr = group_min<G>(tr);
+                const int fl = group_min<G>(sl >= 0 && tl == gl ? sl : INT_MAX);
+                const int fr = group_min<G>(sr >= 0 && tr == gr ? sr : INT_MAX);
+                sl = gl > tl0 && fl != INT_MAX ? fl : -1;
+                sr = gr < tr0 && fr != INT_MAX ? fr : -1;
+                tl = gl;
+                tr = gr;
+            } else {
+                tl = group_max<G>(tl);
+                tr = group_min<G>(tr);
+            }
+            solved = !(group_any<G>(apart) || tl > tr + slack);
+            if (!solved) break;
+            int how, bound;
+            lp1_point<float>(lk, 1, ox, oy, tx, ty, eps, tl, tr, sl, sr, nx, ny, how, bound);
+            if (REC) {
+                inner.a = k;
+                inner.b = bound;
+                inner.kind = how == 3 ? kTie : (bound >= 0 ? kProjProj : kProjDisc);
+            }
+            ++k;
+        }
+        if (!solved) {
+            // failed in FP32 only: solve it again in double (ProjLinesD), the
+            // same walk in each of the group's lanes
+            const double4 lid = make_double4(li.x, li.y, li.z, li.w);
+            ProjLinesD<BLOCK, ACC> srcd{ls, lid, (double)eps};
+            double dx = x, dy = y;
+            solved = lp2<REC, double>(srcd, i, (double)vmax, 1, -lid.w, lid.z, (double)tx,
+                                      (double)ty, (double)eps, dx, dy, &inner) == i;
+            nx = (float)dx;
+            ny = (float)dy;
+        }
+        if (solved) {
+            x = nx;
+            y = ny;
+            if (REC) {
+                *rec = inner;
+                rec->i3 = i;
+            }
+        }
+        level = det2(li.z, li.w, li.x - x, li.y - y);
+        ++i;
+    }
+    vx = x;
+    vy = y;
+}
+
+// LP3 of every lane of the wavefront with `need` (its LP2 stopped at line
+// fail < m), all 64 lanes taking part: by groups of lanes, or by each lane
+// itself (lp3) where most of the wavefront needs it and the walk keeps its
+// lanes busy.  The line at 24, 32, 40 and 48 lanes and groups alone: the 1M
+// crossing simulated over steps 10-110 403, 403, 407, 410 and 419 us per step
+// (419 us by the walk alone), 512 scenes at 32, 40 and groups alone 3.68, 3.57
+// and 3.56 ms, 200,003 capped at 24 to 48 253, 238, 211 and 212 us; small
+// crowds are the same down to 32 and lose at 24 (4,999 mixed: 92 and 112 us).
+template <bool REC, int K, int BLOCK, bool ACC>
+__device__ __forceinline__ void wave_lp3(const LdsLines<BLOCK, ACC> &ls, int tid, bool need, int m,
+                                         int fail, float vmax, float tx, float ty, float eps,
+                                         float &vx, float &vy, ActiveSet *rec)
+{
+    constexpr int G = ACC ? 8 : 4;
+    constexpr int NL = (K + (ACC ? kAccLines + kTurnLines : 0) + G - 1) / G;
+    constexpr int kGroups = kWave / G;
+    const uint64_t needm = __ballot(need);
+    const int nf = __popcll(needm);
+    if (nf > (ACC ? 48 : 40)) {
+        if (need) lp3<REC, BLOCK, ACC>(ls, m, fail, vmax, tx, ty, eps, vx, vy, rec);
+        return;
+    }
+    const int lane = tid & (kWave - 1);
+    const int rank = __popcll(needm & ((1ull << lane) - 1ull));
+    lane_order<kWave>();  // the groups read other lanes' lines
+    for (int base = 0; base < nf; base += kGroups) {
+        const bool mine = need && rank >= base && rank < base + kGroups;
+        const int slot = (rank - base) * G;
+        // each group learns whose agent it takes (a lane without one sends to
+        // lane 1, which nobody reads)
+        const int from = __shfl(__builtin_amdgcn_ds_permute((mine ? slot : 1) * 4, lane), 0, G);
+        const bool busy = lane / G < nf - base;
+        const int src = busy ? from : lane;
+        float qx = __shfl(vx, src, kWave), qy = __shfl(vy, src, kWave);
+        const float qvm = __shfl(vmax, src, kWave), qtx = __shfl(tx, src, kWave),
+                    qty = __shfl(ty, src, kWave), qeps = __shfl(eps, src, kWave);
+        const int qm = __shfl(m, src, kWave), qfail = __shfl(fail, src, kWave);
+        LdsLines<BLOCK, ACC> ql{ls.L, (tid - lane) + src};
+        if (ACC) {
+            ql.nh = __shfl(ls.nh, src, kWave);
+            ql.nacc = __shfl(ls.nacc, src, kWave);
+            ql.cx = __shfl(ls.cx, src, kWave);
+            ql.cy = __shfl(ls.cy, src, kWave);
+            ql.h = __shfl(ls.h, src, kWave);
+            ql.rx = __shfl(ls.rx, src, kWave);
+            ql.ry = __shfl(ls.ry, src, kWave);
+            ql.lx = __shfl(ls.lx, src, kWave);
+            ql.ly = __shfl(ls.ly, src, kWave);
+        }
+        ActiveSet r{kFree, -1, -1, -1};
+        if (REC) r = ActiveSet{__shfl(rec->kind, src, kWave), __shfl(rec->i3, src, kWave),
+                               __shfl(rec->a, src, kWave), __shfl(rec->b, src, kWave)};
+        if (busy)
+            group_lp3<REC, BLOCK, ACC, G, NL>(ql, lane % G, qm, qfail, qvm, qtx, qty, qeps, qx,
+                                              qy, &r);
+        const int back = mine ? slot : lane;
+        const float gx = __shfl(qx, back, kWave), gy = __shfl(qy, back, kWave);
+        vx = mine ? gx : vx;
+        vy = mine ? gy : vy;
+        if (REC) {
+            const ActiveSet g{__shfl(r.kind, back, kWave), __shfl(r.i3, back, kWave),
+                              __shfl(r.a, back, kWave), __shfl(r.b, back, kWave)};
+            if (mine) *rec = g;
+        }
+    }
 }
 
 // Scalar parameters of the scene an agent belongs to, in the form the
@@ -1277,11 +1520,11 @@ __device__ __forceinline__ void desired_velocity(const SceneP &p, float xi, floa
 // pass.  ACC compiles the acceleration lines in (used for agents whose class
 // has a cap).  EXPORT also writes the neighbour list the step used (caller
 // indices, ascending, -1 padded) to nbr[i * kout ..] and its length to
-// cnt[i] (either nullable); the step itself is unchanged.  LP3CACHE lets
-// LP3 cache its sub-problems' boundaries in spare LDS columns (CachedProj;
-// without hard lines), which changes no result.
-template <int K, int BLOCK, bool ACC = false, bool EXPORT = false, bool LP3CACHE = false>
-__device__ __forceinline__ void step_agent(int s, const GridMeta &g, const SceneP &p,
+// cnt[i] (either nullable); the step itself is unchanged.  All 64 lanes of a
+// wavefront call it; one that is not `live` repeats an agent of another lane
+// and writes nothing (its lanes serve LP3).
+template <int K, int BLOCK, bool ACC = false, bool EXPORT = false>
+__device__ __forceinline__ void step_agent(bool live, int s, const GridMeta &g, const SceneP &p,
                                            const orca_agents_in &in, const orca_agents_out &out,
                                            const uint32_t *__restrict__ start,
                                            const float4 *__restrict__ s0,
@@ -1311,7 +1554,7 @@ __device__ __forceinline__ void step_agent(int s, const GridMeta &g, const Scene
 
     uint64_t *buf = reinterpret_cast<uint64_t *>(lines);
     const int found = knn_select<K, BLOCK>(g, start, s0, xi, yi, i, (uint32_t)s, buf, tid, rg2);
-    if (guess)
+    if (guess && live)
         guess[i] = found == K ? sqrtf(__uint_as_float((uint32_t)(buf[buf_idx<BLOCK>(K - 1, tid)] >> 32)))
                               : 0.0f;
     const int kk = p.k < K ? p.k : K;
@@ -1319,7 +1562,7 @@ __device__ __forceinline__ void step_agent(int s, const GridMeta &g, const Scene
     uint32_t pos[K];
 #pragma unroll
     for (int q = 0; q < K; ++q) pos[q] = q < m ? entry_pos(buf[buf_idx<BLOCK>(q, tid)]) : 0u;
-    if (EXPORT) {
+    if (EXPORT && live) {
         if (nbr) {
             int32_t *row = nbr + (int64_t)i * kout;
             for (int q = 0; q < kout; ++q)
@@ -1356,11 +1599,11 @@ __device__ __forceinline__ void step_agent(int s, const GridMeta &g, const Scene
         fail = nh;
         st = 1;
     }
-    const int col = (ACC || !LP3CACHE) ? -1 : lp3_cache_column<BLOCK>(fail < mt, tid);
-    if (fail < mt) {
-        lp3<false, BLOCK, ACC>(src, mt, fail, vmax, prx, pry, p.eps, vx, vy, nullptr, col);
-        st = 1;
-    }
+    const bool infeasible = fail < mt;
+    wave_lp3<false, K, BLOCK, ACC>(src, tid, live && infeasible, mt, fail, vmax, prx, pry, p.eps,
+                                   vx, vy, nullptr);
+    if (infeasible) st = 1;
+    if (!live) return;
     out.vx[i] = vx;
     out.vy[i] = vy;
     out.px[i] = xi + vx * p.dt;

@@ -36,10 +36,9 @@ __global__ __launch_bounds__(BLOCK) void k_step(StepArgs a, dev::SceneP p)
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;
     const int s = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + tid;
-    if (s >= a.n) return;
     const GridMeta g = *a.meta;
-    dev::step_agent<K, BLOCK, ACC, EXPORT>(s, g, p, a.in, a.out, a.start, a.s0, a.s1, lines, tid,
-                                           a.guess, a.nbr, a.cnt, a.k);
+    dev::step_agent<K, BLOCK, ACC, EXPORT>(s < a.n, min(s, a.n - 1), g, p, a.in, a.out, a.start,
+                                           a.s0, a.s1, lines, tid, a.guess, a.nbr, a.cnt, a.k);
 }
 
 template <int K, int BLOCK>

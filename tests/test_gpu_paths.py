@@ -40,3 +40,33 @@ def test_batch_that_fits_the_device_at_once_equals_the_queued_form(total):
         got.append([getattr(out, k) for k in FIELDS] + [status])
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("k", [1, 4, 5, 16, 20, 32])
+@pytest.mark.parametrize("jam,free,caps", [(15, 49, False), (17, 47, False), (33, 30, False),
+                                           (64, 0, False), (65, 1, False), (9, 40, True),
+                                           (64, 0, True)])
+def test_least_penetration_by_groups_of_lanes(k, jam, free, caps):
+    """A wavefront's agents in LP3 are solved 16 (8 with hard lines) at a
+    time: jammed agents on either side of that, up to whole wavefronts, among
+    free ones in caller order, and the last wavefront partly empty."""
+    from parity import compare_step
+    rng = np.random.Generator(np.random.PCG64(1000 + 7 * jam + k))
+    p = scenarios.Params(dt=0.1, neighbor_dist=6.0, max_neighbors=k, pref_is_goal=0,
+                         accel=(2.0, 1.0) if caps else (0.0, 0.0),
+                         turn=(0.0, 1.0) if caps else (0.0, 0.0))
+    n = jam + free
+    order = rng.permutation(n)
+    x = np.where(np.arange(n) < jam, rng.uniform(0.0, 2.5, n), 50.0 + 20.0 * np.arange(n))[order]
+    y = np.where(np.arange(n) < jam, rng.uniform(0.0, 2.5, n), 10.0)[order]
+    veh = rng.random(n) < 0.2
+    f32 = lambda a: np.ascontiguousarray(a, dtype=np.float32)  # noqa: E731
+    ang, sp = rng.uniform(0.0, 2.0 * np.pi, n), np.where(veh, 6.0, 1.5)
+    st = {"px": f32(x), "py": f32(y), "vx": f32(0.9 * sp * np.cos(ang)),
+          "vy": f32(0.9 * sp * np.sin(ang)), "pref_x": f32(0.9 * sp * np.sin(ang)),
+          "pref_y": f32(0.9 * sp * np.cos(ang)), "radius": f32(np.where(veh, 0.8, 0.3)),
+          "max_speed": f32(sp), "cls": veh.astype(np.uint8)}
+    rep, g, o = compare_step(st, p, max_ill_frac=1.0)
+    assert rep["n_bad"] <= max(2, n // 20), rep
+    if k >= 4:
+        assert rep["lp3_oracle"] >= jam // 3, rep
