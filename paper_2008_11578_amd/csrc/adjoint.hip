@@ -39,8 +39,9 @@ struct AdjArgs {
     int n;
     const GridMeta *meta;
     const uint32_t *start;
-    const float4 *s0;
+    const float2 *s0;
     const float4 *s1;
+    float *guess;  // per-agent radius of the neighbour scan kept between calls
     dev::SceneP p;
     const float *gpx1, *gpy1, *gvx1, *gvy1;
     float *gpx0, *gpy0, *gvx0, *gvy0, *gprx, *gpry;
@@ -174,16 +175,18 @@ __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a
                                               float4 *lines, int tid)
 {
     const dev::SceneP &p = a.p;
-    const float4 me0 = a.s0[s];
+    const float2 me0 = a.s0[s];
     const float4 me1 = a.s1[s];
-    const int i = __float_as_int(me0.z);
-    const float xi = me0.x, yi = me0.y, ri = me0.w, vxi = me1.x, vyi = me1.y;
-    const int ci = __float_as_int(me1.z) & 1;
+    const int i = tag_index(me1.z);
+    const float xi = me0.x, yi = me0.y, ri = me1.w, vxi = me1.x, vyi = me1.y;
+    const int ci = tag_class(me1.z);
 
     // -- forward recomputation (identical to dev::step_agent) --
     uint64_t *buf = reinterpret_cast<uint64_t *>(lines);
-    const int found = dev::knn_select<K, BLOCK>(g, a.start, a.s0, xi, yi, i, (uint32_t)s, buf, tid,
-                                                g.rn2);
+    float kept = a.guess[i];
+    const int found = dev::knn_select<K, BLOCK>(g, a.start, a.s0, a.s1, xi, yi, (uint32_t)s, buf,
+                                                tid, &kept);
+    if (live) a.guess[i] = kept;
     const int kk = p.k < K ? p.k : K;
     const int m = found < kk ? found : kk;
     uint32_t pos[K];
@@ -401,13 +404,13 @@ __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a
 #pragma unroll
             for (int q = 0; q < K; ++q)
                 if (q == qn) pj = pos[q];
-            const float4 b0 = a.s0[pj];
+            const float2 b0 = a.s0[pj];
             const float4 b1 = a.s1[pj];
-            const int j = __float_as_int(b0.z);
-            const float f = (__float_as_int(b1.z) & 1) ? fb : fa;
+            const int j = tag_index(b1.z);
+            const float f = tag_class(b1.z) ? fb : fa;
             float Pbx, Pby, Vbx, Vby, itb;
             bool uses_tau;
-            halfplane_vjp(xi, yi, vxi, vyi, ri, b0.x, b0.y, b1.x, b1.y, b0.w, f, p.inv_tau,
+            halfplane_vjp(xi, yi, vxi, vyi, ri, b0.x, b0.y, b1.x, b1.y, b1.w, f, p.inv_tau,
                           p.inv_dt, i < j, lb.qx[e], lb.qy[e], lb.nx[e], lb.ny[e], Pbx, Pby, Vbx,
                           Vby, itb, uses_tau);
             spx -= Pbx;
@@ -650,6 +653,7 @@ hipError_t launch_adjoint(const orca_agents_in &in, int n, const orca_params &pr
     a.start = w.start;
     a.s0 = w.s0;
     a.s1 = w.s1;
+    a.guess = w.guess;
     a.p = dev::scene_params(prm);
     a.gpx1 = gpx1;
     a.gpy1 = gpy1;

@@ -164,10 +164,10 @@ struct BatchArgs {
     int S;
     int n;
     const uint32_t *start;
-    const float4 *s0;
+    const float2 *s0;
     const float4 *s1;
     uint32_t *queue;
-    float *guess;  // per-agent K-th neighbour distance kept between steps
+    float *guess;  // per-agent radius of the neighbour scan kept between steps
 };
 
 // The agent at cell-order position s (all lanes of the wavefront call it; one

@@ -45,7 +45,7 @@ Layout make_layout(int64_t n, int64_t n_scenes, int64_t max_cells)
     L.tiles = o;
     o = align_up(o + sizeof(uint32_t) * (size_t)(L.n_tiles + 1));
     L.s0 = o;
-    o = align_up(o + sizeof(float4) * (size_t)(n + kScanPad));
+    o = align_up(o + sizeof(float2) * (size_t)(n + kScanPad));
     L.s1 = o;
     o = align_up(o + sizeof(float4) * (size_t)n);
     L.guess = o;
@@ -66,7 +66,7 @@ Work bind(const Layout &L, void *ws)
     w.count = (uint32_t *)(b + L.count);
     w.start = (uint32_t *)(b + L.start);
     w.tiles = (uint32_t *)(b + L.tiles);
-    w.s0 = (float4 *)(b + L.s0);
+    w.s0 = (float2 *)(b + L.s0);
     w.s1 = (float4 *)(b + L.s1);
     w.guess = (float *)(b + L.guess);
     return w;

@@ -205,17 +205,17 @@ __global__ __launch_bounds__(kBlock) void k_scatter(orca_agents_in in, int n,
                                                     const uint32_t *__restrict__ cell,
                                                     const uint32_t *__restrict__ rank,
                                                     const uint32_t *__restrict__ start,
-                                                    float4 *__restrict__ s0,
+                                                    float2 *__restrict__ s0,
                                                     float4 *__restrict__ s1)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     const uint32_t pos = start[cell[i]] + rank[i];
     if (pos >= (uint32_t)n) return;  // cannot happen for a consistent histogram
-    s0[pos] = make_float4(in.px[i], in.py[i], __int_as_float(i), in.radius[i]);
+    s0[pos] = make_float2(in.px[i], in.py[i]);
     float vx = in.vx[i], vy = in.vy[i];
     cap_velocity(vx, vy, in.max_speed[i]);
-    s1[pos] = make_float4(vx, vy, __int_as_float((int)in.cls[i]), 0.0f);
+    s1[pos] = make_float4(vx, vy, __int_as_float(agent_tag(i, (int)in.cls[i])), in.radius[i]);
 }
 
 __global__ void k_fill_zero(uint4 *p, size_t n16)

@@ -210,7 +210,8 @@ __global__ __launch_bounds__(kBlock) void k_spawn_check(orca_agents_in cand, int
                                                          const float *__restrict__ a_max_speed,
                                                          const GridMeta *__restrict__ meta,
                                                          const uint32_t *__restrict__ start,
-                                                         const float4 *__restrict__ s0,
+                                                         const float2 *__restrict__ s0,
+                                                         const float4 *__restrict__ s1,
                                                          const float *__restrict__ bounds,
                                                          float t_clear, int n,
                                                          uint8_t *__restrict__ blocked,
@@ -227,10 +228,11 @@ __global__ __launch_bounds__(kBlock) void k_spawn_check(orca_agents_in cand, int
         const double reach = ((double)cr + (double)bounds[0]) + t * ((double)cs + (double)bounds[1]);
         const double r2 = reach * reach * (1.0 + 1e-9);
         dev::scan_disc(g, start, s0, (double)cx, (double)cy, r2,
-                       [&](const float4 &a, uint32_t, bool valid) {
+                       [&](const float2 &a, uint32_t k, bool valid) {
                            if (valid && !hit) {
-                               const int j = __float_as_int(a.z);
-                               hit = too_close(cx, cy, cr, cs, a.x, a.y, a.w, a_max_speed[j], t);
+                               const float4 b = s1[k];
+                               hit = too_close(cx, cy, cr, cs, a.x, a.y, b.w,
+                                               a_max_speed[tag_index(b.z)], t);
                            }
                        });
     }
@@ -383,7 +385,8 @@ struct OverlapPart {
 
 __global__ __launch_bounds__(kBlock) void k_overlap(const GridMeta *__restrict__ meta,
                                                      const uint32_t *__restrict__ start,
-                                                     const float4 *__restrict__ s0, int n,
+                                                     const float2 *__restrict__ s0,
+                                                     const float4 *__restrict__ s1, int n,
                                                      OverlapPart *__restrict__ part)
 {
     const int s = blockIdx.x * kBlock + threadIdx.x;
@@ -391,13 +394,13 @@ __global__ __launch_bounds__(kBlock) void k_overlap(const GridMeta *__restrict__
     double gap = INFINITY;
     if (s < n) {
         const GridMeta g = *meta;
-        const float4 me = s0[s];
-        const int self = __float_as_int(me.z);
+        const float2 me = s0[s];
+        const double r = (double)s1[s].w;
         dev::scan_disc(g, start, s0, (double)me.x, (double)me.y, g.rn2,
-                       [&](const float4 &a, uint32_t, bool valid) {
+                       [&](const float2 &a, uint32_t k, bool valid) {
                            const double d2 = dev::nb_key(me.x, me.y, a.x, a.y);
-                           if (valid && d2 < g.rn2 && __float_as_int(a.z) != self) {
-                               const double rr = (double)me.w + (double)a.w;
+                           if (valid && d2 < g.rn2 && k != (uint32_t)s) {
+                               const double rr = r + (double)s1[k].w;
                                cnt += d2 < rr * rr ? 1u : 0u;
                                gap = fmin(gap, sqrt(d2) - rr);
                            }
@@ -513,7 +516,7 @@ hipError_t launch_spawn(const orca_agents_buf &state, int n, const orca_agents_i
     const int ncb = (n_cand + kBlock - 1) / kBlock;
     if (ncb > 0) {
         hipLaunchKernelGGL(k_spawn_check, dim3(ncb), dim3(kBlock), 0, stream, cand, n_cand,
-                           (const float *)state.max_speed, w.meta, w.start, w.s0, b.bounds,
+                           (const float *)state.max_speed, w.meta, w.start, w.s0, w.s1, b.bounds,
                            t_clear, n, b.blocked, b.conf_count);
         const int chunks = (ncb + kPairChunk - 1) / kPairChunk;
         hipLaunchKernelGGL(k_spawn_pairs, dim3(ncb, chunks), dim3(kBlock), 0, stream, cand,
@@ -542,7 +545,7 @@ hipError_t launch_overlap_stats(const orca_agents_in &in, int n, float reach, do
         const hipError_t e = launch_grid_build_rn(in, n, reach, 0.0f, nullptr, L, w, stream);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_overlap, dim3(nb), dim3(kBlock), 0, stream, w.meta, w.start, w.s0,
-                           n, part);
+                           w.s1, n, part);
     }
     hipLaunchKernelGGL(k_overlap_final, dim3(1), dim3(kBlock), 0, stream, part, nb, out);
     return hipGetLastError();

@@ -109,13 +109,29 @@ struct KnnShape {
     static constexpr int kCap = 2 * kSlots;       // buffer entries per lane
 };
 
-// Widening of the kept K-th neighbour distance before the counting pass, in
-// speed steps (v_max dt).  The result never depends on it (a circle holding
-// fewer than K is rescanned whole); it trades rescans against candidates.
-#ifndef ORCA_GUESS_SPEED_STEPS
-#define ORCA_GUESS_SPEED_STEPS 2.0
-#endif
-constexpr double kGuessSpeedSteps = ORCA_GUESS_SPEED_STEPS;
+// Words of the sorting network for K nearest.
+template <int K>
+struct SortNet {
+    static constexpr int N = K <= 8 ? 16 : (K <= 24 ? 32 : 64);
+};
+
+// Each agent keeps from step to step a radius that is expected to hold its K
+// nearest and little more (never a part of the result: a circle that holds
+// fewer is widened, one that holds too many is cut by counting).  Where the
+// entries of a circle were sorted, it is the distance of the agent kMore
+// places behind the K-th: a step changes who is inside by a few.  (A margin on
+// the K-th distance, two speed steps, holds 32 and more in a crossing's dense
+// parts: counted and scanned again there, 430 us per step over steps 10-110 of
+// the 1M crossing.  By number, with kMore at 2, 3, 4 and 5: 382, 363, 362 and
+// 363 us.)
+constexpr int kKeptMore = 4;
+template <int K>
+struct KeptShape {
+    static constexpr int kFit = SortNet<K>::N < KnnShape<K>::kCap ? SortNet<K>::N
+                                                                  : KnnShape<K>::kCap - 1;
+    static constexpr int kRoom = (kFit - K - 1) / 2;
+    static constexpr int kMore = kRoom < kKeptMore ? kRoom : kKeptMore;
+};
 
 // Hard lines of a vehicle's own motion limits: the acceleration octagon (see
 // accel_line) and the two sides of the heading wedge (see turn_wedge).
@@ -168,17 +184,17 @@ __device__ __forceinline__ uint32_t entry_pos(uint64_t e) { return (uint32_t)e &
 __device__ __forceinline__ uint32_t entry_bin(uint64_t e) { return (uint32_t)e >> kPosBits; }
 
 // Strict (key, caller index) order of two buffer entries.
-__device__ __forceinline__ bool entry_less(uint64_t ea, uint64_t eb, const float4 *__restrict__ s0,
-                                           float xi, float yi)
+__device__ __forceinline__ bool entry_less(uint64_t ea, uint64_t eb, const float2 *__restrict__ s0,
+                                           const float4 *__restrict__ s1, float xi, float yi)
 {
     const uint32_t ha = (uint32_t)(ea >> 32), hb = (uint32_t)(eb >> 32);
     if (ha != hb) return ha < hb;
-    const float4 ca = s0[entry_pos(ea)];
-    const float4 cb = s0[entry_pos(eb)];
+    const float2 ca = s0[entry_pos(ea)];
+    const float2 cb = s0[entry_pos(eb)];
     const double ka = nb_key(xi, yi, ca.x, ca.y);
     const double kb = nb_key(xi, yi, cb.x, cb.y);
     if (ka != kb) return ka < kb;
-    return __float_as_int(ca.z) < __float_as_int(cb.z);
+    return tag_index(s1[entry_pos(ea)].z) < tag_index(s1[entry_pos(eb)].z);
 }
 
 // Candidates loaded per group by one lane.
@@ -188,49 +204,86 @@ __device__ __forceinline__ bool entry_less(uint64_t ea, uint64_t eb, const float
 constexpr int kScanUnroll = ORCA_SCAN_UNROLL;
 static_assert(kScanUnroll <= kScanPad, "candidate groups may read at most kScanPad past s0");
 
+// A group of positions, two to a 16-byte load (of 8-byte alignment).
+__device__ __forceinline__ void load_group(const float2 *p, float2 (&c)[kScanUnroll])
+{
+    typedef float Pair __attribute__((ext_vector_type(4), aligned(8)));
+    static_assert(kScanUnroll % 2 == 0, "positions are loaded in pairs");
+    const Pair *pp = (const Pair *)p;
+#pragma unroll
+    for (int q = 0; q < kScanUnroll / 2; ++q) {
+        const Pair v = pp[q];
+        c[2 * q] = make_float2(v.x, v.y);
+        c[2 * q + 1] = make_float2(v.z, v.w);
+    }
+}
+
 struct NoGroupEnd {
     __device__ __forceinline__ void operator()() const {}
 };
 
-// Grid rows that can hold an agent within sqrt(r2) of y (r2 <= R_n^2).
-__device__ __forceinline__ void row_span(const GridMeta &g, double yd, double r2, int &ya, int &yb)
+// A disc in cell units around a point: the cell (cx, cy) that holds the
+// centre, the centre's place (fx, fy) in it, and the radius rp.  The cell and
+// the place are formed in double; rp is widened by a relative 1e-6 and by
+// 1e-4 cells, so that everything derived from it in FP32 (whose rounding is a
+// few 1e-7 of rp, and a few 1e-7 rp^2 in a half chord squared, against the
+// widening's 2e-4 rp + 2e-6 rp^2) covers the exact disc.  Which cells are
+// scanned changes no result, only the test of each key does.  (Rows and
+// chords in double, two conversions, a square root and two floors each,
+// were a third of the scan's instructions.)
+struct CellDisc {
+    int cx, cy;
+    float fx, fy, rp;
+};
+
+__device__ __forceinline__ CellDisc cell_disc(const GridMeta &g, double xd, double yd, double r2)
 {
-    const double r = sqrt(r2);
-    const double ua = floor((yd - r - (double)g.y0) * g.inv_cs - 1e-6);
-    const double ub = floor((yd + r - (double)g.y0) * g.inv_cs + 1e-6);
-    ya = (int)fmin(fmax(ua, 0.0), (double)(g.ny - 1));
-    yb = (int)fmin(fmax(ub, 0.0), (double)(g.ny - 1));
+    CellDisc d;
+    // the bounds keep every sum below in int's range, and map NaN to a bound
+    const double ux = fmin(fmax((xd - (double)g.x0) * g.inv_cs, -1e9), 1e9);
+    const double uy = fmin(fmax((yd - (double)g.y0) * g.inv_cs, -1e9), 1e9);
+    const double cx = floor(ux), cy = floor(uy);
+    d.cx = (int)cx;
+    d.cy = (int)cy;
+    d.fx = (float)(ux - cx);
+    d.fy = (float)(uy - cy);
+    d.rp = fminf((float)(sqrt(r2) * g.inv_cs) * 1.000001f + 1e-4f, 1e9f);
+    return d;
 }
 
-// Cell indices [xa, xb] of row yy's cells that meet the chord of the circle
-// of squared radius r2 around (xd, yd) (FP64, with 1e-6-cell margins);
-// false when the chord misses the row (xa = xb = the column of xd then).
-// Returns the offsets of the two `start` entries that bound the row's range.
-__device__ __forceinline__ bool row_cells(const GridMeta &g, double xd, double yd, double r2, int yy,
-                                          int &ia, int &ib)
+__device__ __forceinline__ int clamp_cell(int c, int n) { return max(min(c, n - 1), 0); }
+
+// Grid rows that can hold an agent of the disc.
+__device__ __forceinline__ void row_span(const GridMeta &g, const CellDisc &d, int &ya, int &yb)
 {
-    const double ylo = (double)g.y0 + (double)yy * g.cs_d;
-    const double dy = fmax(fmax(ylo - yd, yd - (ylo + g.cs_d)) - 1e-6 * g.cs_d, 0.0);
-    const double h2 = r2 - dy * dy;
-    const bool meets = h2 > 0.0;
-    const double hw = meets ? sqrt(h2) : 0.0;
-    const double ua = floor((xd - hw - (double)g.x0) * g.inv_cs - 1e-6);
-    const double ub = floor((xd + hw - (double)g.x0) * g.inv_cs + 1e-6);
-    const int xa = (int)fmin(fmax(ua, 0.0), (double)(g.nx - 1));
-    const int xb = (int)fmin(fmax(ub, 0.0), (double)(g.nx - 1));
+    ya = clamp_cell(d.cy + (int)floorf(d.fy - d.rp), g.ny);
+    yb = clamp_cell(d.cy + (int)floorf(d.fy + d.rp), g.ny);
+}
+
+// Row yy's cells that meet the disc's chord, as the offsets of the two
+// `start` entries that bound their range; false when the chord misses the
+// row (the centre's column then).
+__device__ __forceinline__ bool row_cells(const GridMeta &g, const CellDisc &d, int yy, int &ia,
+                                          int &ib)
+{
+    const float o = (float)(yy - d.cy);
+    const float dy = fmaxf(fmaxf(o - d.fy, d.fy - o - 1.0f), 0.0f);
+    const float h2 = d.rp * d.rp - dy * dy;
+    const bool meets = h2 > 0.0f;
+    // the hardware square root: 1 ulp is far below the widening
+    const float hw = meets ? __builtin_amdgcn_sqrtf(h2) : 0.0f;
     const int row = g.cell_base + yy * g.nx;
-    ia = row + xa;
-    ib = row + xb + 1;
+    ia = row + clamp_cell(d.cx + (int)floorf(d.fx - hw), g.nx);
+    ib = row + clamp_cell(d.cx + (int)floorf(d.fx + hw), g.nx) + 1;
     return meets;
 }
 
 // Cell-order range of row yy clipped to the chord; false when empty.
 __device__ __forceinline__ bool row_range(const GridMeta &g, const uint32_t *__restrict__ start,
-                                          double xd, double yd, double r2, int yy, uint32_t &a,
-                                          uint32_t &b)
+                                          const CellDisc &d, int yy, uint32_t &a, uint32_t &b)
 {
     int ia, ib;
-    if (!row_cells(g, xd, yd, r2, yy, ia, ib)) return false;
+    if (!row_cells(g, d, yy, ia, ib)) return false;
     a = start[ia];
     b = start[ib];
     if (b > g.seg_end) b = g.seg_end;  // defensive: stay inside the scene
@@ -241,11 +294,6 @@ __device__ __forceinline__ bool row_range(const GridMeta &g, const uint32_t *__r
 // ascending; every index is a compile-time constant.
 // Largest fixed-point sort key: 26 bits above the 6-bit buffer slot.
 constexpr uint32_t kSortKeyMax = (1u << 26) - 1u;
-
-template <int K>
-struct SortNet {
-    static constexpr int N = K <= 8 ? 16 : (K <= 24 ? 32 : 64);
-};
 
 template <int N>
 __device__ __forceinline__ void cas(uint32_t (&e)[N], int i, int l)
@@ -297,17 +345,18 @@ __device__ __forceinline__ void sort_network(uint32_t (&e)[N])
 template <class H>
 __device__ __forceinline__ void scan_disc_groups(const GridMeta &g,
                                                  const uint32_t *__restrict__ start,
-                                                 const float4 *__restrict__ s0, double xd,
+                                                 const float2 *__restrict__ s0, double xd,
                                                  double yd, double r2, H &&group)
 {
+    const CellDisc disc = cell_disc(g, xd, yd, r2);
     int yr, yb;
-    row_span(g, yd, r2, yr, yb);
+    row_span(g, disc, yr, yb);
     // The range of row yr is loaded into one of two register pairs while the
     // other pair, loaded a pass earlier, is consumed (the two swap roles every
     // pass, so a load never lands in a register that is still being read);
     // rm: row yr's chord meets the row; (ia, ib): its `start` offsets.
     int ia, ib;
-    bool rm = row_cells(g, xd, yd, r2, yr, ia, ib);
+    bool rm = row_cells(g, disc, yr, ia, ib);
     uint32_t pa[2], pb[2];
     pa[0] = start[ia];
     pb[0] = start[ib];
@@ -327,7 +376,7 @@ __device__ __forceinline__ void scan_disc_groups(const GridMeta &g,
             en = pb[P] < g.seg_end ? pb[P] : g.seg_end;  // defensive: stay inside the scene
             if (!rm || !(tn < en)) en = tn;              // an empty row: no valid member
             ++yr;
-            if (yr <= yb) rm = row_cells(g, xd, yd, r2, yr, ia, ib);
+            if (yr <= yb) rm = row_cells(g, disc, yr, ia, ib);
         }
         pa[1 - P] = start[ia];
         pb[1 - P] = start[ib];
@@ -335,33 +384,21 @@ __device__ __forceinline__ void scan_disc_groups(const GridMeta &g,
     };
     // two register groups used in turn, so no group is copied; components a
     // visitor does not read are never loaded
-    float4 c[kScanUnroll], d[kScanUnroll];
+    float2 c[kScanUnroll], d[kScanUnroll];
     uint32_t t0 = 0, e0 = 0;
     next_group(0, 0u, 0u, t0, e0);  // row yr exists: yr <= yb here
-    {
-        const float4 *pc = s0 + t0;
-#pragma unroll
-        for (int q = 0; q < kScanUnroll; ++q) c[q] = pc[q];
-    }
+    load_group(s0 + t0, c);
     for (;;) {
         uint32_t t1, e1;
         const bool more1 = next_group(1, t0, e0, t1, e1);
-        {
-            const float4 *pd = s0 + (more1 ? t1 : t0);
-#pragma unroll
-            for (int q = 0; q < kScanUnroll; ++q) d[q] = pd[q];
-        }
+        load_group(s0 + (more1 ? t1 : t0), d);
         // keep the loads ahead of the visit (the scheduler would otherwise
         // move them next to their use)
         __builtin_amdgcn_sched_barrier(0);
         group(c, t0, e0);
         if (!more1) break;
         const bool more2 = next_group(0, t1, e1, t0, e0);
-        {
-            const float4 *pc = s0 + (more2 ? t0 : t1);
-#pragma unroll
-            for (int q = 0; q < kScanUnroll; ++q) c[q] = pc[q];
-        }
+        load_group(s0 + (more2 ? t0 : t1), c);
         __builtin_amdgcn_sched_barrier(0);
         group(d, t1, e1);
         if (!more2) break;
@@ -378,43 +415,155 @@ __device__ __forceinline__ void scan_disc_groups(const GridMeta &g,
 // member of a group, then group_end().
 template <class F, class G = NoGroupEnd>
 __device__ __forceinline__ void scan_disc(const GridMeta &g, const uint32_t *__restrict__ start,
-                                          const float4 *__restrict__ s0, double xd, double yd,
+                                          const float2 *__restrict__ s0, double xd, double yd,
                                           double r2, F &&visit, G &&group_end = G())
 {
     scan_disc_groups(g, start, s0, xd, yd, r2,
-                     [&](const float4 (&c)[kScanUnroll], uint32_t t0, uint32_t e) {
+                     [&](const float2 (&c)[kScanUnroll], uint32_t t0, uint32_t e) {
 #pragma unroll
                          for (int q = 0; q < kScanUnroll; ++q) visit(c[q], t0 + q, t0 + q < e);
                          group_end();
                      });
 }
 
-// Selects the (at most K) nearest agents of the lane into entries [0, m) of
-// its LDS buffer, ascending; returns m.  rg2 (<= R_n^2) is a guess of a
-// squared radius that holds at least K candidates (from the previous step):
-// the counting pass first covers only that circle and falls back to the
-// whole neighbour circle when it holds fewer than K, so the result never
-// depends on the guess.
+// Orders the `take` entries of the lane's buffer, its own agent's (position
+// spos, key 0) among them, and leaves the nearest K others at least, ascending,
+// in entries [0, min(take - 1, K)).
+//
+// A sorting network in registers when the entries fit it, over 32-bit words
+// (the FP32 key in 26-bit fixed point of r2c, above the entry's buffer
+// slot); the nearest entries are then gathered by slot.  The fixed-point key
+// is non-decreasing in the FP32 key, which is non-decreasing in the FP64 key,
+// so distinct fixed-point keys are in (FP64 key) order; a tie among the
+// entries that decide the result needs the (FP64 key, caller index) order
+// of entry_less, left to the insertion pass (the buffer is then untouched).
+// `next` becomes the distance of the entry kMore places behind the K-th
+// where there is one.  Without a tie the own entry, key 0, comes first.  Loads and stores are not
+// bounded by the lane's count: the words past it sort last and in slot order
+// (also behind a key of kSortKeyMax, whose slot is lower), so the first K + 1
+// words name slots below kCap.
 template <int K, int BLOCK>
-__device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
-                          const float4 *__restrict__ s0, float xi, float yi, int self,
-                          uint32_t spos, uint64_t *buf, int tid, double rg2)
+__device__ __forceinline__ void sort_entries(const float2 *__restrict__ s0,
+                                             const float4 *__restrict__ s1, float xi, float yi,
+                                             uint32_t spos, uint64_t *buf, int tid, uint32_t take,
+                                             double r2c, float &next)
+{
+    constexpr int N = SortNet<K>::N;
+    constexpr int kCap = KnnShape<K>::kCap;
+    static_assert(N <= 64, "buffer slots must fit six bits");
+    static_assert(K + 1 <= N && K + 1 <= kCap, "room for K entries and the lane's own");
+    if (take <= (uint32_t)N) {
+        const float qscale = 67108864.0f / (float)r2c;  // 2^26 / r2c
+        uint32_t e[N];
+#pragma unroll
+        for (int p = 0; p < N; ++p) {
+            if (p < kCap) {
+                const float fk = __uint_as_float((uint32_t)(buf[buf_idx<BLOCK>(p, tid)] >> 32));
+                // clamp in the integer domain: the FP32 product reaches
+                // 2^26 for keys within a few 1e-8 (relative) below r2c,
+                // and 2^26 - 1 has no FP32 value to clamp to
+                const uint32_t q = min((uint32_t)(fk * qscale), kSortKeyMax);
+                e[p] = (p < (int)take ? q << 6 : ~63u) | (uint32_t)p;
+            } else {
+                e[p] = ~63u | (uint32_t)p;
+            }
+        }
+        sort_network<N>(e);
+        bool tie = false;
+#pragma unroll
+        for (int p = 0; p + 1 < N; ++p)
+            tie = tie || (p <= K && p + 1 < (int)take && (e[p] >> 6) == (e[p + 1] >> 6));
+        if (!tie) {
+            uint64_t got[K];
+#pragma unroll
+            for (int p = 0; p < K; ++p) got[p] = buf[buf_idx<BLOCK>((int)(e[p + 1] & 63u), tid)];
+            constexpr int kAt = K + KeptShape<K>::kMore;
+            if (kAt < (int)take)
+                next = sqrtf(__uint_as_float(
+                    (uint32_t)(buf[buf_idx<BLOCK>((int)(e[kAt] & 63u), tid)] >> 32)));
+#pragma unroll
+            for (int p = 0; p < K; ++p) buf[buf_idx<BLOCK>(p, tid)] = got[p];
+            return;
+        }
+    }
+    // drop the own entry: those after it move up one slot
+    uint32_t w = 0;
+    for (uint32_t e = 0; e < take; ++e) {
+        const uint64_t ent = buf[buf_idx<BLOCK>((int)e, tid)];
+        buf[buf_idx<BLOCK>((int)w, tid)] = ent;
+        w += entry_pos(ent) != spos ? 1u : 0u;
+    }
+    for (int p = 1; p < (int)take - 1; ++p) {
+        const uint64_t e = buf[buf_idx<BLOCK>(p, tid)];
+        int q = p - 1;
+        while (q >= 0) {
+            const uint64_t f = buf[buf_idx<BLOCK>(q, tid)];
+            if (!entry_less(e, f, s0, s1, xi, yi)) break;
+            buf[buf_idx<BLOCK>(q + 1, tid)] = f;
+            --q;
+        }
+        buf[buf_idx<BLOCK>(q + 1, tid)] = e;
+    }
+}
+
+// Collects into the lane's buffer a set that holds its K nearest within R_n
+// (or all, when there are fewer) and its own agent; returns the number of
+// entries, or 0 when no such set fits the buffer, and the squared radius r2c
+// that bounds their keys.  rg2 (<= R_n^2) is a guess of a squared radius that
+// holds at least K candidates; with `kept` (from the previous step) it is
+// expected to hold little more.  A circle that holds fewer than K is widened
+// to the whole neighbour circle, so the result never depends on the guess.
+//
+// The lane's own agent is scanned as any other (key 0, bin 0), which keeps
+// the test for it out of the loops.
+template <int K, int BLOCK>
+__device__ __forceinline__ uint32_t knn_collect(const GridMeta &g,
+                                                const uint32_t *__restrict__ start,
+                                                const float2 *__restrict__ s0, float xi, float yi,
+                                                uint64_t *buf, int tid, double rg2, bool kept,
+                                                double &r2c)
 {
     constexpr int kCap = KnnShape<K>::kCap;
     const double xd = xi, yd = yi;
-    lane_order<BLOCK>();  // other lanes' half-planes of a previous tile are read
+    r2c = rg2 < g.rn2 ? rg2 : g.rn2;
+    // A kept circle: every candidate in range is stored, and that is the set
+    // when all fit.  (The counting pass below, with a bin and two counters per
+    // candidate, is needed only to cut a circle that holds too many.)
+    constexpr uint32_t kFit = (uint32_t)KeptShape<K>::kFit;
+    if (kept) {
+        uint32_t n = 0;
+        scan_disc_groups(
+            g, start, s0, xd, yd, r2c,
+            [&](const float2 (&c)[kScanUnroll], uint32_t t0, uint32_t e) {
+                // the keys of the whole group first (independent of one
+                // another, so their FP64 chains interleave), then the buffer
+                // in member order
+                double key[kScanUnroll];
+#pragma unroll
+                for (int q = 0; q < kScanUnroll; ++q) key[q] = nb_key(xi, yi, c[q].x, c[q].y);
+                // branch-free, so that the candidates of a group form one
+                // block: every candidate is written at the next free slot
+                // and kept only when in range; once the buffer is full the
+                // writes land on its last slot, the only one they can
+                // overwrite
+#pragma unroll
+                for (int q = 0; q < kScanUnroll; ++q) {
+                    const int slot = (int)min(n, (uint32_t)(kCap - 1));
+                    buf[buf_idx<BLOCK>(slot, tid)] = pack_entry(key[q], t0 + q);
+                    n += t0 + q < e && key[q] < r2c ? 1u : 0u;
+                }
+            });
+        if (n <= kFit && (n > (uint32_t)K || !(r2c < g.rn2))) return n;
+        if (n <= (uint32_t)K) r2c = g.rn2;  // too few: count them all
+    }
     // pass 1: per-bin counts of the keys below r2c in kBins equal-area bins,
-    // and the candidates themselves while they fit the buffer.  The lane's
-    // own agent is counted (and stored) too -- it is always scanned, with
-    // key 0, in bin 0 -- and taken out afterwards, which keeps the index
-    // test out of this loop.
-    double r2c = rg2 < g.rn2 ? rg2 : g.rn2;
+    // and the candidates themselves while they fit the buffer.
     double bscale;
     // Counts per bin: 4-bit counters of one group of candidates in `nib`
     // (a group adds at most kScanUnroll <= 15 to a bin), widened after each
     // group into byte counters, even bins in `hev` (byte k: bin 2k) and odd
     // bins in `hod` (byte k: bin 2k + 1); bytes cannot overflow either, since
-    // a lane with more than 255 candidates takes the exact fallback below.
+    // a lane with more than 255 candidates takes the exact fallback.
     static_assert(kScanUnroll <= 15, "a group must fit the 4-bit counters");
     uint64_t hev, hod, nib;
     uint32_t total;
@@ -426,10 +575,7 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
         total = 0;
         scan_disc_groups(
             g, start, s0, xd, yd, r2c,
-            [&](const float4 (&c)[kScanUnroll], uint32_t t0, uint32_t e) {
-                // the keys of the whole group first (independent of one
-                // another, so their FP64 chains interleave), then the
-                // counters and the buffer in member order
+            [&](const float2 (&c)[kScanUnroll], uint32_t t0, uint32_t e) {
                 double key[kScanUnroll];
                 int bin[kScanUnroll];
                 bool in[kScanUnroll];
@@ -445,11 +591,6 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
 #pragma unroll
                 for (int q = 0; q < kScanUnroll; ++q) {
                     nib += (uint64_t)(in[q] ? 1u : 0u) << (bin[q] * 4);
-                    // branch-free, so that the candidates of a group form one
-                    // block: every candidate is written at the next free slot
-                    // and kept only when in range; once the buffer is full the
-                    // writes land on its last slot, the only one they can
-                    // overwrite
                     const int slot = total < (uint32_t)(kCap - 1) ? (int)total : kCap - 1;
                     buf[buf_idx<BLOCK>(slot, tid)] = pack_entry(key[q], t0 + q, (uint32_t)bin[q]);
                     total += in[q] ? 1u : 0u;
@@ -458,23 +599,21 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
                 hod += (nib >> 4) & 0x0F0F0F0F0F0F0F0Full;
                 nib = 0;
             });
-        hev -= 1ull;  // the lane's own entry, key 0, bin 0
-        total -= 1u;
-        if (total >= (uint32_t)K || !(r2c < g.rn2)) break;
+        if (total > (uint32_t)K || !(r2c < g.rn2)) break;
         r2c = g.rn2;  // the guessed circle holds fewer than K: count them all
     }
-    // every candidate of the circle (and the lane's own entry) is in the
-    // buffer, below its last slot
-    const bool captured = total + 1u <= (uint32_t)(kCap - 1);
+    // every candidate of the circle is in the buffer, below its last slot
+    const bool captured = total <= (uint32_t)(kCap - 1);
 
     // threshold bin b*: the first bin at which the cumulative count reaches K
+    // others
     uint32_t cum = 0, take = 0;
     int bstar = kBins - 1;
     bool found = false;
 #pragma unroll
     for (int b = 0; b < kBins; ++b) {
         cum += (uint32_t)((((b & 1) ? hod : hev) >> ((b >> 1) * 8)) & 0xffull);
-        if (!found && cum >= (uint32_t)K) {
+        if (!found && cum > (uint32_t)K) {
             found = true;
             bstar = b;
             take = cum;
@@ -482,102 +621,70 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
     }
     if (!found) take = total;
 
-    if (total <= 255u && take <= (uint32_t)kCap) {
-        if (captured) {
-            // the candidates of bins <= b* are already in the buffer: keep
-            // them in place, dropping the lane's own entry.  Branch-free: each
-            // entry is written at the next kept position, which never passes
-            // the one being read, and the position advances only for kept
-            // entries
-            uint32_t w = 0;
-            for (uint32_t e = 0; e <= total; ++e) {
-                const uint64_t ent = buf[buf_idx<BLOCK>((int)e, tid)];
-                buf[buf_idx<BLOCK>((int)w, tid)] = ent;
-                w += (entry_pos(ent) != spos && (int)entry_bin(ent) <= bstar) ? 1u : 0u;
-            }
-        } else {
-            // pass 2: collect the candidates of bins <= b*, in scan order.  For
-            // b* below the last bin, bin <= b* is exactly key * bscale < b* + 1
-            // (truncation of a non-negative value), so both passes count alike.
-            // Every such key is below (b* + 1) R_n^2 / kBins, so only rows and
-            // chords of that smaller circle are visited (with a relative margin
-            // far above the rounding of key * bscale).
-            const bool last = bstar + 1 >= kBins;
-            const double bnext = last ? INFINITY : (double)(bstar + 1);
-            const double r2 = last ? r2c : (double)(bstar + 1) * (r2c / (double)kBins) * (1.0 + 1e-9);
-            uint32_t slot = 0;
-            scan_disc(g, start, s0, xd, yd, r2, [&](const float4 &c, uint32_t t, bool valid) {
-                const double key = nb_key(xi, yi, c.x, c.y);
-                if (valid && key < r2c && key * bscale < bnext && __float_as_int(c.z) != self) {
-                    if (slot < (uint32_t)kCap)  // always true: both passes count alike
-                        buf[buf_idx<BLOCK>((int)slot, tid)] = pack_entry(key, t);
-                    ++slot;
-                }
-            });
+    if (total > 255u || take > (uint32_t)kCap) return 0;
+    // the circle that holds bins <= b* (with a relative margin far above the
+    // rounding of key * bscale)
+    const bool last = bstar + 1 >= kBins;
+    const double r2 = last ? r2c : (double)(bstar + 1) * (r2c / (double)kBins) * (1.0 + 1e-9);
+    if (captured) {
+        // the candidates of bins <= b* are already in the buffer: keep them in
+        // place.  Branch-free: each entry is written at the next kept
+        // position, which never passes the one being read, and the position
+        // advances only for kept entries
+        uint32_t w = 0;
+        for (uint32_t e = 0; e < total; ++e) {
+            const uint64_t ent = buf[buf_idx<BLOCK>((int)e, tid)];
+            buf[buf_idx<BLOCK>((int)w, tid)] = ent;
+            w += (int)entry_bin(ent) <= bstar ? 1u : 0u;
         }
-        // order: a sorting network in registers when the entries fit it,
-        // over 32-bit words (the FP32 key in 26-bit fixed point of r2c, above
-        // the entry's buffer slot); the nearest K entries are then gathered
-        // by slot.  The fixed-point key is non-decreasing in the FP32 key,
-        // which is non-decreasing in the FP64 key, so distinct fixed-point
-        // keys are in (FP64 key) order; a tie among the entries that decide
-        // the result needs the (FP64 key, caller index) order of entry_less,
-        // left to the insertion pass below (the buffer is then untouched).
-        constexpr int N = SortNet<K>::N;
-        static_assert(N <= 64, "buffer slots must fit six bits");
-        bool sorted = false;
-        if (take <= (uint32_t)N) {
-            const float qscale = 67108864.0f / (float)r2c;  // 2^26 / r2c
-            uint32_t e[N];
-#pragma unroll
-            for (int p = 0; p < N; ++p) {
-                uint32_t w = ~0u;
-                if (p < (int)take) {
-                    const float fk = __uint_as_float(
-                        (uint32_t)(buf[buf_idx<BLOCK>(p, tid)] >> 32));
-                    // clamp in the integer domain: the FP32 product reaches
-                    // 2^26 for keys within a few 1e-8 (relative) below r2c,
-                    // and 2^26 - 1 has no FP32 value to clamp to
-                    const uint32_t q = min((uint32_t)(fk * qscale), kSortKeyMax);
-                    w = (q << 6) | (uint32_t)p;
-                }
-                e[p] = w;
+    } else {
+        // pass 2: collect the candidates of bins <= b*, in scan order.  For
+        // b* below the last bin, bin <= b* is exactly key * bscale < b* + 1
+        // (truncation of a non-negative value), so both passes count alike.
+        // Every such key is below r2, so only rows and chords of that smaller
+        // circle are visited.
+        const double bnext = last ? INFINITY : (double)(bstar + 1);
+        uint32_t slot = 0;
+        scan_disc(g, start, s0, xd, yd, r2, [&](const float2 &c, uint32_t t, bool valid) {
+            const double key = nb_key(xi, yi, c.x, c.y);
+            if (valid && key < r2c && key * bscale < bnext) {
+                if (slot < (uint32_t)kCap)  // always true: both passes count alike
+                    buf[buf_idx<BLOCK>((int)slot, tid)] = pack_entry(key, t);
+                ++slot;
             }
-            sort_network<N>(e);
-            bool tie = false;
-#pragma unroll
-            for (int p = 0; p + 1 < N; ++p)
-                tie = tie || (p < K && p + 1 < (int)take && (e[p] >> 6) == (e[p + 1] >> 6));
-            if (!tie) {
-                uint64_t got[K];
-#pragma unroll
-                for (int p = 0; p < K; ++p)
-                    if (p < (int)take) got[p] = buf[buf_idx<BLOCK>((int)(e[p] & 63u), tid)];
-#pragma unroll
-                for (int p = 0; p < K; ++p)
-                    if (p < (int)take) buf[buf_idx<BLOCK>(p, tid)] = got[p];
-                sorted = true;
-            }
-        }
-        if (!sorted) {
-            for (int p = 1; p < (int)take; ++p) {
-                const uint64_t e = buf[buf_idx<BLOCK>(p, tid)];
-                int q = p - 1;
-                while (q >= 0) {
-                    const uint64_t f = buf[buf_idx<BLOCK>(q, tid)];
-                    if (!entry_less(e, f, s0, xi, yi)) break;
-                    buf[buf_idx<BLOCK>(q + 1, tid)] = f;
-                    --q;
-                }
-                buf[buf_idx<BLOCK>(q + 1, tid)] = e;
-            }
-        }
-        return take < (uint32_t)K ? (int)take : K;
+        });
     }
+    r2c = r2;
+    return take;
+}
 
+// Selects the (at most K) nearest agents of the lane into entries [0, m) of
+// its LDS buffer, ascending; returns m.  `keep` (nullable): the agent's kept
+// radius, 0 for none; the counting pass starts from the whole neighbour
+// circle then.
+template <int K, int BLOCK>
+__device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
+                          const float2 *__restrict__ s0, const float4 *__restrict__ s1, float xi,
+                          float yi, uint32_t spos, uint64_t *buf, int tid, float *keep)
+{
+    const double xd = xi, yd = yi;
+    const float last = keep ? *keep : 0.0f;
+    const bool kept = last > 0.0f;
+    const double rg2 = kept ? (double)last * (double)last : g.rn2;
+    lane_order<BLOCK>();  // other lanes' half-planes of a previous tile are read
+    double r2c;
+    const uint32_t take = knn_collect<K, BLOCK>(g, start, s0, xi, yi, buf, tid, rg2, kept, r2c);
+    if (take) {
+        // a circle of fewer entries is widened by their share
+        float next = (float)sqrt(r2c) * sqrtf((float)(K + 1 + KeptShape<K>::kMore) / (float)take);
+        sort_entries<K, BLOCK>(s0, s1, xi, yi, spos, buf, tid, take, r2c, next);
+        if (keep) *keep = fminf(next, g.rn);
+        return (int)min(take - 1u, (uint32_t)K);
+    }
     // fallback: repeated minimum over all candidates, strictly above the last pick
+    const CellDisc disc = cell_disc(g, xd, yd, g.rn2);
     int ya, yb;
-    row_span(g, yd, g.rn2, ya, yb);
+    row_span(g, disc, ya, yb);
     double lk = -1.0;
     int lj = -1;
     int m = 0;
@@ -587,14 +694,14 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
         uint32_t bt = 0;
         for (int yy = ya; yy <= yb; ++yy) {
             uint32_t ra, rb;
-            if (!row_range(g, start, xd, yd, g.rn2, yy, ra, rb)) continue;
+            if (!row_range(g, start, disc, yy, ra, rb)) continue;
             for (uint32_t t = ra; t < rb; ++t) {
-                const float4 c = s0[t];
-                const int j = __float_as_int(c.z);
+                const float2 c = s0[t];
+                const int j = tag_index(s1[t].z);
                 const double key = nb_key(xi, yi, c.x, c.y);
                 const bool above = key > lk || (key == lk && j > lj);
                 const bool below = key < bk || (key == bk && j < bj);
-                if (key < g.rn2 && j != self && above && below) {
+                if (key < g.rn2 && t != spos && above && below) {
                     bk = key;
                     bj = j;
                     bt = t;
@@ -606,6 +713,7 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
         lk = bk;
         lj = bj;
     }
+    if (keep) *keep = 0.0f;
     return m;
 }
 
@@ -1466,7 +1574,7 @@ __device__ __host__ __forceinline__ SceneP scene_params(const orca_params &p)
 // flight together; the half-planes of the group follow.
 template <int K, int BLOCK>
 __device__ __forceinline__ void build_halfplanes(const uint32_t (&pos)[K], int m,
-                                                 const float4 *__restrict__ s0,
+                                                 const float2 *__restrict__ s0,
                                                  const float4 *__restrict__ s1, float xi,
                                                  float yi, float vxi, float vyi, float ri, int i,
                                                  int ci, const SceneP &p, float4 *lines, int tid)
@@ -1477,7 +1585,8 @@ __device__ __forceinline__ void build_halfplanes(const uint32_t (&pos)[K], int m
     lane_order<BLOCK>();  // every lane's selection entries are read
 #pragma unroll
     for (int q0 = 0; q0 < K; q0 += kHpGroup) {
-        float4 b0[kHpGroup], b1[kHpGroup];
+        float2 b0[kHpGroup];
+        float4 b1[kHpGroup];
 #pragma unroll
         for (int u = 0; u < kHpGroup; ++u) {
             if (q0 + u < K) {
@@ -1489,10 +1598,10 @@ __device__ __forceinline__ void build_halfplanes(const uint32_t (&pos)[K], int m
         for (int u = 0; u < kHpGroup; ++u) {
             const int q = q0 + u;
             if (q < K && q < m) {
-                const float f = (__float_as_int(b1[u].z) & 1) ? fb : fa;
+                const float f = tag_class(b1[u].z) ? fb : fa;
                 lines[q * BLOCK + tid] =
-                    halfplane(xi, yi, vxi, vyi, ri, b0[u].x, b0[u].y, b1[u].x, b1[u].y, b0[u].w,
-                              f, p.inv_tau, p.inv_dt, i < __float_as_int(b0[u].z));
+                    halfplane(xi, yi, vxi, vyi, ri, b0[u].x, b0[u].y, b1[u].x, b1[u].y, b1[u].w,
+                              f, p.inv_tau, p.inv_dt, i < tag_index(b1[u].z));
             }
         }
     }
@@ -1515,9 +1624,8 @@ __device__ __forceinline__ void desired_velocity(const SceneP &p, float xi, floa
 // One whole ORCA step of the agent at cell-order position s: neighbours,
 // half-planes (into the lane's LDS column), LP2, LP3 if needed, update.
 // `lines` is a [KnnShape<K>::kSlots][BLOCK] float4 array; lane `tid` owns
-// column tid.  `guess` (caller order, nullable) keeps each agent's K-th
-// neighbour distance between steps (0: none); it only narrows the counting
-// pass.  ACC compiles the acceleration lines in (used for agents whose class
+// column tid.  `guess` (caller order, nullable) keeps each agent's radius of
+// the neighbour scan between steps (0: none).  ACC compiles the acceleration lines in (used for agents whose class
 // has a cap).  EXPORT also writes the neighbour list the step used (caller
 // indices, ascending, -1 padded) to nbr[i * kout ..] and its length to
 // cnt[i] (either nullable); the step itself is unchanged.  All 64 lanes of a
@@ -1527,36 +1635,22 @@ template <int K, int BLOCK, bool ACC = false, bool EXPORT = false>
 __device__ __forceinline__ void step_agent(bool live, int s, const GridMeta &g, const SceneP &p,
                                            const orca_agents_in &in, const orca_agents_out &out,
                                            const uint32_t *__restrict__ start,
-                                           const float4 *__restrict__ s0,
+                                           const float2 *__restrict__ s0,
                                            const float4 *__restrict__ s1, float4 *lines, int tid,
                                            float *__restrict__ guess, int32_t *nbr = nullptr,
                                            int32_t *cnt = nullptr, int kout = 0)
 {
-    const float4 me0 = s0[s];
+    const float2 me0 = s0[s];
     const float4 me1 = s1[s];
-    const int i = __float_as_int(me0.z);
-    const float xi = me0.x, yi = me0.y, ri = me0.w, vxi = me1.x, vyi = me1.y;
-    const int ci = __float_as_int(me1.z) & 1;
+    const int i = tag_index(me1.z);
+    const float xi = me0.x, yi = me0.y, ri = me1.w, vxi = me1.x, vyi = me1.y;
+    const int ci = tag_class(me1.z);
     const float vmax = in.max_speed[i];
 
-    // the K nearest of the previous step, moved apart by at most their two
-    // speeds times dt, stay within d_K + 2 v dt; a small slack covers the
-    // faster neighbours the lane does not know of
-    double rg2 = g.rn2;
-    if (guess) {
-        const float d = guess[i];
-        if (d > 0.0f) {
-            const double r = (double)d + kGuessSpeedSteps * (double)p.dt * (double)vmax +
-                             0.005 * (double)g.rn;
-            rg2 = fmin(r * r, g.rn2);
-        }
-    }
-
     uint64_t *buf = reinterpret_cast<uint64_t *>(lines);
-    const int found = knn_select<K, BLOCK>(g, start, s0, xi, yi, i, (uint32_t)s, buf, tid, rg2);
-    if (guess && live)
-        guess[i] = found == K ? sqrtf(__uint_as_float((uint32_t)(buf[buf_idx<BLOCK>(K - 1, tid)] >> 32)))
-                              : 0.0f;
+    float kept = guess ? guess[i] : 0.0f;
+    const int found = knn_select<K, BLOCK>(g, start, s0, s1, xi, yi, (uint32_t)s, buf, tid, &kept);
+    if (guess && live) guess[i] = kept;
     const int kk = p.k < K ? p.k : K;
     const int m = found < kk ? found : kk;
     uint32_t pos[K];
@@ -1566,7 +1660,7 @@ __device__ __forceinline__ void step_agent(bool live, int s, const GridMeta &g, 
         if (nbr) {
             int32_t *row = nbr + (int64_t)i * kout;
             for (int q = 0; q < kout; ++q)
-                row[q] = q < m ? __float_as_int(s0[entry_pos(buf[buf_idx<BLOCK>(q, tid)])].z) : -1;
+                row[q] = q < m ? tag_index(s1[entry_pos(buf[buf_idx<BLOCK>(q, tid)])].z) : -1;
         }
         if (cnt) cnt[i] = m;
     }

@@ -14,7 +14,7 @@ constexpr int kBboxBlocks = 1024;   // partial bounding boxes per scene (max)
 constexpr int kBboxSplit = 8;      // blocks (partial boxes) per scene of a batch
 constexpr int kScanTile = 2048;     // cells per scan tile (256 threads x 8)
 constexpr int kAlign = 256;
-constexpr int kScanPad = 16;        // float4 entries after the cell-ordered copy s0,
+constexpr int kScanPad = 16;        // entries after the cell-ordered copy s0,
                                     // so candidate groups may read past its end
 
 // Uniform grid of one scene, computed on the device from its bounding box.
@@ -33,6 +33,11 @@ struct GridMeta {
     int n;             // agents in this scene
     uint32_t seg_end;  // one past the scene's last cell-order position
 };
+
+// Caller index (28 bits at most) and class of an agent in one word.
+__host__ __device__ inline int agent_tag(int i, int cls) { return (i << 1) | (cls & 1); }
+__device__ __forceinline__ int tag_index(float z) { return (int)(__float_as_uint(z) >> 1); }
+__device__ __forceinline__ int tag_class(float z) { return __float_as_int(z) & 1; }
 
 // Byte offsets of the workspace regions (all 256-byte aligned).
 struct Layout {
@@ -196,9 +201,9 @@ struct Work {
     uint32_t *count;
     uint32_t *start;
     uint32_t *tiles;
-    float4 *s0;   // cell order: (px, py, bits(caller index), radius)
-    float4 *s1;   // cell order: (vx, vy, bits(class), 0)
-    float *guess; // caller order: K-th neighbour distance of the last step (0: none)
+    float2 *s0;   // cell order: position (what the neighbour scan reads)
+    float4 *s1;   // cell order: (vx, vy, bits(tag), radius), see agent_tag
+    float *guess; // caller order: radius of the neighbour scan kept from the last call (0: none)
 };
 
 Work bind(const Layout &L, void *ws);

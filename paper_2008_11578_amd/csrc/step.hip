@@ -15,13 +15,13 @@ struct StepArgs {
     orca_agents_out out;
     const GridMeta *meta;
     const uint32_t *start;
-    const float4 *s0;
+    const float2 *s0;
     const float4 *s1;
     int n;
     int k;
     int32_t *nbr;   // knn export only
     int32_t *cnt;
-    float *guess;   // per-agent K-th neighbour distance kept between steps
+    float *guess;   // per-agent radius of the neighbour scan kept between steps
     orca_params prm;
 };
 
@@ -49,16 +49,18 @@ __global__ __launch_bounds__(BLOCK) void k_knn_export(StepArgs a)
     const int s = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + tid;
     if (s >= a.n) return;
     const GridMeta g = *a.meta;
-    const float4 me0 = a.s0[s];
-    const int i = __float_as_int(me0.z);
+    const float2 me = a.s0[s];
+    const int i = tag_index(a.s1[s].z);
     uint64_t *buf = reinterpret_cast<uint64_t *>(lds);
+    float kept = a.guess[i];
     const int found =
-        knn_select<K, BLOCK>(g, a.start, a.s0, me0.x, me0.y, i, (uint32_t)s, buf, tid, g.rn2);
+        knn_select<K, BLOCK>(g, a.start, a.s0, a.s1, me.x, me.y, (uint32_t)s, buf, tid, &kept);
+    a.guess[i] = kept;
     const int m = found < a.k ? found : a.k;
     if (a.nbr) {
         int32_t *row = a.nbr + (int64_t)i * a.k;
         for (int q = 0; q < a.k; ++q)
-            row[q] = q < m ? __float_as_int(a.s0[dev::entry_pos(buf[buf_idx<BLOCK>(q, tid)])].z) : -1;
+            row[q] = q < m ? tag_index(a.s1[dev::entry_pos(buf[buf_idx<BLOCK>(q, tid)])].z) : -1;
     }
     if (a.cnt) a.cnt[i] = m;
 }

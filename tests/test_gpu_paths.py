@@ -70,3 +70,45 @@ def test_least_penetration_by_groups_of_lanes(k, jam, free, caps):
     assert rep["n_bad"] <= max(2, n // 20), rep
     if k >= 4:
         assert rep["lp3_oracle"] >= jam // 3, rep
+
+
+@pytest.mark.parametrize("k", [1, 4, 8, 10, 12, 16, 20, 24, 32])
+def test_kept_scan_radius_changes_no_result(k):
+    """Each agent keeps the radius of its neighbour scan in the workspace.  A
+    circle kept from another crowd holds too few (sparse after dense), more
+    than the sorting network takes, more than the buffer, more than the
+    byte counters (300 agents within it), agents at one place (ties and keys
+    of zero beside the own), or no agent but the own: lists and velocities
+    equal those of a fresh workspace bit for bit, call after call."""
+    import torch
+    from paper_2008_11578_amd import orca
+    n = 331
+    rng = np.random.Generator(np.random.PCG64(500 + k))
+    p = scenarios.Params(dt=0.1, neighbor_dist=4.0, max_neighbors=k)
+    sides = [3.0, 8.0, 14.0, 20.0, 60.0, 2000.0, 8.0, 20.0]
+    ws, wsb = orca.Workspace(n), orca.Workspace(n, backward=True)
+    g = [torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(j))
+         for j in range(4)]
+
+    def backward(st, w):
+        acc = [torch.zeros(n, device="cuda") for _ in range(2)] + [torch.zeros(1, device="cuda")]
+        return list(orca.step_backward(st, p, w, *g, *acc)) + acc
+
+    for rep, side in enumerate(sides):
+        sc = scenarios.random_state(n, side, seed=600 + 31 * rep + k, n_vehicles=8, params=p)
+        if rep % 2:  # lattice places: ties in distance, and agents at one place
+            sc.px = np.round(sc.px * 2.0).astype(np.float32) / 2
+            sc.py = np.round(sc.py * 2.0).astype(np.float32) / 2
+        sc.px[rng.integers(0, n, 9)] = sc.px[0]
+        st = orca.State.from_arrays(sc)
+        for again in range(2):
+            out, nbr, cnt = orca.step_nbr(st, p, ws)
+            ref, rnbr, rcnt = orca.step_nbr(st, p, orca.Workspace(n))
+            lnbr, lcnt = orca.build_grid(st, p, ws)
+            fnbr, fcnt = orca.build_grid(st, p, orca.Workspace(n))
+            torch.cuda.synchronize()
+            for a, b in ((nbr, rnbr), (cnt, rcnt), (lnbr, fnbr), (lcnt, fcnt), (nbr, fnbr),
+                         *[(getattr(out, f), getattr(ref, f)) for f in FIELDS]):
+                assert torch.equal(a, b), (rep, again)
+            for a, b in zip(backward(st, wsb), backward(st, orca.Workspace(n, backward=True))):
+                assert torch.equal(a, b), (rep, again)
