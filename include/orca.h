@@ -183,8 +183,9 @@ typedef struct {
     const orca_params *params;    /* DEVICE, n_scenes entries (cell_size 0 = R_n) */
     int32_t max_neighbors;        /* HOST: largest max_neighbors over the scenes,
                                      1..ORCA_K_MAX (selects the compiled kernel) */
-    int32_t mode;                 /* 0: persistent kernel with per-XCD tile queues
-                                     (default); 1: one workgroup per tile */
+    int32_t mode;                 /* 0: the library's own launch shape (default);
+                                     1: lanes per workgroup as `block` says.
+                                     Results do not depend on it. */
     int32_t *error_flag;          /* DEVICE, nullable: set to 1 (never cleared) when
                                      an offset or a scene's parameters are invalid
                                      (including an accel or turn cap > 0 while
@@ -194,8 +195,9 @@ typedef struct {
                                      turn[c] > 0 (selects the kernel with hard
                                      lines; without it caps are ignored and
                                      flagged), else 0 */
-    int32_t block;                /* HOST: lanes per workgroup of the step kernel,
-                                     64, 128 or 256 (1, 2 or 4 wavefronts); 0 = 128 */
+    int32_t block;                /* HOST: lanes per workgroup of the step kernel in
+                                     mode 1, 64, 128 or 256 (1, 2 or 4 wavefronts);
+                                     0 = 64.  Small batches have one shape. */
     int32_t k_tile;               /* HOST: neighbour-list capacity compiled into the
                                      step kernel, max_neighbors..ORCA_K_MAX, rounded
                                      up to a compiled one (4, 8, 10, 12, 16, 20, 24,

@@ -25,7 +25,7 @@
 //   k_tau_*         the per-agent tau contributions summed in double in a
 //                   fixed order (block sums, then one block).
 // Neighbour sets and branches are held fixed (they are piecewise constant).
-#include "orca_device.h"
+#include "orca_group.h"
 
 namespace orca {
 namespace {
@@ -170,66 +170,38 @@ __device__ __forceinline__ void solve2(float g1x, float g1y, float g2x, float g2
     m2 = (g1x * wy - g1y * wx) * id;
 }
 
-template <int K, int BLOCK, bool ACC>
-__device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a, const GridMeta &g,
-                                              float4 *lines, int tid)
+// One agent's step as the adjoint needs it: what its forward recomputation
+// found, the same whichever kernel form ran it.
+template <int BLOCK, bool ACC>
+struct AdjAgent {
+    int i, ci;
+    float xi, yi, ri, vxi, vyi, vmax;  // state of the step
+    float prx, pry;                    // desired velocity
+    float vx, vy;                      // new velocity
+    int nh, nacc;                      // hard lines, octagon lines among them
+    dev::LdsLines<BLOCK, ACC> src;
+    dev::ActiveSet rec;
+};
+
+// The VJP of an agent's step; pos_of(q): cell-order position of neighbour q.
+template <int BLOCK, bool ACC, class PosOf>
+__device__ __forceinline__ void adjoint_vjp(const AdjArgs &a, const AdjAgent<BLOCK, ACC> &f,
+                                            PosOf &&pos_of)
 {
     const dev::SceneP &p = a.p;
-    const float2 me0 = a.s0[s];
-    const float4 me1 = a.s1[s];
-    const int i = tag_index(me1.z);
-    const float xi = me0.x, yi = me0.y, ri = me1.w, vxi = me1.x, vyi = me1.y;
-    const int ci = tag_class(me1.z);
-
-    // -- forward recomputation (identical to dev::step_agent) --
-    uint64_t *buf = reinterpret_cast<uint64_t *>(lines);
-    float kept = a.guess[i];
-    const int found = dev::knn_select<K, BLOCK>(g, a.start, a.s0, a.s1, xi, yi, (uint32_t)s, buf,
-                                                tid, &kept);
-    if (live) a.guess[i] = kept;
-    const int kk = p.k < K ? p.k : K;
-    const int m = found < kk ? found : kk;
-    uint32_t pos[K];
-#pragma unroll
-    for (int q = 0; q < K; ++q)
-        pos[q] = q < m ? dev::entry_pos(buf[dev::buf_idx<BLOCK>(q, tid)]) : 0u;
-    const float vmax = a.in.max_speed[i];
-    const float acc = ACC ? (ci ? p.acc1 : p.acc0) : 0.0f;
+    const int i = f.i, ci = f.ci, nh = f.nh, nacc = f.nacc;
+    const float xi = f.xi, yi = f.yi, ri = f.ri, vxi = f.vxi, vyi = f.vyi, vmax = f.vmax;
+    const float prx = f.prx, pry = f.pry, vx = f.vx, vy = f.vy;
+    const dev::LdsLines<BLOCK, ACC> &src = f.src;
+    const dev::ActiveSet &rec = f.rec;
     const float turn = ACC ? (ci ? p.turn1 : p.turn0) : 0.0f;
-    const int nacc = (ACC && acc > 0.0f) ? dev::kAccLines : 0;
-    float rx = 0.0f, ry = 0.0f, lx = 0.0f, ly = 0.0f;
-    const int nh = nacc + ((ACC && dev::turn_wedge(vxi, vyi, turn, p.dt, rx, ry, lx, ly))
-                               ? dev::kTurnLines : 0);
-    dev::build_halfplanes<K, BLOCK>(pos, m, a.s0, a.s1, xi, yi, vxi, vyi, ri, i, ci, p, lines,
-                                    tid);
-    float cx = 0.0f, cy = 0.0f;
-    if (ACC && nh) dev::accel_centre(vxi, vyi, vmax, cx, cy);
-    const float pin_x = a.in.pref_x[i], pin_y = a.in.pref_y[i];
-    float prx = pin_x, pry = pin_y;
-    dev::desired_velocity(p, xi, yi, vmax, prx, pry);
     // the goal-mode quantities the desired velocity was formed from
     float gxg = 0.0f, gyg = 0.0f, d2g = 0.0f;
     if (p.pref_is_goal) {
-        gxg = pin_x - xi;
-        gyg = pin_y - yi;
+        gxg = a.in.pref_x[i] - xi;
+        gyg = a.in.pref_y[i] - yi;
         d2g = gxg * gxg + gyg * gyg;
     }
-    const dev::LdsLines<BLOCK, ACC> src{lines, tid, nh, cx, cy,
-                                        ACC && nacc ? dev::accel_half_width(acc, p.dt) : 0.0f,
-                                        nacc, rx, ry, lx, ly};
-    float vx, vy;
-    dev::ActiveSet rec{dev::kFree, -1, -1, -1};
-    const int mt = nh + m;
-    int fail = dev::lp2<true, float>(src, mt, vmax, 0, prx, pry, 0.0f, 0.0f, p.eps, vx, vy, &rec);
-    if (ACC && fail < nh) {
-        vx = cx;
-        vy = cy;
-        fail = nh;
-        rec.kind = dev::kCentre;
-    }
-    dev::wave_lp3<true, K, BLOCK, ACC>(src, tid, live && fail < mt, mt, fail, vmax, prx, pry, p.eps,
-                                       vx, vy, &rec);
-    if (!live) return;
 
     // -- cotangent of the new velocity: v' directly and through p' = p + v' dt --
     const float gpx = a.gpx1[i], gpy = a.gpy1[i];
@@ -399,11 +371,7 @@ __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a
                 hby -= -sn * dbx + cs * dby;
             }
         } else if (lb.idx[e] >= 0) {
-            uint32_t pj = 0u;
-            const int qn = lb.idx[e] - nh;
-#pragma unroll
-            for (int q = 0; q < K; ++q)
-                if (q == qn) pj = pos[q];
+            const uint32_t pj = pos_of(lb.idx[e] - nh);
             const float2 b0 = a.s0[pj];
             const float4 b1 = a.s1[pj];
             const int j = tag_index(b1.z);
@@ -478,6 +446,73 @@ __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a
 }
 
 template <int K, int BLOCK, bool ACC>
+__device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a, const GridMeta &g,
+                                              float4 *lines, int tid)
+{
+    const dev::SceneP &p = a.p;
+    const float2 me0 = a.s0[s];
+    const float4 me1 = a.s1[s];
+    AdjAgent<BLOCK, ACC> f;
+    f.i = tag_index(me1.z);
+    f.ci = tag_class(me1.z);
+    f.xi = me0.x;
+    f.yi = me0.y;
+    f.ri = me1.w;
+    f.vxi = me1.x;
+    f.vyi = me1.y;
+
+    // -- forward recomputation (identical to dev::step_agent) --
+    uint64_t *buf = reinterpret_cast<uint64_t *>(lines);
+    float kept = a.guess[f.i];
+    const int found = dev::knn_select<K, BLOCK>(g, a.start, a.s0, a.s1, f.xi, f.yi, (uint32_t)s, buf,
+                                                tid, &kept);
+    if (live) a.guess[f.i] = kept;
+    const int kk = p.k < K ? p.k : K;
+    const int m = found < kk ? found : kk;
+    uint32_t pos[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+        pos[q] = q < m ? dev::entry_pos(buf[dev::buf_idx<BLOCK>(q, tid)]) : 0u;
+    f.vmax = a.in.max_speed[f.i];
+    const float acc = ACC ? (f.ci ? p.acc1 : p.acc0) : 0.0f;
+    const float turn = ACC ? (f.ci ? p.turn1 : p.turn0) : 0.0f;
+    f.nacc = (ACC && acc > 0.0f) ? dev::kAccLines : 0;
+    float rx = 0.0f, ry = 0.0f, lx = 0.0f, ly = 0.0f;
+    f.nh = f.nacc + ((ACC && dev::turn_wedge(f.vxi, f.vyi, turn, p.dt, rx, ry, lx, ly))
+                         ? dev::kTurnLines : 0);
+    dev::build_halfplanes<K, BLOCK>(pos, m, a.s0, a.s1, f.xi, f.yi, f.vxi, f.vyi, f.ri, f.i, f.ci, p,
+                                    lines, tid);
+    float cx = 0.0f, cy = 0.0f;
+    if (ACC && f.nh) dev::accel_centre(f.vxi, f.vyi, f.vmax, cx, cy);
+    f.prx = a.in.pref_x[f.i];
+    f.pry = a.in.pref_y[f.i];
+    dev::desired_velocity(p, f.xi, f.yi, f.vmax, f.prx, f.pry);
+    f.src = dev::LdsLines<BLOCK, ACC>{lines, tid, f.nh, cx, cy,
+                                      ACC && f.nacc ? dev::accel_half_width(acc, p.dt) : 0.0f,
+                                      f.nacc, rx, ry, lx, ly};
+    f.rec = dev::ActiveSet{dev::kFree, -1, -1, -1};
+    const int mt = f.nh + m;
+    int fail = dev::lp2<true, float>(f.src, mt, f.vmax, 0, f.prx, f.pry, 0.0f, 0.0f, p.eps, f.vx,
+                                     f.vy, &f.rec);
+    if (ACC && fail < f.nh) {
+        f.vx = cx;
+        f.vy = cy;
+        fail = f.nh;
+        f.rec.kind = dev::kCentre;
+    }
+    dev::wave_lp3<true, K, BLOCK, ACC>(f.src, tid, live && fail < mt, mt, fail, f.vmax, f.prx, f.pry,
+                                       p.eps, f.vx, f.vy, &f.rec);
+    if (!live) return;
+    adjoint_vjp(a, f, [&](int qn) {
+        uint32_t pj = 0u;
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+            if (q == qn) pj = pos[q];
+        return pj;
+    });
+}
+
+template <int K, int BLOCK, bool ACC>
 __global__ __launch_bounds__(BLOCK) void k_adjoint(AdjArgs a)
 {
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
@@ -486,6 +521,40 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(AdjArgs a)
     const GridMeta g = *a.meta;
     // every lane of the last wavefront takes part (LP3 is solved by quads)
     adjoint_agent<K, BLOCK, ACC>(s < a.n, min(s, a.n - 1), a, g, lines, tid);
+}
+
+// The same for a small crowd: a group of lanes per agent (orca_group.h), the
+// VJP by its first lane.
+template <int K, int G, bool ACC, bool WHOLE>
+__global__ __launch_bounds__(kWave) void k_adjoint_group(AdjArgs a, float rn)
+{
+    __shared__ dev::GroupLds<K, G> lds;
+    constexpr int A = kWave / G;
+    const int who = threadIdx.x / G, c = threadIdx.x % G;
+    const int at = xcd_tile(blockIdx.x, gridDim.x) * A + who;
+    const bool live = at < a.n;
+    const GridMeta g = WHOLE ? whole_crowd(a.n, rn) : *a.meta;
+    AdjAgent<A, ACC> f;
+    f.rec = dev::ActiveSet{dev::kFree, -1, -1, -1};
+    const dev::GroupAgent<K, G, ACC> r = dev::group_step<true, K, G, ACC, WHOLE>(
+        min(at, a.n - 1), g, a.p, a.in, a.start, a.s0, a.s1, lds, who, c, live, a.guess, &f.rec);
+    if (!live || c != 0) return;
+    f.i = r.i;
+    f.ci = tag_class(r.s.z);
+    f.xi = r.p.x;
+    f.yi = r.p.y;
+    f.ri = r.s.w;
+    f.vxi = r.s.x;
+    f.vyi = r.s.y;
+    f.vmax = r.vmax;
+    f.prx = r.prx;
+    f.pry = r.pry;
+    f.vx = r.vx;
+    f.vy = r.vy;
+    f.nh = r.nh;
+    f.nacc = r.nacc;
+    f.src = r.lines;
+    adjoint_vjp(a, f, [&](int q) { return lds.nbr[who][q]; });
 }
 
 // Edges by target: count and rank.
@@ -636,6 +705,29 @@ void launch_adjoint_k(const AdjArgs &a, hipStream_t stream)
                            a);
 }
 
+template <int K, bool ACC>
+void launch_adjoint_group_k(const AdjArgs &a, bool whole, float rn, hipStream_t stream)
+{
+    const int nb = (a.n + kWave / kGroup - 1) / (kWave / kGroup);
+    if (whole)
+        hipLaunchKernelGGL((k_adjoint_group<K, kGroup, ACC, true>), dim3(nb), dim3(kWave), 0, stream,
+                           a, rn);
+    else
+        hipLaunchKernelGGL((k_adjoint_group<K, kGroup, ACC, false>), dim3(nb), dim3(kWave), 0,
+                           stream, a, rn);
+}
+
+void launch_adjoint_group(const AdjArgs &a, bool whole, float rn, hipStream_t stream)
+{
+    const bool acc = a.p.acc0 > 0.0f || a.p.acc1 > 0.0f || a.p.turn0 > 0.0f || a.p.turn1 > 0.0f;
+    if (a.p.k <= 16)
+        acc ? launch_adjoint_group_k<16, true>(a, whole, rn, stream)
+            : launch_adjoint_group_k<16, false>(a, whole, rn, stream);
+    else
+        acc ? launch_adjoint_group_k<32, true>(a, whole, rn, stream)
+            : launch_adjoint_group_k<32, false>(a, whole, rn, stream);
+}
+
 }  // namespace
 
 hipError_t launch_adjoint(const orca_agents_in &in, int n, const orca_params &prm,
@@ -672,7 +764,9 @@ hipError_t launch_adjoint(const orca_agents_in &in, int n, const orca_params &pr
     const int k = prm.max_neighbors;
     if (ev && ev->step_begin && hipEventRecord(ev->step_begin, stream) != hipSuccess)
         return hipErrorInvalidValue;
-    if (k <= 4)
+    if (n <= (has_hard_lines(prm) ? kGroupAdjointMaxHard : kGroupAdjointMax))
+        launch_adjoint_group(a, n <= kWholeMax, prm.neighbor_dist, stream);
+    else if (k <= 4)
         launch_adjoint_k<4>(a, stream);
     else if (k <= 8)
         launch_adjoint_k<8>(a, stream);

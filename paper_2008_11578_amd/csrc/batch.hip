@@ -9,49 +9,20 @@
 // [off[s], off[s+1])).  Agents of different scenes never share a cell and so
 // never see each other.
 //
-// The step kernel is persistent: a grid sized to the device's occupancy
-// whose wavefronts pop 64-agent tiles from eight queues, one per XCD (each
-// over a contiguous range of tiles, so neighbouring agents stay in one L2),
-// and steal from the other queues once their own is drained.  Every queue is
-// a monotone counter, so every wavefront exits.
+// The step kernel takes one 64-agent tile per wavefront in an XCD-aware order
+// (neighbouring tiles stay in one L2), small batches a group of lanes per agent.
 #include "orca_device.h"
 
 namespace orca {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kStepBlock = 128;
-constexpr int kTile = 64;
-
-// Scene of caller index i: the largest s with off[s] <= i (off ascending).
-__device__ __forceinline__ int scene_of(const int32_t *__restrict__ off, int S, int i)
-{
-    int lo = 0, hi = S - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (off[mid] <= i)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
 
 __device__ __forceinline__ int clamp_off(int v, int n) { return v < 0 ? 0 : (v > n ? n : v); }
 
-// Scene of caller index i given the scene s0 of an index <= i (off
-// ascending): a walk forward from s0, a step or two for the indices of one
-// tile, instead of a binary search per index.
-__device__ __forceinline__ int scene_from(const int32_t *__restrict__ off, int S, int s0, int i)
-{
-    int s = s0;
-    while (s + 1 < S && off[s + 1] <= i) ++s;
-    return s;
-}
-
 // (1) kBboxSplit blocks per scene: partial bounding boxes of its agents (a
 // block per scene left the largest scenes to one block each).  All blocks
-// also clear the histogram and block 0 the tile queues; scene offsets and
+// also clear the histogram; scene offsets and
 // parameters are checked and any violation is flagged (the kernels stay in
 // bounds regardless: offsets are clamped to [0, n]).
 __global__ __launch_bounds__(kBlock) void k_batch_bbox(const float *__restrict__ px,
@@ -60,7 +31,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_bbox(const float *__restrict__
                                                        const orca_params *__restrict__ prm,
                                                        float4 *__restrict__ partial,
                                                        uint32_t *__restrict__ count, int count_len,
-                                                       uint32_t *__restrict__ queue,
                                                        int32_t *__restrict__ error_flag,
                                                        int has_accel)
 {
@@ -76,7 +46,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_bbox(const float *__restrict__
     }
     const int stride = gridDim.x * kBlock;
     for (int c = blockIdx.x * kBlock + threadIdx.x; c < count_len; c += stride) count[c] = 0u;
-    if (s == 0 && threadIdx.x < kXcds) queue[threadIdx.x] = 0u;
     bb = block_bbox<kBlock>(bb);
     if (threadIdx.x == 0) {
         partial[blockIdx.x] = bb;
@@ -155,21 +124,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_count(const float *__restrict_
     rank[i] = atomicAdd(&count[c], 1u);
 }
 
-struct BatchArgs {
-    orca_agents_in in;
-    orca_agents_out out;
-    const GridMeta *meta;
-    const orca_params *prm;
-    const int32_t *off;
-    int S;
-    int n;
-    const uint32_t *start;
-    const float2 *s0;
-    const float4 *s1;
-    uint32_t *queue;
-    float *guess;  // per-agent radius of the neighbour scan kept between steps
-};
-
 // The agent at cell-order position s (all lanes of the wavefront call it; one
 // past the last agent takes part without an agent of its own).
 template <int K, int BLOCK, bool ACC>
@@ -185,34 +139,7 @@ __device__ __forceinline__ void batch_agent(const BatchArgs &a, int s, int first
                                    a.guess);
 }
 
-// Persistent step: wavefronts pop 64-agent tiles, first from their XCD's
-// queue (a contiguous eighth of the tiles), then from the others.
-template <int K, int BLOCK, bool ACC>
-__global__ __launch_bounds__(BLOCK) void k_step_batched(BatchArgs a)
-{
-    __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int n_tiles = (a.n + kTile - 1) / kTile;
-    const int xcd = blockIdx.x % kXcds;
-    for (int v = 0; v < kXcds; ++v) {
-        const int x = (xcd + v) % kXcds;
-        const int lo = (int)(((int64_t)n_tiles * x) / kXcds);
-        const int hi = (int)(((int64_t)n_tiles * (x + 1)) / kXcds);
-        for (;;) {
-            int t = 0;
-            if (lane == 0) t = (int)atomicAdd(&a.queue[x], 1u);
-            t = __shfl(t, 0, kWave);
-            if (t >= hi - lo) break;
-            const int s = (lo + t) * kTile + lane;
-            // the tile's first scene, searched once (a wavefront-uniform index)
-            const int first = scene_of(a.off, a.S, (lo + t) * kTile);
-            batch_agent<K, BLOCK, ACC>(a, s, first, lines, tid);
-        }
-    }
-}
-
-// Flat form of the same step: one tile per workgroup wave, XCD-aware order.
+// The step: one 64-agent tile per wavefront, XCD-aware order.
 template <int K, int BLOCK, bool ACC>
 __global__ __launch_bounds__(BLOCK) void k_step_batched_flat(BatchArgs a)
 {
@@ -222,62 +149,29 @@ __global__ __launch_bounds__(BLOCK) void k_step_batched_flat(BatchArgs a)
     batch_agent<K, BLOCK, ACC>(a, s0 + tid, scene_of(a.off, a.S, s0), lines, tid);
 }
 
-// Workgroups of k_step_batched that fit the device at once (cached per
-// instantiation; multiple of the XCD count).
-template <int K, int BLOCK, bool ACC>
-int persistent_grid()
+template <int K, int BLOCK>
+hipError_t launch_step_batched_b(const BatchArgs &a, bool acc, hipStream_t stream)
 {
-    static int cached = 0;
-    if (cached) return cached;
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_step_batched<K, BLOCK, ACC>, BLOCK,
-                                                     0) !=
-        hipSuccess)
-        return 0;
-    int g = cus * (per_cu > 0 ? per_cu : 1);
-    g = (g + kXcds - 1) / kXcds * kXcds;
-    cached = g;
-    return g;
-}
-
-template <int K, int BLOCK, bool ACC>
-hipError_t launch_step_batched_v(const BatchArgs &a, int mode, hipStream_t stream)
-{
-    const int nb = (a.n + BLOCK - 1) / BLOCK;
-    const int g = mode == 1 ? nb : persistent_grid<K, BLOCK, ACC>();
-    if (g <= 0) return hipErrorInvalidValue;
-    // A batch whose tiles all fit the device at once has nothing to queue: the
-    // flat form then, without the queues' atomics.  (6 scenes of 1,024 agents:
-    // the persistent grid's 4,096 wavefronts, 40 for each tile, spent 295 us on
-    // 32,768 atomics of one cache line; a whole step 312 -> 44 us.)
-    if (mode == 1 || nb <= g) {
-        hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, ACC>), dim3(nb), dim3(BLOCK), 0, stream,
-                           a);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((k_step_batched<K, BLOCK, ACC>), dim3(g), dim3(BLOCK), 0, stream, a);
+    const dim3 nb((a.n + BLOCK - 1) / BLOCK);
+    if (acc)
+        hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, true>), nb, dim3(BLOCK), 0, stream, a);
+    else
+        hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, false>), nb, dim3(BLOCK), 0, stream, a);
     return hipGetLastError();
 }
 
-template <int K, int BLOCK>
-hipError_t launch_step_batched_b(const BatchArgs &a, int mode, bool acc, hipStream_t stream)
-{
-    return acc ? launch_step_batched_v<K, BLOCK, true>(a, mode, stream)
-               : launch_step_batched_v<K, BLOCK, false>(a, mode, stream);
-}
-
-// Workgroup size (one, two or four wavefronts; the LDS column per lane is
-// the same, so occupancy differs only through the workgroup granularity).
+// Workgroup size: one wavefront, whose LDS is free again as soon as it ends,
+// unless the caller asks for 128 or 256 lanes.  512 scenes, 5.56M agents: 3.17
+// ms at 64 lanes, 3.69 at 128, 3.87 at 256.  (Wavefronts that stay and pop tiles
+// from a queue per XCD took 3.54 ms: the pops, and each wavefront's look at every
+// queue at the end, are atomics on one line, 9 ns each; 3.41 ms with a line per
+// queue.  The hardware's own dispatch balances as well and costs nothing.)
 template <int K>
-hipError_t launch_step_batched_k(const BatchArgs &a, int mode, bool acc, int block,
-                                 hipStream_t stream)
+hipError_t launch_step_batched_k(const BatchArgs &a, bool acc, int block, hipStream_t stream)
 {
-    if (block == 64) return launch_step_batched_b<K, 64>(a, mode, acc, stream);
-    if (block == 256) return launch_step_batched_b<K, 256>(a, mode, acc, stream);
-    return launch_step_batched_b<K, kStepBlock>(a, mode, acc, stream);
+    if (block == 128) return launch_step_batched_b<K, 128>(a, acc, stream);
+    if (block == 256) return launch_step_batched_b<K, 256>(a, acc, stream);
+    return launch_step_batched_b<K, 64>(a, acc, stream);
 }
 
 }  // namespace
@@ -285,7 +179,7 @@ hipError_t launch_step_batched_k(const BatchArgs &a, int mode, bool acc, int blo
 hipError_t launch_batched(const orca_agents_in &in, const orca_agents_out &out, int n,
                           const int32_t *scene_off, int n_scenes, const orca_params *params,
                           int k_max, bool acc, int block, const Layout &L, const Work &w,
-                          int32_t *error_flag, int mode, const orca_step_events *ev,
+                          int32_t *error_flag, const orca_step_events *ev,
                           hipStream_t stream)
 {
     const int S = n_scenes;
@@ -294,7 +188,7 @@ hipError_t launch_batched(const orca_agents_in &in, const orca_agents_out &out, 
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_batch_bbox, dim3(S * kBboxSplit), dim3(kBlock), 0, stream, in.px, in.py,
                        n, scene_off,
-                       S, params, w.partial, w.count, (int)L.max_cells, w.queue, error_flag,
+                       S, params, w.partial, w.count, (int)L.max_cells, error_flag,
                        acc ? 1 : 0);
     hipLaunchKernelGGL(k_batch_setup, dim3((S + kBlock - 1) / kBlock), dim3(kBlock), 0, stream,
                        w.partial, scene_off, S, n, params, w.meta);
@@ -313,26 +207,30 @@ hipError_t launch_batched(const orca_agents_in &in, const orca_agents_out &out, 
     a.start = w.start;
     a.s0 = w.s0;
     a.s1 = w.s1;
-    a.queue = w.queue;
     a.guess = w.guess;
     if (ev && ev->step_begin && hipEventRecord(ev->step_begin, stream) != hipSuccess)
         return hipErrorInvalidValue;
-    if (k_max <= 4)
-        e = launch_step_batched_k<4>(a, mode, acc, block, stream);
+    // (8 scenes with vehicles, group / lane per agent: 72,000 agents 95 / 140 us,
+    // 100,000 124 / 147, 150,000 158 / 155; pedestrians alone, k 10: 72,000 78 /
+    // 78, 100,000 98 / 81)
+    if (n <= kGroupBatchMax)
+        e = launch_batched_group(a, k_max, acc, stream);
+    else if (k_max <= 4)
+        e = launch_step_batched_k<4>(a, acc, block, stream);
     else if (k_max <= 8)
-        e = launch_step_batched_k<8>(a, mode, acc, block, stream);
+        e = launch_step_batched_k<8>(a, acc, block, stream);
     else if (k_max <= 10)
-        e = launch_step_batched_k<10>(a, mode, acc, block, stream);
+        e = launch_step_batched_k<10>(a, acc, block, stream);
     else if (k_max <= 12)
-        e = launch_step_batched_k<12>(a, mode, acc, block, stream);
+        e = launch_step_batched_k<12>(a, acc, block, stream);
     else if (k_max <= 16)
-        e = launch_step_batched_k<16>(a, mode, acc, block, stream);
+        e = launch_step_batched_k<16>(a, acc, block, stream);
     else if (k_max <= 20)
-        e = launch_step_batched_k<20>(a, mode, acc, block, stream);
+        e = launch_step_batched_k<20>(a, acc, block, stream);
     else if (k_max <= 24)
-        e = launch_step_batched_k<24>(a, mode, acc, block, stream);
+        e = launch_step_batched_k<24>(a, acc, block, stream);
     else
-        e = launch_step_batched_k<32>(a, mode, acc, block, stream);
+        e = launch_step_batched_k<32>(a, acc, block, stream);
     if (e != hipSuccess) return e;
     if (ev && ev->step_end && hipEventRecord(ev->step_end, stream) != hipSuccess)
         return hipErrorInvalidValue;

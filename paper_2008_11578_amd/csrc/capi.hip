@@ -32,8 +32,6 @@ Layout make_layout(int64_t n, int64_t n_scenes, int64_t max_cells)
     const size_t n_partial = (size_t)S * kBboxSplit;
     o = align_up(o + sizeof(float4) * (n_partial > (size_t)kBboxBlocks ? n_partial
                                                                        : (size_t)kBboxBlocks));
-    L.queue = o;
-    o = align_up(o + sizeof(uint32_t) * kXcds);
     L.cell = o;
     o = align_up(o + sizeof(uint32_t) * (size_t)n);
     L.rank = o;
@@ -60,7 +58,6 @@ Work bind(const Layout &L, void *ws)
     Work w;
     w.meta = (GridMeta *)(b + L.meta);
     w.partial = (float4 *)(b + L.partial);
-    w.queue = (uint32_t *)(b + L.queue);
     w.cell = (uint32_t *)(b + L.cell);
     w.rank = (uint32_t *)(b + L.rank);
     w.count = (uint32_t *)(b + L.count);
@@ -254,7 +251,9 @@ int orca_build_grid(const orca_agents_in *in, int32_t n, const orca_params *para
     const Work w = bind(L, ws);
     if (launch_grid_build(*in, n, *params, L, w, stream) != hipSuccess) return ORCA_EHIP;
     if (nbr || nbr_count) {
-        if (launch_knn_export(*in, n, *params, L, w, nbr, nbr_count, stream) != hipSuccess)
+        if ((n <= (params->max_neighbors > 24 ? kGroupListMaxLarge : kGroupListMax) ? launch_list_group(n, *params, w, nbr, nbr_count, stream)
+                            : launch_knn_export(*in, n, *params, L, w, nbr, nbr_count, stream)) !=
+            hipSuccess)
             return ORCA_EHIP;
     }
     return ORCA_OK;
@@ -279,10 +278,15 @@ int step_impl(const orca_agents_in *in, const orca_agents_out *out, int32_t n,
     const Work w = bind(L, ws);
     if (events && events->grid_begin && hipEventRecord(events->grid_begin, stream) != hipSuccess)
         return ORCA_EHIP;
-    if (launch_grid_build(*in, n, *params, L, w, stream) != hipSuccess) return ORCA_EHIP;
+    const bool whole = n <= kWholeMax;
+    if ((whole ? launch_pack(*in, n, w, stream)
+               : launch_grid_build(*in, n, *params, L, w, stream)) != hipSuccess)
+        return ORCA_EHIP;
     if (events && events->step_begin && hipEventRecord(events->step_begin, stream) != hipSuccess)
         return ORCA_EHIP;
-    if (launch_step(*in, *out, n, *params, L, w, nbr, nbr_count, stream) != hipSuccess)
+    if ((n <= (has_hard_lines(*params) ? kGroupStepMaxHard : kGroupStepMax) ? launch_step_group(*in, *out, n, *params, w, whole, nbr, nbr_count, stream)
+                        : launch_step(*in, *out, n, *params, L, w, nbr, nbr_count, stream)) !=
+        hipSuccess)
         return ORCA_EHIP;
     if (events && events->step_end && hipEventRecord(events->step_end, stream) != hipSuccess)
         return ORCA_EHIP;
@@ -364,8 +368,8 @@ int orca_step_batched_ex(const orca_agents_in *in, const orca_agents_out *out, i
     const Work w = bind(L, ws);
     if (launch_batched(*in, *out, n, batch->scene_off, batch->n_scenes, batch->params,
                        batch->k_tile ? batch->k_tile : batch->max_neighbors,
-                       batch->has_accel != 0, batch->block ? batch->block : 128, L, w,
-                       batch->error_flag, batch->mode, events, stream) != hipSuccess)
+                       batch->has_accel != 0, batch->mode == 1 ? batch->block : 64, L, w,
+                       batch->error_flag, events, stream) != hipSuccess)
         return ORCA_EHIP;
     return ORCA_OK;
 }
@@ -408,7 +412,9 @@ int orca_step_backward_ex(const orca_agents_in *in, int32_t n, const orca_params
     const AdjointBufs b = bind_adjoint(n, (char *)ws + L.total);
     if (events && events->grid_begin && hipEventRecord(events->grid_begin, stream) != hipSuccess)
         return ORCA_EHIP;
-    if (launch_grid_build(*in, n, *params, L, w, stream) != hipSuccess) return ORCA_EHIP;
+    if ((n <= kWholeMax ? launch_pack(*in, n, w, stream)
+                        : launch_grid_build(*in, n, *params, L, w, stream)) != hipSuccess)
+        return ORCA_EHIP;
     if (launch_adjoint(*in, n, *params, L, w, b, g1->px, g1->py, g1->vx, g1->vy, g0->px, g0->py,
                        g0->vx, g0->vy, g0->pref_x, g0->pref_y, g0->tau, events,
                        stream) != hipSuccess)

@@ -713,7 +713,11 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
         lk = bk;
         lj = bj;
     }
-    if (keep) *keep = 0.0f;
+    // the next circle, from the last pick's distance
+    if (keep)
+        *keep = m == K ? fminf((float)sqrt(lk) * sqrtf((float)(K + 1 + KeptShape<K>::kMore) / (float)(K + 1)),
+                               g.rn)
+                       : g.rn;
     return m;
 }
 
@@ -1144,14 +1148,12 @@ __device__ __forceinline__ bool lp1(const Src &src, int i, typename LpVec<S>::T 
     return true;
 }
 
-// Incremental 2D LP over lines 0..m-1 of `src` and the disc |v| <= vmax.
-// Returns the first infeasible line, or m; v keeps its pre-failure value.
-// With REC the active set of the result is written to *rec.
-template <bool REC, class S, class Src>
-__device__ __forceinline__ int lp2(const Src &src, int m, S vmax, int mode, S ox, S oy, S tx,
-                                   S ty, S eps, S &vx, S &vy, ActiveSet *rec)
+// The LP's answer without any line: in the direction (ox, oy) on the speed
+// circle (mode 1), or the point (ox, oy) itself, scaled onto the circle when
+// it lies outside.
+template <bool REC, class S>
+__device__ __forceinline__ void lp2_start(S vmax, int mode, S ox, S oy, S &x, S &y, ActiveSet *rec)
 {
-    S x, y;
     if (mode == 1) {
         x = ox * vmax;
         y = oy * vmax;
@@ -1169,6 +1171,28 @@ __device__ __forceinline__ int lp2(const Src &src, int m, S vmax, int mode, S ox
             if (REC) rec->kind = kFree;
         }
     }
+}
+
+// Line i was re-solved (lp1_point's `how` and bounding line).
+__device__ __forceinline__ void lp2_record(int i, int bound, int mode, int how, ActiveSet *rec)
+{
+    rec->a = i;
+    rec->b = bound;
+    if (mode == 0)
+        rec->kind = how == 0 ? kLine : (bound >= 0 ? kLineLine : kLineDisc);
+    else
+        rec->kind = how == 3 ? kTie : (bound >= 0 ? kProjProj : kProjDisc);
+}
+
+// Incremental 2D LP over lines 0..m-1 of `src` and the disc |v| <= vmax.
+// Returns the first infeasible line, or m; v keeps its pre-failure value.
+// With REC the active set of the result is written to *rec.
+template <bool REC, class S, class Src>
+__device__ __forceinline__ int lp2(const Src &src, int m, S vmax, int mode, S ox, S oy, S tx,
+                                   S ty, S eps, S &vx, S &vy, ActiveSet *rec)
+{
+    S x, y;
+    lp2_start<REC>(vmax, mode, ox, oy, x, y, rec);
     for (int i = 0; i < m; ++i) {
         typename LpVec<S>::T li;
         const bool valid = src.get(i, li);
@@ -1182,14 +1206,7 @@ __device__ __forceinline__ int lp2(const Src &src, int m, S vmax, int mode, S ox
             }
             x = nx;
             y = ny;
-            if (REC) {
-                rec->a = i;
-                rec->b = bound;
-                if (mode == 0)
-                    rec->kind = how == 0 ? kLine : (bound >= 0 ? kLineLine : kLineDisc);
-                else
-                    rec->kind = how == 3 ? kTie : (bound >= 0 ? kProjProj : kProjDisc);
-            }
+            if (REC) lp2_record(i, bound, mode, how, rec);
         }
     }
     vx = x;
@@ -1343,6 +1360,57 @@ __device__ __forceinline__ float4 group_line(const float4 (&l)[NL], int k)
                        __shfl(v.w, k % G, G));
 }
 
+// lp2 by the group: lane c holds lines c, c + G, ... of the m in ln, valid where
+// bit r of `valid` is set (only below m).
+template <bool REC, int G, int NL>
+__device__ __forceinline__ int group_lp2(const float4 (&ln)[NL], uint32_t valid, int c, int m,
+                                         float vmax, int mode, float ox, float oy, float tx,
+                                         float ty, float eps, float &vx, float &vy, ActiveSet *rec)
+{
+    const float slack = vmax * FeasSlack<float>::v;
+    const float pslack = vmax * 0x1p-20f;
+    lp2_start<REC>(vmax, mode, ox, oy, vx, vy, rec);
+    for (int k = 0;; ++k) {
+        // the next violated line
+        int next = m;
+#pragma unroll
+        for (int r = NL - 1; r >= 0; --r) {
+            const int j = c + G * r;
+            if (G * r < m) {  // the same in the whole group
+                const bool out = det2(ln[r].z, ln[r].w, ln[r].x - vx, ln[r].y - vy) > 0.0f;
+                next = ((valid >> r) & 1u) && j >= k && out ? j : next;
+            }
+        }
+        k = group_min<G>(next);
+        if (k >= m) return m;
+        const float4 lk = group_line<G>(ln, k);
+        float tl, tr;
+        if (!lp1_disc<float>(lk, vmax, tl, tr)) return k;
+        const float tl0 = tl, tr0 = tr;
+        int sl = -1, sr = -1;
+        bool apart = false;
+#pragma unroll
+        for (int r = 0; r < NL; ++r) {
+            const int j = c + G * r;
+            if (G * r < k)
+                lp1_cut<float>(j, ln[r], ((valid >> r) & 1u) && j < k, lk, eps, pslack, tl, tr, sl,
+                               sr, apart);
+        }
+        const float gl = group_max<G>(tl), gr = group_min<G>(tr);
+        if (REC) {
+            // the first line that sets each end
+            const int fl = group_min<G>(sl >= 0 && tl == gl ? sl : INT_MAX);
+            const int fr = group_min<G>(sr >= 0 && tr == gr ? sr : INT_MAX);
+            sl = gl > tl0 && fl != INT_MAX ? fl : -1;
+            sr = gr < tr0 && fr != INT_MAX ? fr : -1;
+        }
+        if (group_any<G>(apart) || gl > gr + slack) return k;
+        int how, bound;
+        lp1_point<float>(lk, mode, ox, oy, tx, ty, eps, gl, gr, sl, sr, vx, vy, how, bound);
+        if (REC) lp2_record(k, bound, mode, how, rec);
+    }
+}
+
 // LP3 of one agent by the group this lane belongs to (c = its lane there); all
 // arguments are the same in the group's lanes.  ls reads the agent's lines.  NL:
 // lines per lane.
@@ -1360,8 +1428,6 @@ __device__ __forceinline__ void group_lp3(const LdsLines<BLOCK, ACC> &ls, int c,
     // decide whether a later tied line triggers a re-solve, and the re-solve
     // then jumps to another vertex of the tie
     const float tol = vmax * FeasSlack<float>::v;
-    const float slack = vmax * FeasSlack<float>::v;
-    const float pslack = vmax * 0x1p-20f;
     float4 ln[NL];
 #pragma unroll
     for (int r = 0; r < NL; ++r) ln[r] = ls.line(min(c + G * r, m - 1));
@@ -1390,60 +1456,10 @@ __device__ __forceinline__ void group_lp3(const LdsLines<BLOCK, ACC> &ls, int c,
             }
         }
         // LP2 over the boundaries, objective: deepest into line i
-        const float ox = -li.w, oy = li.z;
-        float nx = ox * vmax, ny = oy * vmax;
-        ActiveSet inner{kDir, -1, -1, -1};
-        bool solved = true;
-        for (int k = 0;;) {
-            int next = i;
-#pragma unroll
-            for (int r = NL - 1; r >= 0; --r) {
-                const int j = c + G * r;
-                if (G * r < i) {
-                    const bool out = det2(bd[r].z, bd[r].w, bd[r].x - nx, bd[r].y - ny) > 0.0f;
-                    next = ((valid >> r) & 1u) && j >= k && out ? j : next;
-                }
-            }
-            k = group_min<G>(next);
-            if (k >= i) break;
-            const float4 lk = group_line<G>(bd, k);
-            float tl, tr;
-            solved = lp1_disc<float>(lk, vmax, tl, tr);
-            if (!solved) break;
-            const float tl0 = tl, tr0 = tr;
-            int sl = -1, sr = -1;
-            bool apart = false;
-#pragma unroll
-            for (int r = 0; r < NL; ++r) {
-                const int j = c + G * r;
-                if (G * r < k)
-                    lp1_cut<float>(j, bd[r], ((valid >> r) & 1u) && j < k, lk, eps, pslack, tl, tr,
-                                   sl, sr, apart);
-            }
-            if (REC) {
-                // the first line that sets each end
-                const float gl = group_max<G>(tl), gr = group_min<G>(tr);
-                const int fl = group_min<G>(sl >= 0 && tl == gl ? sl : INT_MAX);
-                const int fr = group_min<G>(sr >= 0 && tr == gr ? sr : INT_MAX);
-                sl = gl > tl0 && fl != INT_MAX ? fl : -1;
-                sr = gr < tr0 && fr != INT_MAX ? fr : -1;
-                tl = gl;
-                tr = gr;
-            } else {
-                tl = group_max<G>(tl);
-                tr = group_min<G>(tr);
-            }
-            solved = !(group_any<G>(apart) || tl > tr + slack);
-            if (!solved) break;
-            int how, bound;
-            lp1_point<float>(lk, 1, ox, oy, tx, ty, eps, tl, tr, sl, sr, nx, ny, how, bound);
-            if (REC) {
-                inner.a = k;
-                inner.b = bound;
-                inner.kind = how == 3 ? kTie : (bound >= 0 ? kProjProj : kProjDisc);
-            }
-            ++k;
-        }
+        float nx, ny;
+        ActiveSet inner;
+        bool solved = group_lp2<REC, G>(bd, valid, c, i, vmax, 1, -li.w, li.z, tx, ty, eps, nx, ny,
+                                        &inner) == i;
         if (!solved) {
             // failed in FP32 only: solve it again in double (ProjLinesD), the
             // same walk in each of the group's lanes

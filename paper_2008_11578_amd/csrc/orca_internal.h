@@ -39,9 +39,45 @@ __host__ __device__ inline int agent_tag(int i, int cls) { return (i << 1) | (cl
 __device__ __forceinline__ int tag_index(float z) { return (int)(__float_as_uint(z) >> 1); }
 __device__ __forceinline__ int tag_class(float z) { return __float_as_int(z) & 1; }
 
+// A velocity within the speed cap: (vx, vy) itself when |v| <= v_max (the
+// test in double from the FP32 values, products exact), else scaled onto the
+// cap and rounded to FP32, then moved toward zero one ulp at a time until the
+// test holds.  The ORCA lines an agent takes no responsibility for (f = 0)
+// all pass through its own velocity; a velocity the previous step left on
+// the speed circle lies outside it by a few FP32 ulps half of the time, and
+// the LP's feasible set around that apex would then be thinner than FP32
+// resolves.  Inside the cap, the apex is a feasible point exactly.
+__device__ __forceinline__ void cap_velocity(float &vx, float &vy, float vmax)
+{
+    const double vm2 = (double)vmax * (double)vmax;
+    const double d = (double)vx * (double)vx + (double)vy * (double)vy;
+    if (!(d > vm2)) return;
+    const double s = (double)vmax / sqrt(d);
+    float x = (float)((double)vx * s), y = (float)((double)vy * s);
+    for (int it = 0; it < 16 && (double)x * (double)x + (double)y * (double)y > vm2; ++it) {
+        if (fabsf(x) >= fabsf(y))
+            x = nextafterf(x, 0.0f);
+        else
+            y = nextafterf(y, 0.0f);
+    }
+    vx = x;
+    vy = y;
+}
+
+// Agent i's scan position and record at place `pos` of the cell-ordered copies;
+// velocities taken within the speed cap.
+__device__ __forceinline__ void write_record(const orca_agents_in &in, int i, uint32_t pos,
+                                             float2 *__restrict__ s0, float4 *__restrict__ s1)
+{
+    s0[pos] = make_float2(in.px[i], in.py[i]);
+    float vx = in.vx[i], vy = in.vy[i];
+    cap_velocity(vx, vy, in.max_speed[i]);
+    s1[pos] = make_float4(vx, vy, __int_as_float(agent_tag(i, (int)in.cls[i])), in.radius[i]);
+}
+
 // Byte offsets of the workspace regions (all 256-byte aligned).
 struct Layout {
-    size_t meta, partial, queue, cell, rank, count, start, tiles, s0, s1, guess, total;
+    size_t meta, partial, cell, rank, count, start, tiles, s0, s1, guess, total;
     int64_t n, n_scenes, max_cells, n_tiles;
 };
 
@@ -195,7 +231,6 @@ inline int64_t default_max_cells(int64_t n) { return n * 2 > 4096 ? n * 2 : 4096
 struct Work {
     GridMeta *meta;
     float4 *partial;
-    uint32_t *queue;   // 8 tile counters (one per XCD) of the persistent kernel
     uint32_t *cell;
     uint32_t *rank;
     uint32_t *count;
@@ -229,14 +264,99 @@ hipError_t launch_scan_scatter(const orca_agents_in &in, int n, const Layout &L,
 hipError_t launch_batched(const orca_agents_in &in, const orca_agents_out &out, int n,
                           const int32_t *scene_off, int n_scenes, const orca_params *params,
                           int k_max, bool acc, int block, const Layout &L, const Work &w,
-                          int32_t *error_flag, int mode, const orca_step_events *ev,
+                          int32_t *error_flag, const orca_step_events *ev,
                           hipStream_t stream);
+
+// What the batched step kernels read.
+struct BatchArgs {
+    orca_agents_in in;
+    orca_agents_out out;
+    const GridMeta *meta;
+    const orca_params *prm;
+    const int32_t *off;
+    int S;
+    int n;
+    const uint32_t *start;
+    const float2 *s0;
+    const float4 *s1;
+    float *guess;  // per-agent radius of the neighbour scan kept between steps
+};
+
+// Scene of caller index i: the largest s with off[s] <= i (off ascending).
+__device__ __forceinline__ int scene_of(const int32_t *__restrict__ off, int S, int i)
+{
+    int lo = 0, hi = S - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= i)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+// Scene of caller index i given the scene s0 of an index <= i (off
+// ascending): a walk forward from s0, a step or two for the indices of one
+// tile, instead of a binary search per index.
+__device__ __forceinline__ int scene_from(const int32_t *__restrict__ off, int S, int s0, int i)
+{
+    int s = s0;
+    while (s + 1 < S && off[s + 1] <= i) ++s;
+    return s;
+}
 
 // Fused neighbour search + half-planes + LP + update for one scene; with
 // nbr / cnt (nullable) also the neighbour lists the step used.
 hipError_t launch_step(const orca_agents_in &in, const orca_agents_out &out, int n,
                        const orca_params &p, const Layout &L, const Work &w, int32_t *nbr,
                        int32_t *cnt, hipStream_t stream);
+
+// Small crowds: a group of lanes per agent, over the grid or (whole) over the
+// copies that launch_pack makes in caller order.  The largest crowd that takes
+// the form, by what it costs beside a lane per agent (whole calls in us, group /
+// lane): a lane per agent is one wavefront per SIMD up to 65,536 agents and
+// takes a wavefront's latency however few they are; a group of 16 does the
+// same work in more instructions.
+//   step          66,560 mixed 82 / 88, k 10 67 / 68, dense 94 / 96; 100,000
+//                 104 / 105, 85 / 76, 115 / 102
+//   hard lines    100,000 129 / 149, 150,000 168 / 176, 200,000 211 / 191
+//   adjoint       50,000 103 / 115 (k 10), 136 / 134 (dense), 72,000 124 / 117,
+//                 167 / 151; hard lines 72,000 193 / 200, 100,000 237 / 209
+//   lists         50,000 45 / 61 (k 16), 72,000 54 / 47; k 32 (a network of 64)
+//                 200,000 146 / 158, 300,000 203 / 217
+//   batched step  see launch_batched
+// Without a grid, each agent scanning the whole crowd: 1,500 agents 31 / 34, 2,500
+// 40 / 35 (256 agents: 23 us, bound by the host).
+constexpr int kGroup = 16;  // lanes per agent
+constexpr int kWholeMax = 2048;
+constexpr int kGroupStepMax = 72000, kGroupStepMaxHard = 131072;
+constexpr int kGroupAdjointMax = 49152, kGroupAdjointMaxHard = 72000;
+constexpr int kGroupListMax = 65536, kGroupListMaxLarge = 262144;
+constexpr int kGroupBatchMax = 98304;
+inline bool has_hard_lines(const orca_params &p)
+{
+    return p.accel[0] > 0.0f || p.accel[1] > 0.0f || p.turn[0] > 0.0f || p.turn[1] > 0.0f;
+}
+// What a scan of the whole crowd needs of a grid.
+__device__ __forceinline__ GridMeta whole_crowd(int n, float rn)
+{
+    GridMeta g{};
+    g.rn = rn;
+    g.rn2 = (double)rn * (double)rn;
+    g.n = n;
+    g.seg_end = (uint32_t)n;
+    return g;
+}
+hipError_t launch_pack(const orca_agents_in &in, int n, const Work &w, hipStream_t stream);
+hipError_t launch_step_group(const orca_agents_in &in, const orca_agents_out &out, int n,
+                             const orca_params &prm, const Work &w, bool whole, int32_t *nbr,
+                             int32_t *cnt, hipStream_t stream);
+
+// The flat batched step by groups of lanes.
+hipError_t launch_list_group(int n, const orca_params &prm, const Work &w, int32_t *nbr,
+                             int32_t *cnt, hipStream_t stream);
+hipError_t launch_batched_group(const BatchArgs &a, int k_max, bool acc, hipStream_t stream);
 
 // Neighbour lists only (caller order), for orca_build_grid.
 hipError_t launch_knn_export(const orca_agents_in &in, int n, const orca_params &p,

@@ -20,19 +20,20 @@ def _scenes(total, params, seed):
     return off, {k: np.concatenate([getattr(p, k) for p in parts]) for k in parts[0].arrays()}
 
 
-@pytest.mark.parametrize("total", [65536, 65537])
-def test_batch_that_fits_the_device_at_once_equals_the_queued_form(total):
-    """Neighbour capacity 32 at 256 lanes takes 128 KB of LDS, so one workgroup
-    per CU: 256 of them hold 65,536 agents, one more agent goes to the
-    queues; the flat launch form never queues."""
+@pytest.mark.parametrize("total", [98304, 98305])
+def test_batch_by_groups_of_lanes_equals_a_lane_per_agent(total):
+    """Batches of up to 98,304 agents are stepped by groups of lanes, larger
+    ones by a lane per agent: every scene equals its plain step (itself by
+    groups up to 72,000 agents), and a workgroup size of 256 lanes with a
+    capacity of 32 neighbours gives the same."""
     import torch
     from paper_2008_11578_amd import orca
     p = scenarios.Params(dt=0.05, neighbor_dist=5.0, max_neighbors=16)
     off, cat = _scenes(total, p, seed=70)
     st = orca.State.from_arrays(cat)
     got = []
-    for mode in (0, 1):
-        b = orca.Batch(off, [p] * (len(off) - 1), mode=mode, block=256, k_tile=32)
+    for mode, block, k_tile in ((0, 0, 0), (1, 256, 32)):
+        b = orca.Batch(off, [p] * (len(off) - 1), mode=mode, block=block, k_tile=k_tile)
         status = torch.zeros(st.n, dtype=torch.uint8, device="cuda")
         out = orca.step_batched(st, b, orca.Workspace(st.n, n_scenes=len(off) - 1), status=status)
         torch.cuda.synchronize()
@@ -40,6 +41,12 @@ def test_batch_that_fits_the_device_at_once_equals_the_queued_form(total):
         got.append([getattr(out, k) for k in FIELDS] + [status])
     for a, b in zip(*got):
         assert torch.equal(a, b)
+    for a, z in zip(off[:-1], off[1:]):
+        part = orca.State(**{k: getattr(st, k)[a:z].clone() for k in orca.STATE_FIELDS})
+        o1 = orca.step(part, p, orca.Workspace(part.n))
+        torch.cuda.synchronize()
+        for k, v in zip(FIELDS, got[0]):
+            assert torch.equal(v[a:z], getattr(o1, k)), (a, k)
 
 
 @pytest.mark.parametrize("k", [1, 4, 5, 16, 20, 32])
@@ -112,3 +119,48 @@ def test_kept_scan_radius_changes_no_result(k):
                 assert torch.equal(a, b), (rep, again)
             for a, b in zip(backward(st, wsb), backward(st, orca.Workspace(n, backward=True))):
                 assert torch.equal(a, b), (rep, again)
+
+
+@pytest.mark.parametrize("caps", [False, True])
+@pytest.mark.parametrize("n,k,side", [(1, 4, 1.0), (2, 1, 1.0), (5, 32, 2.0), (66, 16, 4.0),
+                                      (257, 10, 30.0), (300, 17, 2.0), (2048, 20, 40.0),
+                                      (2049, 20, 40.0), (5003, 16, 100.0), (4000, 24, 12.0)])
+def test_small_crowd_by_groups_of_lanes_equals_a_lane_per_agent(n, k, side, caps):
+    """The same crowd alone (a group of lanes per agent; without a grid up to
+    2,048 agents) and with 140,000 agents standing far away, which makes the
+    call take a lane per agent: velocities, lists and the VJP agree bit for bit.
+    300 agents within 2 m and 4,000 within 12 m hold more than a group's
+    buffer (64) in every circle; a hundred stand at one place, more than fit
+    any cut of it."""
+    import torch
+    from paper_2008_11578_amd import orca
+    p = scenarios.Params(dt=0.1, neighbor_dist=4.0, max_neighbors=k, pref_is_goal=k % 2,
+                         accel=(2.0, 1.0) if caps else (0.0, 0.0),
+                         turn=(0.0, 1.0) if caps else (0.0, 0.0))
+    sc = scenarios.random_state(n, side, seed=40 + n + k, n_vehicles=n // 10, params=p)
+    if n == 300:
+        sc.px[100:200], sc.py[100:200] = sc.px[0], sc.py[0]
+    m = 140000
+    far = {f: np.zeros(m, v.dtype) for f, v in sc.arrays().items()}
+    far["px"] = (1000.0 + 10.0 * (np.arange(m) % 400)).astype(np.float32)
+    far["py"] = (1000.0 + 10.0 * (np.arange(m) // 400)).astype(np.float32)
+    far["pref_x"], far["pref_y"] = far["px"].copy(), far["py"].copy()
+    far["radius"] += np.float32(0.3)
+    far["max_speed"] += np.float32(1.5)
+    both = {f: np.concatenate([v, far[f]]) for f, v in sc.arrays().items()}
+    gen = np.random.Generator(np.random.PCG64(9))
+    cot = [gen.standard_normal(n).astype(np.float32) for _ in range(4)]
+    got = []
+    for arrays in (sc.arrays(), both):
+        st = orca.State.from_arrays(arrays)
+        ws, wsb = orca.Workspace(st.n), orca.Workspace(st.n, backward=True)
+        for again in range(2):  # the second call from the kept radii
+            out, nbr, cnt = orca.step_nbr(st, p, ws)
+            g = [torch.cat([torch.from_numpy(c), torch.zeros(st.n - n)]).cuda() for c in cot]
+            acc = [torch.zeros(st.n, device="cuda") for _ in range(2)]
+            b = orca.step_backward(st, p, wsb, *g, *acc, torch.zeros(1, device="cuda"))
+            torch.cuda.synchronize()
+            got.append([t[:n] for t in (*[getattr(out, f) for f in FIELDS], nbr, cnt, *b, *acc)])
+    for other in got[1:]:
+        for q, (a, b) in enumerate(zip(got[0], other)):
+            assert torch.equal(a, b), q
