@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_count(const float *__restrict_
     const int cy = cell_axis(py[i], g.y0, g.inv_cs, g.ny);
     const uint32_t c = (uint32_t)(g.cell_base + cx + g.nx * cy);
     cell[i] = c;
-    rank[i] = atomicAdd(&count[c], 1u);
+    rank[i] = count_run(c, count);
 }
 
 // The agent at cell-order position s (all lanes of the wavefront call it; one

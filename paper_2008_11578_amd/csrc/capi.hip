@@ -169,8 +169,7 @@ int check_buf(const orca_agents_buf *b)
     return ORCA_OK;
 }
 
-// Workspace of the lifecycle entry points: the grid of n agents, then the
-// lifecycle buffers.
+// Workspace of the overlap statistics: the grid of n agents, then their buffers.
 Layout life_layout(int64_t n) { return make_layout(n > 0 ? n : 1, 0, 0); }
 
 // Cell count that keeps the grid within what the 32-bit indices address.
@@ -425,7 +424,7 @@ int orca_step_backward_ex(const orca_agents_in *in, int32_t n, const orca_params
 size_t orca_lifecycle_workspace_bytes(int32_t n, int32_t n_cand)
 {
     if (n < 0 || n_cand < 0) return 0;
-    return align_up(life_layout(n).total) + lifecycle_extra_bytes(n, n_cand);
+    return lifecycle_bytes(n, n_cand);
 }
 
 int orca_remove_arrived(const orca_agents_in *in, const orca_agents_buf *out, int32_t n,
@@ -435,11 +434,10 @@ int orca_remove_arrived(const orca_agents_in *in, const orca_agents_buf *out, in
     if (n < 0 || !n_alive || !ws) return ORCA_EINVAL;
     if (n > 0 && (check_in(in) != ORCA_OK || check_buf(out) != ORCA_OK)) return ORCA_EINVAL;
     if (ws_bytes < orca_lifecycle_workspace_bytes(n, 0)) return ORCA_EWORKSPACE;
-    void *extra = (char *)ws + align_up(life_layout(n).total);
     const orca_agents_in no_in{};
     const orca_agents_buf no_out{};
     if (launch_remove_arrived(n > 0 ? *in : no_in, n > 0 ? *out : no_out, n, n_alive, old_to_new,
-                              extra, stream) != hipSuccess)
+                              ws, stream) != hipSuccess)
         return ORCA_EHIP;
     return ORCA_OK;
 }
@@ -454,13 +452,10 @@ int orca_spawn(const orca_agents_buf *state, int32_t n, int32_t capacity,
     if (n + n_cand > 0 && check_buf(state) != ORCA_OK) return ORCA_EINVAL;
     if (n_cand > 0 && check_in(cand) != ORCA_OK) return ORCA_EINVAL;
     if (ws_bytes < orca_lifecycle_workspace_bytes(n, n_cand)) return ORCA_EWORKSPACE;
-    const Layout L = life_layout(n);
-    const Work w = bind(L, ws);
-    void *extra = (char *)ws + align_up(L.total);
     const orca_agents_in no_cand{};
     const orca_agents_buf no_state{};
     if (launch_spawn(n + n_cand > 0 ? *state : no_state, n, n_cand > 0 ? *cand : no_cand, n_cand,
-                     t_clear, n_total, accepted, L, w, extra, stream) != hipSuccess)
+                     t_clear, n_total, accepted, ws, stream) != hipSuccess)
         return ORCA_EHIP;
     return ORCA_OK;
 }

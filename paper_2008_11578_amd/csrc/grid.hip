@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_count(const float *__restrict__
     const int cy = cell_axis(py[i], g.y0, g.inv_cs, g.ny);
     const uint32_t c = (uint32_t)(cx + g.nx * cy);
     cell[i] = c;
-    rank[i] = atomicAdd(&count[c], 1u);
+    rank[i] = count_run(c, count);
 }
 
 constexpr int kPer = kScanTile / kBlock;  // 8 cells per thread

@@ -5,10 +5,11 @@
 //  - leaving: a stable compaction (per-block counts, one scan block, move),
 //    with the arrival test evaluated in double without fused multiply-add so
 //    that the decision is exactly reproducible;
-//  - entering: candidates are checked against the current agents through a
-//    uniform grid whose query radius is computed on the device from the
-//    largest radii and speed caps, then against each other: every candidate
-//    lists the earlier candidates it conflicts with, and one workgroup
+//  - entering: the candidates (a few thousand, in the start regions) are put
+//    into a grid whose cells are as large as the widest clearance, computed on
+//    the device from the largest radii and speed caps.  Every agent looks up
+//    the candidates around it and blocks those too close; every candidate
+//    lists the earlier candidates it conflicts with; and one workgroup
 //    settles the first-come decisions in rounds (a candidate enters once all
 //    its earlier conflicts are rejected, and is rejected as soon as one of
 //    them enters), which equals taking the candidates one by one in order.
@@ -22,37 +23,56 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kScanThreads = 1024;
 constexpr int kConfCap = 16;  // earlier conflicts listed per candidate
-constexpr uint8_t kUndecided = 0, kAccepted = 1, kRejected = 2;
+constexpr int kUndecided = 0, kAccepted = 1, kRejected = 2;
 constexpr int kBoundBlocksMax = 1024;
+
+// Grid over the spawn candidates.
+constexpr int kCandCells = 8192;  // histogram of 32 KB in one workgroup's LDS
+struct CandGrid {
+    double x0, y0, inv;  // origin and 1 / cell size
+    int nx, ny;
+};
 
 struct LifeBufs {
     uint32_t *block_count;  // leaving: survivors per block, then their offsets
     float4 *partial;        // entering: per-block maxima
-    float *bounds;          // entering: max r, max s (agents), max r, max s (candidates), D_max
-    uint8_t *blocked;       // entering: candidate blocked by a current agent
+    float4 *box;            // entering: per-block bounding boxes of the candidates
+    CandGrid *grid;
+    uint32_t *start;        // entering: first candidate of each cell (+ 1 entry)
+    float4 *cand;           // entering: candidates in cell order (x, y, radius, speed cap)
+    int32_t *index;         // entering: their places in the caller's order
+    uint8_t *blocked;       // entering, in cell order: blocked by a current agent
+    int32_t *decision;      // entering: places in cell order; then kUndecided, kAccepted or
+                            // kRejected; then the place of an accepted candidate or -1
     int32_t *conf_count;    // entering: earlier conflicting candidates (may exceed the cap)
     int32_t *conf;          // entering: their indices, kConfCap per candidate
 };
 
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-LifeBufs bind_life(int64_t n, int64_t n_cand, void *base)
+LifeBufs bind_life(int64_t n, int64_t n_cand, void *base, size_t *bytes = nullptr)
 {
     char *b = (char *)base;
     LifeBufs r;
     size_t o = 0;
-    const int64_t nb = (n + kBlock - 1) / kBlock;
-    r.block_count = (uint32_t *)(b + o);
-    o += a256(sizeof(uint32_t) * (size_t)(nb + 1));
-    r.partial = (float4 *)(b + o);
-    o += a256(sizeof(float4) * kBoundBlocksMax);
-    r.bounds = (float *)(b + o);
-    o += a256(sizeof(float) * 8);
-    r.blocked = (uint8_t *)(b + o);
-    o += a256((size_t)n_cand);
-    r.conf_count = (int32_t *)(b + o);
-    o += a256(sizeof(int32_t) * (size_t)n_cand);
-    r.conf = (int32_t *)(b + o);
+    auto take = [&](size_t len) {
+        char *p = b + o;
+        o += a256(len);
+        return p;
+    };
+    const size_t nc = (size_t)n_cand;
+    r.block_count = (uint32_t *)take(sizeof(uint32_t) * (size_t)((n + kBlock - 1) / kBlock + 1));
+    r.partial = (float4 *)take(sizeof(float4) * kBoundBlocksMax);
+    r.box = (float4 *)take(sizeof(float4) * kBoundBlocksMax);
+    r.grid = (CandGrid *)take(sizeof(CandGrid));
+    r.start = (uint32_t *)take(sizeof(uint32_t) * (kCandCells + 1));
+    r.cand = (float4 *)take(sizeof(float4) * nc);
+    r.index = (int32_t *)take(sizeof(int32_t) * nc);
+    r.blocked = (uint8_t *)take(nc);
+    r.decision = (int32_t *)take(sizeof(int32_t) * nc);
+    r.conf_count = (int32_t *)take(sizeof(int32_t) * nc);
+    r.conf = (int32_t *)take(sizeof(int32_t) * kConfCap * nc);
+    if (bytes) *bytes = o;
     return r;
 }
 
@@ -157,174 +177,325 @@ __global__ __launch_bounds__(kBlock) void k_arrive_move(orca_agents_in in, orca_
     if (old_to_new) old_to_new[i] = keep ? (int32_t)rank : -1;
 }
 
-// (entering 1a) per-block largest radius and speed cap of the agents and of
-// the candidates
+// (entering 1) per block: largest radius and speed cap of the agents and of
+// the candidates, and the candidates' bounding box
 __global__ __launch_bounds__(kBlock) void k_spawn_bounds(const float *__restrict__ r_a,
                                                           const float *__restrict__ s_a, int n,
-                                                          const float *__restrict__ r_c,
-                                                          const float *__restrict__ s_c, int nc,
-                                                          float4 *__restrict__ partial)
+                                                          orca_agents_in cand, int nc,
+                                                          float4 *__restrict__ partial,
+                                                          float4 *__restrict__ box)
 {
     float4 m = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float4 b = make_float4(INFINITY, INFINITY, -INFINITY, -INFINITY);
     const int stride = gridDim.x * kBlock;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         m.x = fmaxf(m.x, r_a[i]);
         m.y = fmaxf(m.y, s_a[i]);
     }
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < nc; i += stride) {
-        m.z = fmaxf(m.z, r_c[i]);
-        m.w = fmaxf(m.w, s_c[i]);
+        m.z = fmaxf(m.z, cand.radius[i]);
+        m.w = fmaxf(m.w, cand.max_speed[i]);
+        const float x = cand.px[i], y = cand.py[i];
+        b = make_float4(fminf(b.x, x), fminf(b.y, y), fmaxf(b.z, x), fmaxf(b.w, y));
     }
     // the bounding-box reduction's (min, min, max, max) applied to (-x, -y, z, w)
     float4 q = block_bbox<kBlock>(make_float4(-m.x, -m.y, m.z, m.w));
     if (threadIdx.x == 0) partial[blockIdx.x] = make_float4(-q.x, -q.y, q.z, q.w);
+    __syncthreads();  // the reduction's LDS is used again
+    b = block_bbox<kBlock>(b);
+    if (threadIdx.x == 0) box[blockIdx.x] = b;
 }
 
-// (entering 1b) the maxima, and the grid's query radius D_max (rounded up)
-__global__ __launch_bounds__(kBlock) void k_spawn_dmax(const float4 *__restrict__ partial, int np,
-                                                        float t_clear, float *__restrict__ bounds)
+// Cell of a place along one axis, -2 or n + 1 for places with no cell beside them
+// (and for NaN).  Without a finite box (inv 0) every place is in cell 0.
+__device__ __forceinline__ int cand_axis(float v, double v0, double inv, int n)
 {
-    float4 m = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int k = threadIdx.x; k < np; k += kBlock) {
-        const float4 v = partial[k];
-        m.x = fmaxf(m.x, v.x);
-        m.y = fmaxf(m.y, v.y);
-        m.z = fmaxf(m.z, v.z);
-        m.w = fmaxf(m.w, v.w);
-    }
-    float4 q = block_bbox<kBlock>(make_float4(-m.x, -m.y, m.z, m.w));
-    if (threadIdx.x != 0) return;
-    bounds[0] = -q.x;
-    bounds[1] = -q.y;
-    bounds[2] = q.z;
-    bounds[3] = q.w;
-    const double d = ((double)bounds[2] + (double)bounds[0]) +
-                     (double)t_clear * ((double)bounds[3] + (double)bounds[1]);
-    // a positive radius for the grid even when everything is a point at rest
-    bounds[4] = fmaxf(nextafterf((float)d, INFINITY) * (1.0f + 1e-6f), 1e-3f);
+    if (inv == 0.0) return 0;
+    return (int)fmin(fmax(floor(((double)v - v0) * inv), -2.0), (double)(n + 1));
 }
 
-// (entering 2) candidates blocked by a current agent: each lane scans the
-// grid disc of its own largest possible clearance.
-__global__ __launch_bounds__(kBlock) void k_spawn_check(orca_agents_in cand, int nc,
-                                                         const float *__restrict__ a_max_speed,
-                                                         const GridMeta *__restrict__ meta,
-                                                         const uint32_t *__restrict__ start,
-                                                         const float2 *__restrict__ s0,
-                                                         const float4 *__restrict__ s1,
-                                                         const float *__restrict__ bounds,
-                                                         float t_clear, int n,
-                                                         uint8_t *__restrict__ blocked,
-                                                         int32_t *__restrict__ conf_count)
+// (entering 2) one workgroup: the widest clearance D_max, a grid over the
+// candidates with cells at least that large (so whoever is too close to a
+// candidate stands in the 3 x 3 cells around it), and each candidate's place in
+// cell order.  The rounding of the cell coordinates is covered by the cells' margin
+// of 1e-6.
+__global__ __launch_bounds__(kScanThreads) void k_spawn_grid(
+    orca_agents_in cand, int nc, float t_clear, const float4 *__restrict__ partial,
+    const float4 *__restrict__ box, int np, CandGrid *__restrict__ grid,
+    uint32_t *__restrict__ start, int32_t *__restrict__ place)
+{
+    __shared__ uint32_t count[kCandCells];
+    __shared__ CandGrid gs;
+    float4 m = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float4 b = make_float4(INFINITY, INFINITY, -INFINITY, -INFINITY);
+    for (int k = threadIdx.x; k < np; k += kScanThreads) {
+        const float4 v = partial[k], w = box[k];
+        m = make_float4(fmaxf(m.x, v.x), fmaxf(m.y, v.y), fmaxf(m.z, v.z), fmaxf(m.w, v.w));
+        b = make_float4(fminf(b.x, w.x), fminf(b.y, w.y), fmaxf(b.z, w.z), fmaxf(b.w, w.w));
+    }
+    for (int k = threadIdx.x; k < kCandCells; k += kScanThreads) count[k] = 0u;
+    const float4 q = block_bbox<kScanThreads>(make_float4(-m.x, -m.y, m.z, m.w));
+    __syncthreads();
+    b = block_bbox<kScanThreads>(b);
+    if (threadIdx.x == 0) {
+        // clearance of the largest radii and speed caps, of a candidate beside
+        // an agent or another candidate
+        const double r = fmax(-(double)q.x, (double)q.z), s = fmax(-(double)q.y, (double)q.w);
+        const double d = ((double)q.z + r) + (double)t_clear * ((double)q.w + s);
+        const bool finite = isfinite(b.x) && isfinite(b.y) && isfinite(b.z) && isfinite(b.w) &&
+                            isfinite(d);
+        const double w = finite ? (double)b.z - (double)b.x : 0.0;
+        const double h = finite ? (double)b.w - (double)b.y : 0.0;
+        // a positive size even when everything is a point at rest; larger where
+        // the box would need more cells (or one cell, by its size, for all)
+        double c = fmax(d * (1.0 + 1e-6), fmax(1e-3, fmax(w, h) * 1e-6));
+        for (int it = 0; it < 200 && (floor(w / c) + 1.0) * (floor(h / c) + 1.0) > kCandCells; ++it)
+            c *= 1.125;
+        gs.x0 = finite ? (double)b.x : 0.0;
+        gs.y0 = finite ? (double)b.y : 0.0;
+        gs.inv = finite ? 1.0 / c : 0.0;
+        gs.nx = (int)(floor(w * gs.inv) + 1.0);
+        gs.ny = (int)(floor(h * gs.inv) + 1.0);
+        if ((double)gs.nx * (double)gs.ny > (double)kCandCells) gs.nx = gs.ny = 1;
+        *grid = gs;
+    }
+    __syncthreads();
+    const CandGrid g = gs;
+    // a thread's candidates are loaded together (their latencies overlap); an
+    // index past the last candidate repeats it and is not used
+    constexpr int kMine = ORCA_SPAWN_MAX / kScanThreads;
+    float px[kMine], py[kMine];
+    uint32_t at[kMine];  // cell (13 bits and more) and rank inside it
+#pragma unroll
+    for (int k = 0; k < kMine; ++k) {
+        const int c = min(k * kScanThreads + (int)threadIdx.x, nc - 1);
+        px[k] = cand.px[c];
+        py[k] = cand.py[c];
+    }
+#pragma unroll
+    for (int k = 0; k < kMine; ++k) {
+        const int cx = min(max(cand_axis(px[k], g.x0, g.inv, g.nx), 0), g.nx - 1);
+        const int cy = min(max(cand_axis(py[k], g.y0, g.inv, g.ny), 0), g.ny - 1);
+        at[k] = (uint32_t)(cx + g.nx * cy);
+        if (k * kScanThreads + (int)threadIdx.x < nc) at[k] |= atomicAdd(&count[at[k]], 1u) << 14;
+    }
+    __syncthreads();
+    // exclusive scan of the histogram, kCandCells / kScanThreads cells a thread
+    constexpr int kPer = kCandCells / kScanThreads;
+    uint32_t v[kPer], sum = 0, tot;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        v[k] = count[threadIdx.x * kPer + k];
+        sum += v[k];
+    }
+    uint32_t run = block_excl_scan<kScanThreads>(sum, &tot);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        count[threadIdx.x * kPer + k] = run;
+        start[threadIdx.x * kPer + k] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == 0) start[kCandCells] = (uint32_t)nc;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kMine; ++k) {
+        const int c = k * kScanThreads + threadIdx.x;
+        if (c < nc) place[c] = (int32_t)(count[at[k] & 16383u] + (at[k] >> 14));
+    }
+}
+static_assert(kCandCells <= 1 << 14 && ORCA_SPAWN_MAX <= 1 << 18, "a cell and a rank share a word");
+
+// (entering 3) the candidates in cell order
+__global__ __launch_bounds__(kBlock) void k_spawn_sort(orca_agents_in cand, int nc,
+                                                        const int32_t *__restrict__ place,
+                                                        float4 *__restrict__ sorted,
+                                                        int32_t *__restrict__ index,
+                                                        uint8_t *__restrict__ blocked)
 {
     const int c = blockIdx.x * kBlock + threadIdx.x;
     if (c >= nc) return;
-    conf_count[c] = 0;
-    const float cx = cand.px[c], cy = cand.py[c], cr = cand.radius[c], cs = cand.max_speed[c];
-    const double t = (double)t_clear;
-    bool hit = false;
-    if (n > 0) {
-        const GridMeta g = *meta;
-        const double reach = ((double)cr + (double)bounds[0]) + t * ((double)cs + (double)bounds[1]);
-        const double r2 = reach * reach * (1.0 + 1e-9);
-        dev::scan_disc(g, start, s0, (double)cx, (double)cy, r2,
-                       [&](const float2 &a, uint32_t k, bool valid) {
-                           if (valid && !hit) {
-                               const float4 b = s1[k];
-                               hit = too_close(cx, cy, cr, cs, a.x, a.y, b.w,
-                                               a_max_speed[tag_index(b.z)], t);
-                           }
-                       });
-    }
-    blocked[c] = hit ? 1 : 0;
+    const int to = place[c];
+    sorted[to] = make_float4(cand.px[c], cand.py[c], cand.radius[c], cand.max_speed[c]);
+    index[to] = c;
+    blocked[to] = 0;
 }
 
-// (entering 3) each candidate's earlier conflicting candidates, found by
-// tiles of candidates staged in LDS.  A candidate blocked by the agents is
-// rejected whatever else happens, so lists are built for the unblocked ones
-// and hold unblocked candidates only.  blockIdx.y splits the earlier
-// candidates into chunks of kPairChunk tiles, so a list is filled through
-// its atomic counter (zeroed by k_spawn_check); the decision rounds read a
-// list as a set, and one that overflows sends its candidate to the
-// exhaustive test, so the order of the entries does not matter.
-constexpr int kPairChunk = 8;
+// Visits the candidates in the 3 x 3 cells around (x, y), a row of cells (one
+// range of the cell order) at a time and four candidates together: visit(t, e)
+// for positions t .. t + 3 below e.
+constexpr int kAhead = 4;
 
-__global__ __launch_bounds__(kBlock) void k_spawn_pairs(orca_agents_in cand, int nc, float t_clear,
+template <class F>
+__device__ __forceinline__ void near_candidates(const CandGrid &g, const uint32_t *__restrict__ start,
+                                                float x, float y, F &&visit)
+{
+    const int cx = cand_axis(x, g.x0, g.inv, g.nx), cy = cand_axis(y, g.y0, g.inv, g.ny);
+    const int xa = max(cx - 1, 0), xb = min(cx + 1, g.nx - 1);
+    for (int yy = max(cy - 1, 0); yy <= min(cy + 1, g.ny - 1); ++yy) {
+        const uint32_t e = start[yy * g.nx + xb + 1];
+        for (uint32_t t = start[yy * g.nx + xa]; t < e; t += kAhead) visit(t, e);
+    }
+}
+
+// (entering 4) every agent blocks the candidates it is too close to.  One pass
+// over the positions: only agents beside a candidate read more.  (A grid over
+// the agents and a look from each candidate: 1M agents and 16,384 candidates
+// 125 us, most of it the counting atomics of cells as wide as the clearance.)
+__global__ __launch_bounds__(kBlock) void k_spawn_block(const float *__restrict__ px,
+                                                         const float *__restrict__ py,
+                                                         const float *__restrict__ radius,
+                                                         const float *__restrict__ max_speed, int n,
+                                                         float t_clear,
+                                                         const CandGrid *__restrict__ grid,
+                                                         const uint32_t *__restrict__ start,
+                                                         const float4 *__restrict__ sorted,
+                                                         uint8_t *__restrict__ blocked)
+{
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n) return;
+    const CandGrid g = *grid;
+    const float x = px[i], y = py[i];
+    near_candidates(g, start, x, y, [&](uint32_t t, uint32_t e) {
+        float4 c[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) c[u] = sorted[min(t + u, e - 1u)];
+        const float r = radius[i], v = max_speed[i];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (t + u < e && too_close(c[u].x, c[u].y, c[u].z, c[u].w, x, y, r, v, (double)t_clear))
+                blocked[t + u] = 1;  // every writer writes the same
+    });
+}
+
+// (entering 5) each candidate's earlier conflicting candidates.  A candidate
+// blocked by the agents is rejected whatever else happens, so lists are built
+// for the unblocked ones and hold unblocked candidates only.  The decision
+// rounds read a list as a set, and one that overflows sends its candidate to
+// the exhaustive test, so the order of the entries does not matter.
+__global__ __launch_bounds__(kBlock) void k_spawn_pairs(int nc, float t_clear,
+                                                         const CandGrid *__restrict__ grid,
+                                                         const uint32_t *__restrict__ start,
+                                                         const float4 *__restrict__ sorted,
+                                                         const int32_t *__restrict__ index,
                                                          const uint8_t *__restrict__ blocked,
+                                                         int32_t *__restrict__ decision,
                                                          int32_t *__restrict__ conf_count,
                                                          int32_t *__restrict__ conf)
 {
-    __shared__ float4 tile[kBlock];
-    __shared__ uint8_t tile_blocked[kBlock];
-    const int last = min((int)(blockIdx.x + 1) * kBlock, nc);  // candidates before the block's end
-    const int b0 = (int)blockIdx.y * kPairChunk * kBlock;
-    if (b0 >= last) return;  // the whole workgroup: no earlier candidates in this chunk
-    const int b1 = min(b0 + kPairChunk * kBlock, last);
-    const int c = blockIdx.x * kBlock + threadIdx.x;
-    const bool live = c < nc && !blocked[c];
-    float cx = 0.0f, cy = 0.0f, cr = 0.0f, cs = 0.0f;
-    if (live) {
-        cx = cand.px[c];
-        cy = cand.py[c];
-        cr = cand.radius[c];
-        cs = cand.max_speed[c];
-    }
-    const double t = (double)t_clear;
-    for (int base = b0; base < b1; base += kBlock) {
-        const int e0 = base + threadIdx.x;
-        __syncthreads();
-        if (e0 < nc) {
-            tile[threadIdx.x] = make_float4(cand.px[e0], cand.py[e0], cand.radius[e0],
-                                            cand.max_speed[e0]);
-            tile_blocked[threadIdx.x] = blocked[e0];
-        }
-        __syncthreads();
-        if (!live) continue;
-        const int m = min(kBlock, c - base);  // earlier candidates only
-        for (int k = 0; k < m; ++k) {
-            if (tile_blocked[k]) continue;
-            const float4 e = tile[k];
-            if (too_close(cx, cy, cr, cs, e.x, e.y, e.z, e.w, t)) {
-                const int slot = atomicAdd(&conf_count[c], 1);
-                if (slot < kConfCap) conf[(int64_t)c * kConfCap + slot] = base + k;
+    const int s = blockIdx.x * kBlock + threadIdx.x;
+    if (s >= nc) return;
+    const int c = index[s];
+    const bool free = !blocked[s];
+    int found = 0;
+    if (free) {
+        const CandGrid g = *grid;
+        const float4 me = sorted[s];
+        near_candidates(g, start, me.x, me.y, [&](uint32_t t, uint32_t e) {
+            float4 o[kAhead];
+            int other[kAhead];
+            bool out[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const uint32_t p = min(t + u, e - 1u);
+                o[u] = sorted[p];
+                other[u] = index[p];
+                out[u] = blocked[p] != 0;
             }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (t + u >= e || other[u] >= c || out[u] ||
+                    !too_close(me.x, me.y, me.z, me.w, o[u].x, o[u].y, o[u].z, o[u].w,
+                               (double)t_clear))
+                    continue;
+                if (found < kConfCap) conf[(int64_t)c * kConfCap + found] = other[u];
+                ++found;
+            }
+        });
+    }
+    conf_count[c] = found;
+    decision[c] = !free ? kRejected : (found ? kUndecided : kAccepted);
+}
+
+// The decision of an undecided candidate from those of its conflicts, kUndecided
+// while an earlier one that is open could still enter.
+template <class Get>
+__device__ __forceinline__ int decide(int cnt, const int32_t *__restrict__ list, Get &&get)
+{
+    bool any_open = false;
+    for (int q = 0; q < cnt; ++q) {
+        const int d = get(list[q]);
+        if (d == kAccepted) return kRejected;
+        any_open = any_open || d == kUndecided;
+    }
+    return any_open ? kUndecided : kAccepted;
+}
+
+// (entering 6) a few rounds of first-come decisions by all candidates at once.  A
+// decision never changes once taken, so it does not matter which of the others'
+// a thread sees already; what stays open is left to (7), one workgroup, whose
+// rounds over all 16,384 candidates took 80 us.
+constexpr int kOpenRounds = 4;
+
+__global__ __launch_bounds__(kBlock) void k_spawn_decide(int nc, int32_t *__restrict__ decision,
+                                                          const int32_t *__restrict__ conf_count,
+                                                          const int32_t *__restrict__ conf)
+{
+    const int c = blockIdx.x * kBlock + threadIdx.x;
+    if (c >= nc || decision[c] != kUndecided) return;
+    const int cnt = conf_count[c];
+    if (cnt > kConfCap) return;
+    for (int round = 0; round < kOpenRounds; ++round) {
+        const int d = decide(cnt, conf + (int64_t)c * kConfCap, [&](int e) {
+            return __hip_atomic_load(&decision[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
+        if (d != kUndecided) {
+            __hip_atomic_store(&decision[c], d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
         }
     }
 }
 
-// (entering 4) one workgroup: first-come decisions in rounds, then the
-// accepted candidates are appended in order.
+// (entering 7) one workgroup: the decisions still open, in rounds, and the places
+// of the accepted candidates.
 __global__ __launch_bounds__(kScanThreads) void k_spawn_resolve(
-    orca_agents_in cand, int nc, float t_clear, const uint8_t *__restrict__ blocked,
-    const int32_t *__restrict__ conf_count, const int32_t *__restrict__ conf,
-    orca_agents_buf state, int n, int32_t *__restrict__ n_total, uint8_t *__restrict__ accepted)
+    orca_agents_in cand, int nc, float t_clear, int32_t *__restrict__ decision,
+    const int32_t *__restrict__ conf_count, const int32_t *__restrict__ conf, int n,
+    int32_t *__restrict__ n_total)
 {
     __shared__ uint8_t st[ORCA_SPAWN_MAX];
-    __shared__ uint32_t part[kScanThreads];
+    __shared__ uint16_t todo[ORCA_SPAWN_MAX];
+    __shared__ uint32_t n_todo;
+    static_assert(ORCA_SPAWN_MAX <= 65536, "candidates fit 16 bits");
     const int tid = threadIdx.x;
     const double t = (double)t_clear;
-    for (int c = tid; c < nc; c += kScanThreads) st[c] = blocked[c] ? kRejected : kUndecided;
+    if (tid == 0) n_todo = 0u;
+    __syncthreads();
+#pragma unroll 4
+    for (int c = tid; c < nc; c += kScanThreads) {
+        const int d = decision[c];
+        st[c] = (uint8_t)d;
+        if (d == kUndecided) todo[atomicAdd(&n_todo, 1u)] = (uint16_t)c;
+    }
     __syncthreads();
     // every round decides at least the first undecided candidate, so at most
-    // nc rounds; a decision never changes once taken
+    // nc rounds
+    const uint32_t open_at_first = n_todo;
     for (int round = 0; round <= nc; ++round) {
         int open = 0;
-        for (int c = tid; c < nc; c += kScanThreads) {
+        for (uint32_t w = tid; w < open_at_first; w += kScanThreads) {
+            const int c = todo[w];
             if (st[c] != kUndecided) continue;
-            bool any_acc = false, any_open = false;
             const int cnt = conf_count[c];
+            int d;
             if (cnt <= kConfCap) {
-                for (int k = 0; k < cnt; ++k) {
-                    const uint8_t s = st[conf[(int64_t)c * kConfCap + k]];
-                    any_acc = any_acc || s == kAccepted;
-                    any_open = any_open || s == kUndecided;
-                }
+                d = decide(cnt, conf + (int64_t)c * kConfCap, [&](int e) { return (int)st[e]; });
             } else {
                 // more conflicts than listed: test every earlier candidate
                 const float cx = cand.px[c], cy = cand.py[c], cr = cand.radius[c],
                             cs = cand.max_speed[c];
+                bool any_acc = false, any_open = false;
                 for (int e = 0; e < c; ++e) {
-                    const uint8_t s = st[e];
+                    const int s = st[e];
                     if (s == kRejected) continue;
                     if (too_close(cx, cy, cr, cs, cand.px[e], cand.py[e], cand.radius[e],
                                   cand.max_speed[e], t)) {
@@ -332,46 +503,45 @@ __global__ __launch_bounds__(kScanThreads) void k_spawn_resolve(
                         any_open = any_open || s == kUndecided;
                     }
                 }
+                d = any_acc ? kRejected : (any_open ? kUndecided : kAccepted);
             }
-            if (any_acc)
-                st[c] = kRejected;
-            else if (!any_open)
-                st[c] = kAccepted;
+            if (d != kUndecided)
+                st[c] = (uint8_t)d;
             else
                 open = 1;
         }
         if (!__syncthreads_or(open)) break;
     }
-    // ranks of the accepted candidates (exclusive scan over thread chunks)
+    // places of the accepted candidates (exclusive scan over thread chunks)
     const int per = (nc + kScanThreads - 1) / kScanThreads;
     const int a = tid * per, b = min(a + per, nc);
-    uint32_t s = 0;
+    uint32_t s = 0, tot;
     for (int c = a; c < b; ++c) s += st[c] == kAccepted ? 1u : 0u;
-    part[tid] = s;
-    __syncthreads();
-    for (int off = 1; off < kScanThreads; off <<= 1) {
-        const uint32_t v = tid >= off ? part[tid - off] : 0u;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    uint32_t rank = (uint32_t)n + (tid ? part[tid - 1] : 0u);
-    for (int c = a; c < b; ++c) {
-        const bool ok = st[c] == kAccepted;
-        if (accepted) accepted[c] = ok ? 1 : 0;
-        if (!ok) continue;
-        state.px[rank] = cand.px[c];
-        state.py[rank] = cand.py[c];
-        state.vx[rank] = cand.vx[c];
-        state.vy[rank] = cand.vy[c];
-        state.pref_x[rank] = cand.pref_x[c];
-        state.pref_y[rank] = cand.pref_y[c];
-        state.radius[rank] = cand.radius[c];
-        state.max_speed[rank] = cand.max_speed[c];
-        state.cls[rank] = cand.cls[c];
-        ++rank;
-    }
-    if (tid == kScanThreads - 1) *n_total = (int32_t)((uint32_t)n + part[tid]);
+    uint32_t rank = (uint32_t)n + block_excl_scan<kScanThreads>(s, &tot);
+    for (int c = a; c < b; ++c) decision[c] = st[c] == kAccepted ? (int32_t)rank++ : -1;
+    if (tid == 0) *n_total = (int32_t)((uint32_t)n + tot);
+}
+
+// (entering 8) the accepted candidates appended in order
+__global__ __launch_bounds__(kBlock) void k_spawn_append(orca_agents_in cand, int nc,
+                                                          const int32_t *__restrict__ place,
+                                                          orca_agents_buf state,
+                                                          uint8_t *__restrict__ accepted)
+{
+    const int c = blockIdx.x * kBlock + threadIdx.x;
+    if (c >= nc) return;
+    const int to = place[c];
+    if (accepted) accepted[c] = to >= 0 ? 1 : 0;
+    if (to < 0) return;
+    state.px[to] = cand.px[c];
+    state.py[to] = cand.py[c];
+    state.vx[to] = cand.vx[c];
+    state.vy[to] = cand.vy[c];
+    state.pref_x[to] = cand.pref_x[c];
+    state.pref_y[to] = cand.pref_y[c];
+    state.radius[to] = cand.radius[c];
+    state.max_speed[to] = cand.max_speed[c];
+    state.cls[to] = cand.cls[c];
 }
 
 // Overlap statistics, per block: pairs counted from both ends, agents in
@@ -467,13 +637,11 @@ __global__ __launch_bounds__(kBlock) void k_overlap_final(const OverlapPart *__r
 
 }  // namespace
 
-size_t lifecycle_extra_bytes(int64_t n, int64_t n_cand)
+size_t lifecycle_bytes(int64_t n, int64_t n_cand)
 {
-    const int64_t nb = (n + kBlock - 1) / kBlock;
-    return a256(sizeof(uint32_t) * (size_t)(nb + 1)) + a256(sizeof(float4) * kBoundBlocksMax) +
-           a256(sizeof(float) * 8) +
-           a256((size_t)n_cand) + a256(sizeof(int32_t) * (size_t)n_cand) +
-           a256(sizeof(int32_t) * (size_t)kConfCap * (size_t)n_cand);
+    size_t bytes;
+    bind_life(n, n_cand, nullptr, &bytes);
+    return bytes;
 }
 
 hipError_t launch_remove_arrived(const orca_agents_in &in, const orca_agents_buf &out, int n,
@@ -494,36 +662,36 @@ hipError_t launch_remove_arrived(const orca_agents_in &in, const orca_agents_buf
 }
 
 hipError_t launch_spawn(const orca_agents_buf &state, int n, const orca_agents_in &cand,
-                        int n_cand, float t_clear, int32_t *n_total, uint8_t *accepted,
-                        const Layout &L, const Work &w, void *extra, hipStream_t stream)
+                        int n_cand, float t_clear, int32_t *n_total, uint8_t *accepted, void *extra,
+                        hipStream_t stream)
 {
     const LifeBufs b = bind_life(n, n_cand, extra);
-    const orca_agents_in cur{state.px,     state.py,        state.vx,
-                             state.vy,     state.pref_x,    state.pref_y,
-                             state.radius, state.max_speed, state.cls};
     const int m = n > n_cand ? n : n_cand;
     int nbb = (m + kBlock - 1) / kBlock;
     nbb = nbb < 1 ? 1 : (nbb > kBoundBlocksMax ? kBoundBlocksMax : nbb);
-    hipLaunchKernelGGL(k_spawn_bounds, dim3(nbb), dim3(kBlock), 0, stream, state.radius,
-                       state.max_speed, n, cand.radius, cand.max_speed, n_cand, b.partial);
-    hipLaunchKernelGGL(k_spawn_dmax, dim3(1), dim3(kBlock), 0, stream, b.partial, nbb, t_clear,
-                       b.bounds);
-    if (n > 0) {
-        // the grid's neighbour distance (and cell size) is D_max from the device
-        const hipError_t e = launch_grid_build_rn(cur, n, 1.0f, 0.0f, b.bounds + 4, L, w, stream);
-        if (e != hipSuccess) return e;
-    }
     const int ncb = (n_cand + kBlock - 1) / kBlock;
     if (ncb > 0) {
-        hipLaunchKernelGGL(k_spawn_check, dim3(ncb), dim3(kBlock), 0, stream, cand, n_cand,
-                           (const float *)state.max_speed, w.meta, w.start, w.s0, w.s1, b.bounds,
-                           t_clear, n, b.blocked, b.conf_count);
-        const int chunks = (ncb + kPairChunk - 1) / kPairChunk;
-        hipLaunchKernelGGL(k_spawn_pairs, dim3(ncb, chunks), dim3(kBlock), 0, stream, cand,
-                           n_cand, t_clear, b.blocked, b.conf_count, b.conf);
+        hipLaunchKernelGGL(k_spawn_bounds, dim3(nbb), dim3(kBlock), 0, stream, state.radius,
+                           state.max_speed, n, cand, n_cand, b.partial, b.box);
+        hipLaunchKernelGGL(k_spawn_grid, dim3(1), dim3(kScanThreads), 0, stream, cand, n_cand,
+                           t_clear, b.partial, b.box, nbb, b.grid, b.start, b.decision);
+        hipLaunchKernelGGL(k_spawn_sort, dim3(ncb), dim3(kBlock), 0, stream, cand, n_cand, b.decision,
+                           b.cand, b.index, b.blocked);
+        if (n > 0)
+            hipLaunchKernelGGL(k_spawn_block, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
+                               stream, (const float *)state.px, (const float *)state.py,
+                               (const float *)state.radius, (const float *)state.max_speed, n,
+                               t_clear, b.grid, b.start, b.cand, b.blocked);
+        hipLaunchKernelGGL(k_spawn_pairs, dim3(ncb), dim3(kBlock), 0, stream, n_cand, t_clear, b.grid,
+                           b.start, b.cand, b.index, b.blocked, b.decision, b.conf_count, b.conf);
+        hipLaunchKernelGGL(k_spawn_decide, dim3(ncb), dim3(kBlock), 0, stream, n_cand, b.decision,
+                           b.conf_count, b.conf);
     }
     hipLaunchKernelGGL(k_spawn_resolve, dim3(1), dim3(kScanThreads), 0, stream, cand, n_cand,
-                       t_clear, b.blocked, b.conf_count, b.conf, state, n, n_total, accepted);
+                       t_clear, b.decision, b.conf_count, b.conf, n, n_total);
+    if (ncb > 0)
+        hipLaunchKernelGGL(k_spawn_append, dim3(ncb), dim3(kBlock), 0, stream, cand, n_cand,
+                           b.decision, state, accepted);
     return hipGetLastError();
 }
 

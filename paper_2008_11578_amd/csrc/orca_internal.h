@@ -106,6 +106,23 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
     return x * q + (x < r ? x : r) + b / kXcds;
 }
 
+// Rank of this lane's agent in cell c, counted into count[c]: neighbouring lanes
+// of one cell (a caller whose order follows the places) count together, by the
+// first of them.  Called by all lanes that have an agent, in index order.
+__device__ __forceinline__ uint32_t count_run(uint32_t c, uint32_t *__restrict__ count)
+{
+    const int lane = threadIdx.x % kWave;
+    const uint32_t before = (uint32_t)__shfl_up((int)c, 1, kWave);
+    const uint64_t heads = __ballot(lane == 0 || before != c);
+    const uint64_t live = __ballot(true);
+    const int head = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+    const uint64_t after = head < 63 ? (heads >> (head + 1)) << (head + 1) : 0ull;
+    const int end = after ? __ffsll((long long)after) - 1 : __popcll(live);
+    uint32_t base = 0;
+    if (lane == head) base = atomicAdd(&count[c], (uint32_t)(end - head));
+    return (uint32_t)__shfl((int)base, head, kWave) + (uint32_t)(lane - head);
+}
+
 __device__ __forceinline__ float wave_min(float v)
 {
 #pragma unroll
@@ -366,7 +383,7 @@ hipError_t launch_knn_export(const orca_agents_in &in, int n, const orca_params 
 hipError_t launch_fill_zero(void *ws, size_t bytes, hipStream_t stream);
 
 // Agent lifecycle (leaving at the goal, entering at clear spawn points).
-size_t lifecycle_extra_bytes(int64_t n, int64_t n_cand);
+size_t lifecycle_bytes(int64_t n, int64_t n_cand);
 hipError_t launch_remove_arrived(const orca_agents_in &in, const orca_agents_buf &out, int n,
                                  int32_t *n_alive, int32_t *old_to_new, void *extra,
                                  hipStream_t stream);
@@ -374,8 +391,8 @@ size_t overlap_extra_bytes(int64_t n);
 hipError_t launch_overlap_stats(const orca_agents_in &in, int n, float reach, double *out,
                                 const Layout &L, const Work &w, void *extra, hipStream_t stream);
 hipError_t launch_spawn(const orca_agents_buf &state, int n, const orca_agents_in &cand,
-                        int n_cand, float t_clear, int32_t *n_total, uint8_t *accepted,
-                        const Layout &L, const Work &w, void *extra, hipStream_t stream);
+                        int n_cand, float t_clear, int32_t *n_total, uint8_t *accepted, void *extra,
+                        hipStream_t stream);
 
 // Extra workspace of the adjoint: per-agent tau contributions and the edge
 // list (3 per agent) of contributions to neighbours with its transpose.

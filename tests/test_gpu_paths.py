@@ -164,3 +164,39 @@ def test_small_crowd_by_groups_of_lanes_equals_a_lane_per_agent(n, k, side, caps
     for other in got[1:]:
         for q, (a, b) in enumerate(zip(got[0], other)):
             assert torch.equal(a, b), q
+
+
+@pytest.mark.parametrize("n,nc,spread,agents,t_clear", [
+    (3, 1, 1.0, 5.0, 1.0), (4000, 700, 20000.0, 30000.0, 0.5), (4000, 1500, 3.0, 40.0, 0.0),
+    (2500, 1025, 60.0, 4000.0, 0.25), (500, 16384, 500.0, 100.0, 0.02), (300, 200, 0.0, 30.0, 0.5)])
+@pytest.mark.parametrize("odd", ["", "nan", "inf"])
+def test_spawn_grid_over_the_candidates(n, nc, spread, agents, t_clear, odd):
+    """The candidates' grid: boxes that would need more cells than it has, all
+    candidates in one cell or at one place, agents far outside the box, and
+    places that are not finite (no box: one cell holds everyone).  Decisions
+    equal the oracle's, taken one by one in order."""
+    import oracle
+    import torch
+    from paper_2008_11578_amd import orca
+    rng = np.random.default_rng(n + nc)
+
+    def crowd(m, side, shift):
+        f = {k: np.zeros(m, np.float32) for k in ("vx", "vy", "pref_x", "pref_y")}
+        f["px"] = (shift + rng.uniform(0, max(side, 1e-9), m)).astype(np.float32)
+        f["py"] = (shift + rng.uniform(0, max(side, 1e-9), m)).astype(np.float32)
+        f["radius"] = rng.uniform(0.2, 0.6, m).astype(np.float32)
+        f["max_speed"] = rng.uniform(0.5, 6.0, m).astype(np.float32)
+        return dict(f, cls=np.zeros(m, np.uint8))
+
+    a, c = crowd(n, agents, -agents / 3), crowd(nc, spread, 7.0)
+    if odd:
+        c["px"][nc // 2] = a["py"][n // 2] = np.float32(odd)
+    room = {k: np.concatenate([v, c[k]]) for k, v in a.items()}
+    acc = torch.empty(nc, dtype=torch.uint8, device="cuda")
+    tot = orca.spawn(orca.State.from_arrays(room), n, orca.State.from_arrays(c), t_clear,
+                     orca.LifecycleWorkspace(n, nc), accepted=acc)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        want = oracle.spawn(a, c, t_clear)
+    np.testing.assert_array_equal(acc.cpu().numpy(), want)
+    assert int(tot.item()) == n + int(want.sum())
