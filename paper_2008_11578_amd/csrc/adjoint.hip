@@ -19,11 +19,12 @@
 //                          (c = v, or v scaled onto the speed circle),
 //                   writing the agent's own cotangents and up to three
 //                   contributions to neighbours into an edge list;
-//   k_edge_*,       counting sort of the edges by target (count, tiled scan,
-//   k_escan_*       place), each target summing its edges in source order (no
+//                   the edge also goes to its target's list, by an atomic count;
+//   k_edge_gather   each target sums its edges in source order (no
 //                   floating-point atomics, so results are bit-reproducible);
-//   k_tau_*         the per-agent tau contributions summed in double in a
-//                   fixed order (block sums, then one block).
+//                   also the tau contributions of the block's agents, in double
+//                   and in a fixed order;
+//   k_tau_final     one block adds the block sums.
 // Neighbour sets and branches are held fixed (they are piecewise constant).
 #include "orca_group.h"
 
@@ -45,10 +46,7 @@ struct AdjArgs {
     dev::SceneP p;
     const float *gpx1, *gpy1, *gvx1, *gvy1;
     float *gpx0, *gpy0, *gvx0, *gvy0, *gprx, *gpry;
-    float *tau_part;
-    int32_t *e_tgt;
-    float4 *e_val;
-    uint32_t *e_cnt;
+    AdjointBufs b;
 };
 
 // Cotangents of the (at most three) lines (q, n) that define the LP result:
@@ -168,6 +166,20 @@ __device__ __forceinline__ void solve2(float g1x, float g1y, float g2x, float g2
     const float id = 1.0f / det;
     m1 = (wx * g2y - wy * g2x) * id;
     m2 = (g1x * wy - g1y * wx) * id;
+}
+
+// Edge e's contribution to agent j: into the first free slot of j's list, past
+// them onto its chain.  (Slots found by a count, a scan over all targets and a
+// pass that places every edge: four more launches, 42 of 519 us at 1M agents and
+// 16 of 80 us at 16,384.)
+__device__ __forceinline__ void add_edge(const AdjointBufs &b, uint32_t e, uint32_t j, float4 val)
+{
+    b.e_val[e] = val;
+    const uint32_t slot = atomicAdd(&b.e_cnt[j], 1u);
+    if (slot < (uint32_t)kEdgeSlots)
+        b.e_list[(int64_t)j * kEdgeSlots + slot] = e;
+    else
+        b.e_next[e] = atomicExch(&b.e_head[j], e + 1u);
 }
 
 // One agent's step as the adjoint needs it: what its forward recomputation
@@ -350,8 +362,6 @@ __device__ __forceinline__ void adjoint_vjp(const AdjArgs &a, const AdjAgent<BLO
     float spx = 0.0f, spy = 0.0f, svx = 0.0f, svy = 0.0f, taub = 0.0f;
 #pragma unroll
     for (int e = 0; e < kEdges; ++e) {
-        int32_t tgt = -1;
-        float4 val = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (ACC && lb.idx[e] >= 0 && lb.idx[e] < nacc) {
             // acceleration line: q = c + h n_k with a constant normal
             cbx += lb.qx[e];
@@ -386,11 +396,9 @@ __device__ __forceinline__ void adjoint_vjp(const AdjArgs &a, const AdjAgent<BLO
             svx += Vbx + lb.qx[e];
             svy += Vby + lb.qy[e];
             if (uses_tau) taub -= itb * p.inv_tau * p.inv_tau;
-            tgt = j;
-            val = make_float4(Pbx, Pby, -Vbx, -Vby);
+            add_edge(a.b, (uint32_t)(kEdges * i + e), (uint32_t)j,
+                     make_float4(Pbx, Pby, -Vbx, -Vby));
         }
-        a.e_tgt[(int64_t)kEdges * i + e] = tgt;
-        a.e_val[(int64_t)kEdges * i + e] = val;
     }
     if (ACC && nh > nacc) {
         // h = v / |v|: Jacobian (I - h h^T) / |v|
@@ -441,8 +449,7 @@ __device__ __forceinline__ void adjoint_vjp(const AdjArgs &a, const AdjAgent<BLO
     a.gpy0[i] = gpy + spy;
     a.gvx0[i] = svx;
     a.gvy0[i] = svy;
-    a.tau_part[i] = taub;
-    a.e_cnt[i] = 0u;
+    a.b.tau_part[i] = taub;
 }
 
 template <int K, int BLOCK, bool ACC>
@@ -557,136 +564,91 @@ __global__ __launch_bounds__(kWave) void k_adjoint_group(AdjArgs a, float rn)
     adjoint_vjp(a, f, [&](int q) { return lds.nbr[who][q]; });
 }
 
-// Edges by target: count and rank.
-__global__ __launch_bounds__(kBlock) void k_edge_count(const int32_t *__restrict__ e_tgt, int ne,
-                                                       int n, uint32_t *__restrict__ e_cnt,
-                                                       uint32_t *__restrict__ e_rank)
+// The smallest edge of target j above `last` (edge index + 1, 0 for none),
+// among all c of them.
+__device__ __forceinline__ uint32_t next_edge(const AdjointBufs &b, int j, uint32_t last)
 {
-    const int e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= ne) return;
-    const int t = e_tgt[e];
-    if (t >= 0 && t < n) e_rank[e] = atomicAdd(&e_cnt[t], 1u);
-}
-
-// Exclusive scan of the per-target counts in tiles of kScanTile: the sum of
-// each tile, then the scan inside each tile offset by its prefix, the sum of
-// the tile sums before it (added up by each block itself).
-constexpr int kPer = kScanTile / kBlock;
-
-__global__ __launch_bounds__(kBlock) void k_escan_reduce(const uint32_t *__restrict__ cnt, int n,
-                                                         uint32_t *__restrict__ tiles)
-{
-    const int base = blockIdx.x * kScanTile;
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int c = base + threadIdx.x * kPer + k;
-        if (c < n) s += cnt[c];
+    uint32_t best = ~0u;
+    for (int q = 0; q < kEdgeSlots; ++q) {
+        const uint32_t e = b.e_list[(int64_t)j * kEdgeSlots + q];
+        if (e >= last && e < best) best = e;
     }
-    uint32_t tot;
-    block_excl_scan<kBlock>(s, &tot);
-    if (threadIdx.x == 0) tiles[blockIdx.x] = tot;
+    for (uint32_t h = b.e_head[j]; h; h = b.e_next[h - 1u])
+        if (h - 1u >= last && h - 1u < best) best = h - 1u;
+    return best;
 }
 
-__global__ __launch_bounds__(kBlock) void k_escan_apply(const uint32_t *__restrict__ cnt, int n,
-                                                        const uint32_t *__restrict__ tiles,
-                                                        uint32_t *__restrict__ start)
-{
-    const int base = blockIdx.x * kScanTile;
-    uint32_t before = 0;
-    for (int t = threadIdx.x; t < (int)blockIdx.x; t += kBlock) before += tiles[t];
-    uint32_t prefix;
-    block_excl_scan<kBlock>(before, &prefix);
-    uint32_t v[kPer];
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int c = base + threadIdx.x * kPer + k;
-        v[k] = c < n ? cnt[c] : 0u;
-        s += v[k];
-    }
-    uint32_t tot;
-    uint32_t run = prefix + block_excl_scan<kBlock>(s, &tot);
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int c = base + threadIdx.x * kPer + k;
-        if (c < n) start[c] = run;
-        run += v[k];
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_edge_place(const int32_t *__restrict__ e_tgt, int ne,
-                                                       int n, const uint32_t *__restrict__ e_rank,
-                                                       const uint32_t *__restrict__ start,
-                                                       uint32_t *__restrict__ list)
-{
-    const int e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= ne) return;
-    const int t = e_tgt[e];
-    if (t >= 0 && t < n) list[start[t] + e_rank[e]] = (uint32_t)e;
-}
-
-// Each target sums its edges in increasing edge index (= source agent, slot).
-__global__ __launch_bounds__(kBlock) void k_edge_gather(int n, const uint32_t *__restrict__ e_cnt,
-                                                        const uint32_t *__restrict__ start,
-                                                        uint32_t *__restrict__ list,
-                                                        const float4 *__restrict__ e_val,
-                                                        float *gpx0, float *gpy0, float *gvx0,
-                                                        float *gvy0)
+// Each target sums its edges in increasing edge index (= source agent, slot):
+// those of its list ordered in registers, or picked one by one when there are
+// more.  TAU: the block's tau contributions too (a fixed order: lanes, then
+// wavefronts).
+template <bool TAU>
+__global__ __launch_bounds__(kBlock) void k_edge_gather(int n, AdjointBufs b, float *gpx0, float *gpy0,
+                                                        float *gvx0, float *gvy0)
 {
     const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j >= n) return;
-    const uint32_t a = start[j], c = e_cnt[j];
-    for (uint32_t p = 1; p < c; ++p) {
-        const uint32_t v = list[a + p];
-        int q = (int)p - 1;
-        while (q >= 0 && list[a + q] > v) {
-            list[a + q + 1] = list[a + q];
-            --q;
+    if (j < n) {
+        const uint32_t c = b.e_cnt[j];
+        float sx = 0.0f, sy = 0.0f, tx = 0.0f, ty = 0.0f;
+        auto add = [&](const float4 &v) {
+            sx += v.x;
+            sy += v.y;
+            tx += v.z;
+            ty += v.w;
+        };
+        if (c <= (uint32_t)kEdgeSlots) {
+            uint32_t e[kEdgeSlots];
+            static_assert(kEdgeSlots == 8, "two loads and a network of eight");
+            const uint4 *l = (const uint4 *)(b.e_list + (int64_t)j * kEdgeSlots);
+            const uint4 p = l[0], q = c > 4u ? l[1] : make_uint4(~0u, ~0u, ~0u, ~0u);
+            e[0] = c > 0u ? p.x : ~0u;
+            e[1] = c > 1u ? p.y : ~0u;
+            e[2] = c > 2u ? p.z : ~0u;
+            e[3] = c > 3u ? p.w : ~0u;
+            e[4] = c > 4u ? q.x : ~0u;
+            e[5] = c > 5u ? q.y : ~0u;
+            e[6] = c > 6u ? q.z : ~0u;
+            e[7] = c > 7u ? q.w : ~0u;
+            dev::sort_network<kEdgeSlots>(e);
+#pragma unroll
+            for (int k = 0; k < kEdgeSlots; ++k)
+                if ((uint32_t)k < c) add(b.e_val[e[k]]);
+        } else {
+            for (uint32_t k = 0, last = 0; k < c; ++k) {
+                const uint32_t e = next_edge(b, j, last);
+                add(b.e_val[e]);
+                last = e + 1u;
+            }
         }
-        list[a + q + 1] = v;
+        gpx0[j] += sx;
+        gpy0[j] += sy;
+        gvx0[j] += tx;
+        gvy0[j] += ty;
     }
-    float sx = 0.0f, sy = 0.0f, tx = 0.0f, ty = 0.0f;
-    for (uint32_t p = 0; p < c; ++p) {
-        const float4 v = e_val[list[a + p]];
-        sx += v.x;
-        sy += v.y;
-        tx += v.z;
-        ty += v.w;
+    if (TAU) {
+        __shared__ double red[kBlock / kWave];
+        double t = j < n ? (double)b.tau_part[j] : 0.0;
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, kWave);
+        if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = t;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kBlock / kWave; ++w) t += red[w];
+            b.tau_blocks[blockIdx.x] = t;
+        }
     }
-    gpx0[j] += sx;
-    gpy0[j] += sy;
-    gvx0[j] += tx;
-    gvy0[j] += ty;
 }
 
-// g_tau += sum of the per-agent contributions in double, in a fixed order:
-// kTauBlocks blocks each reduce a contiguous share (threads strided, then a
-// tree), and one block adds the block sums by a tree.
-__global__ __launch_bounds__(kBlock) void k_tau_partial(const float *__restrict__ part, int n,
-                                                        double *__restrict__ blocks)
+// g_tau += the sum of the block sums, in a fixed order.
+__global__ __launch_bounds__(kBlock) void k_tau_final(const double *__restrict__ blocks, int nb,
+                                                      float *g_tau)
 {
     __shared__ double red[kBlock];
-    const int per = (n + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int a = blockIdx.x * per, b = min(a + per, n);
     double s = 0.0;
-    for (int k = a + threadIdx.x; k < b; k += kBlock) s += (double)part[k];
+    for (int k = threadIdx.x; k < nb; k += kBlock) s += blocks[k];
     red[threadIdx.x] = s;
     __syncthreads();
     for (int off = kBlock / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) blocks[blockIdx.x] = red[0];
-}
-
-__global__ __launch_bounds__(kTauBlocks) void k_tau_final(const double *__restrict__ blocks,
-                                                          float *g_tau)
-{
-    __shared__ double red[kTauBlocks];
-    red[threadIdx.x] = blocks[threadIdx.x];
-    __syncthreads();
-    for (int off = kTauBlocks / 2; off > 0; off >>= 1) {
         if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
         __syncthreads();
     }
@@ -757,10 +719,7 @@ hipError_t launch_adjoint(const orca_agents_in &in, int n, const orca_params &pr
     a.gvy0 = gvy0;
     a.gprx = gprx;
     a.gpry = gpry;
-    a.tau_part = b.tau_part;
-    a.e_tgt = b.e_tgt;
-    a.e_val = b.e_val;
-    a.e_cnt = b.e_cnt;
+    a.b = b;
     const int k = prm.max_neighbors;
     if (ev && ev->step_begin && hipEventRecord(ev->step_begin, stream) != hipSuccess)
         return hipErrorInvalidValue;
@@ -784,23 +743,14 @@ hipError_t launch_adjoint(const orca_agents_in &in, int n, const orca_params &pr
         launch_adjoint_k<32>(a, stream);
     if (ev && ev->step_end && hipEventRecord(ev->step_end, stream) != hipSuccess)
         return hipErrorInvalidValue;
-    const int ne = kEdges * n;
-    const int nbe = (ne + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_edge_count, dim3(nbe), dim3(kBlock), 0, stream, b.e_tgt, ne, n, b.e_cnt,
-                       b.e_rank);
-    const int nt = (n + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_escan_reduce, dim3(nt), dim3(kBlock), 0, stream, b.e_cnt, n, b.e_tiles);
-    hipLaunchKernelGGL(k_escan_apply, dim3(nt), dim3(kBlock), 0, stream, b.e_cnt, n, b.e_tiles,
-                       b.e_start);
-    hipLaunchKernelGGL(k_edge_place, dim3(nbe), dim3(kBlock), 0, stream, b.e_tgt, ne, n, b.e_rank,
-                       b.e_start, b.e_list);
-    hipLaunchKernelGGL(k_edge_gather, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, stream, n,
-                       b.e_cnt, b.e_start, b.e_list, b.e_val, gpx0, gpy0, gvx0, gvy0);
+    const int nb = (n + kBlock - 1) / kBlock;
     if (g_tau) {
-        hipLaunchKernelGGL(k_tau_partial, dim3(kTauBlocks), dim3(kBlock), 0, stream, b.tau_part,
-                           n, b.tau_blocks);
-        hipLaunchKernelGGL(k_tau_final, dim3(1), dim3(kTauBlocks), 0, stream, b.tau_blocks,
-                           g_tau);
+        hipLaunchKernelGGL((k_edge_gather<true>), dim3(nb), dim3(kBlock), 0, stream, n, b, gpx0, gpy0,
+                           gvx0, gvy0);
+        hipLaunchKernelGGL(k_tau_final, dim3(1), dim3(kBlock), 0, stream, b.tau_blocks, nb, g_tau);
+    } else {
+        hipLaunchKernelGGL((k_edge_gather<false>), dim3(nb), dim3(kBlock), 0, stream, n, b, gpx0,
+                           gpy0, gvx0, gvy0);
     }
     return hipGetLastError();
 }

@@ -69,40 +69,40 @@ Work bind(const Layout &L, void *ws)
     return w;
 }
 
+namespace {
+AdjointBufs lay_adjoint(int64_t n, char *base, size_t *bytes)
+{
+    size_t o = 0;
+    auto take = [&](size_t len) {
+        char *p = base + o;
+        o += align_up(len);
+        return p;
+    };
+    const size_t m = (size_t)n;
+    AdjointBufs r;
+    r.tau_part = (float *)take(sizeof(float) * m);
+    r.e_val = (float4 *)take(sizeof(float4) * 3 * m);
+    r.e_list = (uint32_t *)take(sizeof(uint32_t) * kEdgeSlots * m);
+    r.e_next = (uint32_t *)take(sizeof(uint32_t) * 3 * m);
+    r.e_cnt = (uint32_t *)take(sizeof(uint32_t) * 2 * m);
+    r.e_head = r.e_cnt + m;
+    r.tau_blocks = (double *)take(sizeof(double) * (m / 256 + 1));
+    *bytes = o;
+    return r;
+}
+}  // namespace
+
 size_t adjoint_extra_bytes(int64_t n)
 {
-    const size_t a = align_up(sizeof(float) * (size_t)n) + align_up(sizeof(int32_t) * 3 * (size_t)n) +
-                     align_up(sizeof(float4) * 3 * (size_t)n) +
-                     2 * align_up(sizeof(uint32_t) * 3 * (size_t)n) +
-                     2 * align_up(sizeof(uint32_t) * (size_t)n) +
-                     align_up(sizeof(uint32_t) * (size_t)((n + kScanTile - 1) / kScanTile + 1)) +
-                     align_up(sizeof(double) * kTauBlocks);
-    return a;
+    size_t bytes;
+    lay_adjoint(n, nullptr, &bytes);
+    return bytes;
 }
 
 AdjointBufs bind_adjoint(int64_t n, void *base)
 {
-    char *b = (char *)base;
-    AdjointBufs r;
-    size_t o = 0;
-    r.tau_part = (float *)(b + o);
-    o += align_up(sizeof(float) * (size_t)n);
-    r.e_tgt = (int32_t *)(b + o);
-    o += align_up(sizeof(int32_t) * 3 * (size_t)n);
-    r.e_val = (float4 *)(b + o);
-    o += align_up(sizeof(float4) * 3 * (size_t)n);
-    r.e_rank = (uint32_t *)(b + o);
-    o += align_up(sizeof(uint32_t) * 3 * (size_t)n);
-    r.e_list = (uint32_t *)(b + o);
-    o += align_up(sizeof(uint32_t) * 3 * (size_t)n);
-    r.e_cnt = (uint32_t *)(b + o);
-    o += align_up(sizeof(uint32_t) * (size_t)n);
-    r.e_start = (uint32_t *)(b + o);
-    o += align_up(sizeof(uint32_t) * (size_t)n);
-    r.e_tiles = (uint32_t *)(b + o);
-    o += align_up(sizeof(uint32_t) * (size_t)((n + kScanTile - 1) / kScanTile + 1));
-    r.tau_blocks = (double *)(b + o);
-    return r;
+    size_t bytes;
+    return lay_adjoint(n, (char *)base, &bytes);
 }
 
 namespace {
@@ -411,8 +411,10 @@ int orca_step_backward_ex(const orca_agents_in *in, int32_t n, const orca_params
     const AdjointBufs b = bind_adjoint(n, (char *)ws + L.total);
     if (events && events->grid_begin && hipEventRecord(events->grid_begin, stream) != hipSuccess)
         return ORCA_EHIP;
-    if ((n <= kWholeMax ? launch_pack(*in, n, w, stream)
-                        : launch_grid_build(*in, n, *params, L, w, stream)) != hipSuccess)
+    // the per-target edge counts and chains start empty
+    if ((n <= kWholeMax ? launch_pack(*in, n, w, stream, b.e_cnt, 2 * (int64_t)n)
+                        : launch_grid_build(*in, n, *params, L, w, stream, b.e_cnt,
+                                            2 * (int64_t)n)) != hipSuccess)
         return ORCA_EHIP;
     if (launch_adjoint(*in, n, *params, L, w, b, g1->px, g1->py, g1->vx, g1->vy, g0->px, g0->py,
                        g0->vx, g0->vy, g0->pref_x, g0->pref_y, g0->tau, events,

@@ -16,12 +16,15 @@ constexpr int kBlock = 256;
 // grid geometry inside (3) (see k_cell_count).
 constexpr int kFusedParts = 128;
 
-// (1) partial bounding boxes; also clears the cell histogram for (3).
+// (1) partial bounding boxes; also clears the cell histogram for (3), and what
+// else the caller wants cleared.
 __global__ __launch_bounds__(kBlock) void k_bbox_partial(const float *__restrict__ px,
                                                          const float *__restrict__ py, int n,
                                                          float4 *__restrict__ partial,
                                                          uint32_t *__restrict__ count,
-                                                         int count_len)
+                                                         int count_len,
+                                                         uint32_t *__restrict__ clear,
+                                                         int64_t clear_len)
 {
     float4 b = make_float4(INFINITY, INFINITY, -INFINITY, -INFINITY);
     const int stride = gridDim.x * kBlock;
@@ -33,6 +36,8 @@ __global__ __launch_bounds__(kBlock) void k_bbox_partial(const float *__restrict
         b.w = fmaxf(b.w, y);
     }
     for (int c = blockIdx.x * kBlock + threadIdx.x; c < count_len; c += stride) count[c] = 0u;
+    for (int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x; c < clear_len; c += stride)
+        clear[c] = 0u;
     b = block_bbox<kBlock>(b);
     if (threadIdx.x == 0) partial[blockIdx.x] = b;
 }
@@ -41,10 +46,8 @@ __global__ __launch_bounds__(kBlock) void k_bbox_partial(const float *__restrict
 __global__ __launch_bounds__(kBlock) void k_grid_setup(const float4 *__restrict__ partial,
                                                        int n_partial, float rn, float cs_req,
                                                        int max_cells, int n,
-                                                       const float *__restrict__ rn_dev,
                                                        GridMeta *__restrict__ meta)
 {
-    if (rn_dev) rn = *rn_dev;
     float4 b = make_float4(INFINITY, INFINITY, -INFINITY, -INFINITY);
     for (int k = threadIdx.x; k < n_partial; k += kBlock) {
         const float4 q = partial[k];
@@ -76,7 +79,6 @@ __global__ __launch_bounds__(kBlock) void k_cell_count(const float *__restrict__
                                                        const float4 *__restrict__ partial,
                                                        int n_partial, float rn, float cs_req,
                                                        int max_cells,
-                                                       const float *__restrict__ rn_dev,
                                                        GridMeta *__restrict__ meta,
                                                        uint32_t *__restrict__ cell,
                                                        uint32_t *__restrict__ rank,
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_count(const float *__restrict__
         b = block_bbox<kBlock>(b);
         if (threadIdx.x == 0) {
             GridMeta h;
-            grid_geometry(b, rn_dev ? *rn_dev : rn, cs_req, max_cells, h);
+            grid_geometry(b, rn, cs_req, max_cells, h);
             h.cell_base = 0;
             h.agent_base = 0;
             h.n = n;
@@ -199,26 +201,27 @@ __global__ void k_fill_zero(uint4 *p, size_t n16)
 }  // namespace
 
 hipError_t launch_grid_build(const orca_agents_in &in, int n, const orca_params &p,
-                             const Layout &L, const Work &w, hipStream_t stream)
+                             const Layout &L, const Work &w, hipStream_t stream, uint32_t *clear,
+                             int64_t clear_len)
 {
-    return launch_grid_build_rn(in, n, p.neighbor_dist, p.cell_size, nullptr, L, w, stream);
+    return launch_grid_build_rn(in, n, p.neighbor_dist, p.cell_size, L, w, stream, clear, clear_len);
 }
 
 hipError_t launch_grid_build_rn(const orca_agents_in &in, int n, float rn, float cell_size,
-                                const float *rn_dev, const Layout &L, const Work &w,
-                                hipStream_t stream)
+                                const Layout &L, const Work &w, hipStream_t stream, uint32_t *clear,
+                                int64_t clear_len)
 {
     const int nb = (int)((n + kBlock - 1) / kBlock);
     const int nbb = nb < kBboxBlocks ? nb : kBboxBlocks;
     const int count_len = (int)L.max_cells;
     hipLaunchKernelGGL(k_bbox_partial, dim3(nbb), dim3(kBlock), 0, stream, in.px, in.py, n,
-                       w.partial, w.count, count_len);
+                       w.partial, w.count, count_len, clear, clear_len);
     const bool fused = nbb <= kFusedParts;
     if (!fused)
         hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kBlock), 0, stream, w.partial, nbb, rn,
-                           cell_size, count_len, n, rn_dev, w.meta);
+                           cell_size, count_len, n, w.meta);
     hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, stream, in.px, in.py, n,
-                       fused ? w.partial : nullptr, nbb, rn, cell_size, count_len, rn_dev, w.meta,
+                       fused ? w.partial : nullptr, nbb, rn, cell_size, count_len, w.meta,
                        w.cell, w.rank, w.count);
     return launch_scan_scatter(in, n, L, w, w.meta, stream);
 }

@@ -23,10 +23,12 @@ struct GroupArgs {
 
 // The cell-ordered copies in caller order, for a scan of the whole crowd.
 __global__ __launch_bounds__(kBlock) void k_pack(orca_agents_in in, int n, float2 *__restrict__ s0,
-                                                 float4 *__restrict__ s1)
+                                                 float4 *__restrict__ s1,
+                                                 uint32_t *__restrict__ clear, int64_t clear_len)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i < n) write_record(in, i, (uint32_t)i, s0, s1);
+    for (int64_t c = i; c < clear_len; c += (int64_t)gridDim.x * kBlock) clear[c] = 0u;
 }
 
 template <int K, int G, bool ACC, bool WHOLE, bool EXPORT>
@@ -105,10 +107,11 @@ void launch_group_k(const GroupArgs &a, const dev::SceneP &p, hipStream_t stream
 
 }  // namespace
 
-hipError_t launch_pack(const orca_agents_in &in, int n, const Work &w, hipStream_t stream)
+hipError_t launch_pack(const orca_agents_in &in, int n, const Work &w, hipStream_t stream,
+                       uint32_t *clear, int64_t clear_len)
 {
     hipLaunchKernelGGL(k_pack, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, stream, in, n, w.s0,
-                       w.s1);
+                       w.s1, clear, clear_len);
     return hipGetLastError();
 }
 

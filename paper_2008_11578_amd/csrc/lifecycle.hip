@@ -710,7 +710,7 @@ hipError_t launch_overlap_stats(const orca_agents_in &in, int n, float reach, do
     OverlapPart *part = (OverlapPart *)extra;
     const int nb = (n + kBlock - 1) / kBlock;
     if (n > 0) {
-        const hipError_t e = launch_grid_build_rn(in, n, reach, 0.0f, nullptr, L, w, stream);
+        const hipError_t e = launch_grid_build_rn(in, n, reach, 0.0f, L, w, stream);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_overlap, dim3(nb), dim3(kBlock), 0, stream, w.meta, w.start, w.s0,
                            w.s1, n, part);

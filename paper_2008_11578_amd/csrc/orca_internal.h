@@ -262,14 +262,15 @@ Work bind(const Layout &L, void *ws);
 
 // Grid build for one scene: bounding box, cell keys, counting sort, SoA
 // gather into cell order.  Returns hipSuccess or the launch error.
+// `clear` (nullable): clear_len words to be set to zero on the way.
 hipError_t launch_grid_build(const orca_agents_in &in, int n, const orca_params &p,
-                             const Layout &L, const Work &w, hipStream_t stream);
+                             const Layout &L, const Work &w, hipStream_t stream,
+                             uint32_t *clear = nullptr, int64_t clear_len = 0);
 
-// The same with the neighbour distance read from device memory when rn_dev
-// is not null (a query radius computed on the device).
+// The same for a neighbour distance and a cell size.
 hipError_t launch_grid_build_rn(const orca_agents_in &in, int n, float rn, float cell_size,
-                                const float *rn_dev, const Layout &L, const Work &w,
-                                hipStream_t stream);
+                                const Layout &L, const Work &w, hipStream_t stream,
+                                uint32_t *clear = nullptr, int64_t clear_len = 0);
 
 // Histogram scan and scatter into cell order; scan_meta supplies the number
 // of cells (n_cells) and of agents (n) of the whole cell space.
@@ -365,7 +366,8 @@ __device__ __forceinline__ GridMeta whole_crowd(int n, float rn)
     g.seg_end = (uint32_t)n;
     return g;
 }
-hipError_t launch_pack(const orca_agents_in &in, int n, const Work &w, hipStream_t stream);
+hipError_t launch_pack(const orca_agents_in &in, int n, const Work &w, hipStream_t stream,
+                       uint32_t *clear = nullptr, int64_t clear_len = 0);
 hipError_t launch_step_group(const orca_agents_in &in, const orca_agents_out &out, int n,
                              const orca_params &prm, const Work &w, bool whole, int32_t *nbr,
                              int32_t *cnt, hipStream_t stream);
@@ -395,20 +397,17 @@ hipError_t launch_spawn(const orca_agents_buf &state, int n, const orca_agents_i
                         hipStream_t stream);
 
 // Extra workspace of the adjoint: per-agent tau contributions and the edge
-// list (3 per agent) of contributions to neighbours with its transpose.
+// list (3 per agent) of contributions to neighbours, found again by target.
+constexpr int kEdgeSlots = 8;  // edges of a target found directly
 struct AdjointBufs {
     float *tau_part;     // n
-    int32_t *e_tgt;      // 3n: target agent or -1
-    float4 *e_val;       // 3n: (gp.x, gp.y, gv.x, gv.y) for the target
-    uint32_t *e_rank;    // 3n
-    uint32_t *e_list;    // 3n
-    uint32_t *e_cnt;     // n
-    uint32_t *e_start;   // n
-    uint32_t *e_tiles;   // ceil(n / kScanTile) tile sums of the count scan
-    double *tau_blocks;  // kTauBlocks partial sums of the tau contributions
+    float4 *e_val;       // 3n: (gp.x, gp.y, gv.x, gv.y) for the edge's target
+    uint32_t *e_list;    // kEdgeSlots n: each target's first edges
+    uint32_t *e_next;    // 3n: edge before this one (+ 1) in its target's chain
+    uint32_t *e_cnt;     // n: edges of each target } cleared by the
+    uint32_t *e_head;    // n: end of its chain + 1 } kernels before the adjoint
+    double *tau_blocks;  // partial sums of the tau contributions
 };
-
-constexpr int kTauBlocks = 256;
 
 size_t adjoint_extra_bytes(int64_t n);
 AdjointBufs bind_adjoint(int64_t n, void *base);

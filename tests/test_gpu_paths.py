@@ -200,3 +200,58 @@ def test_spawn_grid_over_the_candidates(n, nc, spread, agents, t_clear, odd):
         want = oracle.spawn(a, c, t_clear)
     np.testing.assert_array_equal(acc.cpu().numpy(), want)
     assert int(tot.item()) == n + int(want.sum())
+
+
+def _hub(m, n):
+    """A disc and a ring of m agents walking into it, and agents far away."""
+    ang = 2.0 * np.pi * (np.arange(m) + 0.25) / m
+    far = 0.5 * m / np.pi + 4.0
+    f = {k: np.zeros(n, np.float32) for k in ("px", "py", "vx", "vy", "pref_x", "pref_y", "radius",
+                                              "max_speed")}
+    f["px"][1:m + 1], f["py"][1:m + 1] = far * np.cos(ang), far * np.sin(ang)
+    f["px"][m + 1:] = 1000.0 + 40.0 * (np.arange(n - m - 1) % 250)
+    f["py"][m + 1:] = 1000.0 + 40.0 * (np.arange(n - m - 1) // 250)
+    for k, wave in (("vx", np.cos), ("pref_x", np.cos), ("vy", np.sin), ("pref_y", np.sin)):
+        f[k][1:m + 1] = -1.2 * wave(ang + 0.05)
+    f["radius"][:] = 0.3
+    f["radius"][0] = far - 2.0
+    f["max_speed"][:] = 1.5
+    return dict(f, cls=np.zeros(n, np.uint8))
+
+
+@pytest.mark.parametrize("m", [6, 8, 9, 40])
+@pytest.mark.parametrize("filler", [0, 60000])
+def test_adjoint_sums_every_contribution_to_an_agent(m, filler):
+    """Every agent around a hub avoids it, so the hub receives about m
+    contributions: as many as its list holds, one more, and many more.  The VJP
+    is linear in the cotangents, so the hub's answer to all of them together is
+    the sum of its answers to a third of the agents at a time, and those to one
+    agent at a time (three contributions at most), but for the rounding of m
+    FP32 additions; and call after call gives the same bits.  With 60,000
+    agents far away the call takes a lane per agent."""
+    import torch
+    from paper_2008_11578_amd import orca
+    n = m + 1 + filler
+    p = scenarios.Params(dt=0.1, neighbor_dist=120.0, max_neighbors=min(m, 32), pref_is_goal=0)
+    st = orca.State.from_arrays(_hub(m, n))
+    ws = orca.Workspace(n, backward=True)
+    gen = torch.Generator().manual_seed(m)
+    cot = [torch.zeros(n) for _ in range(4)]
+    for c in cot:
+        c[1:m + 1] = torch.randn(m, generator=gen)
+
+    def hub(mask):
+        g = [(c * mask).cuda() for c in cot]
+        acc = [torch.zeros(n, device="cuda") for _ in range(2)] + [torch.zeros(1, device="cuda")]
+        out = orca.step_backward(st, p, ws, *g, *acc)
+        return torch.stack([t[0] for t in (*out, acc[2])]).double().cpu().numpy()
+
+    whole = hub(torch.ones(n))
+    np.testing.assert_array_equal(whole, hub(torch.ones(n)))
+    assert np.abs(whole).sum() > 1e-3
+    ones = [hub((torch.arange(n) == i).float()) for i in range(1, m + 1)]
+    thirds = [hub((torch.arange(n) % 3 == r).float()) for r in range(3)]
+    for parts in (ones, thirds):
+        size = np.sum(np.abs(ones), axis=0)
+        assert (np.abs(whole - np.sum(parts, axis=0)) <= 4 * m * 2.0 ** -24 * size + 1e-30).all()
+    assert sum(np.abs(o[:4]).sum() > 0 for o in ones) > min(m, 32) * 0.6  # the hub is in most ways
