@@ -191,6 +191,54 @@ __global__ __launch_bounds__(kBlock) void k_scatter(orca_agents_in in, int n,
     write_record(in, i, pos, s0, s1);
 }
 
+// (4 + 5) for a small crowd: every block scans the whole histogram (at most
+// kSmallCells cells) into LDS and scatters its agents; block 0 stores the starts
+// for the kernels after this one.  Two launches fewer: a crowd of this size
+// spends its time on launches.  (16,384 agents: grid 19 -> 13 us.)
+constexpr int kSmallCells = 8192;
+
+__global__ __launch_bounds__(kBlock) void k_scan_scatter(orca_agents_in in, int n,
+                                                         const uint32_t *__restrict__ cell,
+                                                         const uint32_t *__restrict__ rank,
+                                                         const uint32_t *__restrict__ count,
+                                                         const GridMeta *__restrict__ meta,
+                                                         uint32_t *__restrict__ start,
+                                                         float2 *__restrict__ s0,
+                                                         float4 *__restrict__ s1)
+{
+    __shared__ uint32_t first[kSmallCells];
+    const int n_cells = min(meta->n_cells, kSmallCells);
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    const uint32_t mine = i < n ? cell[i] : 0u, r = i < n ? rank[i] : 0u;
+    uint32_t before = 0;
+    for (int base = 0; base < n_cells; base += kScanTile) {
+        uint32_t v[kPer], s = 0, tot;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int c = base + threadIdx.x * kPer + k;
+            v[k] = c < n_cells ? count[c] : 0u;
+            s += v[k];
+        }
+        uint32_t run = before + block_excl_scan<kBlock>(s, &tot);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int c = base + threadIdx.x * kPer + k;
+            if (c < n_cells) {
+                first[c] = run;
+                if (blockIdx.x == 0) start[c] = run;
+            }
+            run += v[k];
+        }
+        before += tot;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) start[n_cells] = (uint32_t)n;
+    __syncthreads();
+    if (i >= n) return;
+    const uint32_t pos = first[min(mine, (uint32_t)n_cells - 1u)] + r;
+    if (pos >= (uint32_t)n) return;  // cannot happen for a consistent histogram
+    write_record(in, i, pos, s0, s1);
+}
+
 __global__ void k_fill_zero(uint4 *p, size_t n16)
 {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -200,29 +248,49 @@ __global__ void k_fill_zero(uint4 *p, size_t n16)
 
 }  // namespace
 
+namespace {
+
+// (1) to (3), with at most max_cells cells.
+void launch_count(const orca_agents_in &in, int n, float rn, float cell_size, int max_cells,
+                  const Work &w, hipStream_t stream, uint32_t *clear, int64_t clear_len)
+{
+    const int nb = (int)((n + kBlock - 1) / kBlock);
+    const int nbb = nb < kBboxBlocks ? nb : kBboxBlocks;
+    hipLaunchKernelGGL(k_bbox_partial, dim3(nbb), dim3(kBlock), 0, stream, in.px, in.py, n,
+                       w.partial, w.count, max_cells, clear, clear_len);
+    const bool fused = nbb <= kFusedParts;
+    if (!fused)
+        hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kBlock), 0, stream, w.partial, nbb, rn,
+                           cell_size, max_cells, n, w.meta);
+    hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, stream, in.px, in.py, n,
+                       fused ? w.partial : nullptr, nbb, rn, cell_size, max_cells, w.meta, w.cell,
+                       w.rank, w.count);
+}
+}  // namespace
+
 hipError_t launch_grid_build(const orca_agents_in &in, int n, const orca_params &p,
                              const Layout &L, const Work &w, hipStream_t stream, uint32_t *clear,
                              int64_t clear_len)
 {
-    return launch_grid_build_rn(in, n, p.neighbor_dist, p.cell_size, L, w, stream, clear, clear_len);
+    const int nb = (int)((n + kBlock - 1) / kBlock);
+    if (nb > kFusedParts)
+        return launch_grid_build_rn(in, n, p.neighbor_dist, p.cell_size, L, w, stream, clear,
+                                    clear_len);
+    // a crowd this small is stepped by groups of lanes, which take a row's
+    // candidates 16 at a time: cells finer than kSmallCells give would not help
+    // (the cells change no result)
+    const int max_cells = L.max_cells < kSmallCells ? (int)L.max_cells : kSmallCells;
+    launch_count(in, n, p.neighbor_dist, p.cell_size, max_cells, w, stream, clear, clear_len);
+    hipLaunchKernelGGL(k_scan_scatter, dim3(nb), dim3(kBlock), 0, stream, in, n, w.cell, w.rank,
+                       w.count, w.meta, w.start, w.s0, w.s1);
+    return hipGetLastError();
 }
 
 hipError_t launch_grid_build_rn(const orca_agents_in &in, int n, float rn, float cell_size,
                                 const Layout &L, const Work &w, hipStream_t stream, uint32_t *clear,
                                 int64_t clear_len)
 {
-    const int nb = (int)((n + kBlock - 1) / kBlock);
-    const int nbb = nb < kBboxBlocks ? nb : kBboxBlocks;
-    const int count_len = (int)L.max_cells;
-    hipLaunchKernelGGL(k_bbox_partial, dim3(nbb), dim3(kBlock), 0, stream, in.px, in.py, n,
-                       w.partial, w.count, count_len, clear, clear_len);
-    const bool fused = nbb <= kFusedParts;
-    if (!fused)
-        hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kBlock), 0, stream, w.partial, nbb, rn,
-                           cell_size, count_len, n, w.meta);
-    hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, stream, in.px, in.py, n,
-                       fused ? w.partial : nullptr, nbb, rn, cell_size, count_len, w.meta,
-                       w.cell, w.rank, w.count);
+    launch_count(in, n, rn, cell_size, (int)L.max_cells, w, stream, clear, clear_len);
     return launch_scan_scatter(in, n, L, w, w.meta, stream);
 }
 

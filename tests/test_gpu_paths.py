@@ -255,3 +255,25 @@ def test_adjoint_sums_every_contribution_to_an_agent(m, filler):
         size = np.sum(np.abs(ones), axis=0)
         assert (np.abs(whole - np.sum(parts, axis=0)) <= 4 * m * 2.0 ** -24 * size + 1e-30).all()
     assert sum(np.abs(o[:4]).sum() > 0 for o in ones) > min(m, 32) * 0.6  # the hub is in most ways
+
+
+@pytest.mark.parametrize("n", [2049, 32768, 32769])
+@pytest.mark.parametrize("cell", [0.0, 0.07, 300.0])
+def test_small_crowd_grid_lists_match_oracle(n, cell):
+    """Crowds of up to 32,768 agents bound their grid at 8,192 cells and scan
+    and scatter in one kernel: neighbour lists equal the oracle's on both
+    sides of the line, with cells that would be far more, the default, and one
+    cell for all; also of a crowd on a line (cells along one axis only)."""
+    import oracle
+    from parity import gpu_neighbors
+    p = scenarios.Params(neighbor_dist=3.0, max_neighbors=10, cell_size=cell)
+    sc = scenarios.random_state(n, np.sqrt(n / (0.5 if cell < 200 else 40.0)), seed=n, params=p)
+    lists = [sc]
+    if cell < 200:
+        line = sc.copy()
+        line.px, line.py = (line.px * 300.0).astype(np.float32), (line.py * 0.0).astype(np.float32)
+        lists.append(line)
+    for s in lists:
+        nbr, cnt = gpu_neighbors(s, p)
+        ref = oracle.step(s, p, want_neighbors=True)
+        np.testing.assert_array_equal(nbr, ref["nbr"])
