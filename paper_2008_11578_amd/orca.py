@@ -153,48 +153,46 @@ def version() -> str:
 
 
 def make_params(p) -> OrcaParams:
-    """From a ``scenarios.Params`` or a dict with the same field names."""
-    g = p.get if isinstance(p, dict) else (lambda k: getattr(p, k))
-    out = OrcaParams()
-    out.dt = g("dt")
-    out.time_horizon = g("time_horizon")
-    out.neighbor_dist = g("neighbor_dist")
-    out.cell_size = g("cell_size") if (not isinstance(p, dict) or "cell_size" in p) else 0.0
-    out.max_neighbors = int(g("max_neighbors"))
-    out.pref_is_goal = int(g("pref_is_goal"))
-    f = g("f")
-    for a in range(2):
-        for b in range(2):
-            out.f[a][b] = float(f[a][b])
+    """From a ``scenarios.Params``, a dict with the same field names, or an
+    ``OrcaParams`` (taken as it is: a loop of many calls makes it once)."""
+    if isinstance(p, OrcaParams):
+        return p
+    if isinstance(p, dict):
+        g = p.get
+        cell = p.get("cell_size", 0.0)
+        acc, turn = p.get("accel"), p.get("turn")
+    else:
+        g = p.__getattribute__
+        cell = p.cell_size
+        acc, turn = getattr(p, "accel", None), getattr(p, "turn", None)
+    out = OrcaParams(g("dt"), g("time_horizon"), g("neighbor_dist"), cell, int(g("max_neighbors")),
+                     int(g("pref_is_goal")))
     out.par_eps = g("par_eps")
-    try:
-        acc = g("accel")
-    except (AttributeError, KeyError):
-        acc = None
-    acc = (0.0, 0.0) if acc is None else acc
-    for c in range(2):
-        out.accel[c] = float(acc[c])
-    try:
-        turn = g("turn")
-    except (AttributeError, KeyError):
-        turn = None
-    turn = (0.0, 0.0) if turn is None else turn
-    for c in range(2):
-        out.turn[c] = float(turn[c])
+    # element by element: ctypes builds an array from a tuple far more slowly
+    for row, given in zip(out.f, g("f")):
+        row[0], row[1] = float(given[0]), float(given[1])
+    if acc is not None:
+        a = out.accel
+        a[0], a[1] = float(acc[0]), float(acc[1])
+    if turn is not None:
+        t = out.turn
+        t[0], t[1] = float(turn[0]), float(turn[1])
     return out
 
 
 def _stream_handle(stream=None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is None:
+        # the current stream's handle without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return int(stream.cuda_stream)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check(t: torch.Tensor, name: str, dtype, n: int):
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if t.dtype != dtype or not t.is_contiguous() or t.numel() != n:
         raise TypeError(f"{name} must be contiguous {dtype} with {n} elements")
@@ -235,9 +233,12 @@ class State:
 
     def agents_in(self) -> AgentsIn:
         n = self.n
+        ptrs = []
         for k in STATE_FIELDS:
-            _check(getattr(self, k), k, torch.uint8 if k == "cls" else torch.float32, n)
-        return AgentsIn(*[_ptr(getattr(self, k)) for k in STATE_FIELDS])
+            t = getattr(self, k)
+            _check(t, k, torch.uint8 if k == "cls" else torch.float32, n)
+            ptrs.append(t.data_ptr())
+        return AgentsIn(*ptrs)
 
 
 def workspace_bytes(n: int, n_scenes: int = 0, max_cells: int = 0) -> int:

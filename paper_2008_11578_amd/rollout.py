@@ -18,6 +18,20 @@ import torch
 from . import orca
 
 
+MOVING = ("px", "py", "vx", "vy")
+
+
+def _at(base: orca.State, rows: torch.Tensor) -> orca.State:
+    """`base` with the positions and velocities in the four rows of `rows`
+    (views; everything else is shared)."""
+    return dataclasses.replace(base, **dict(zip(MOVING, rows)))
+
+
+def _rows(st: orca.State) -> torch.Tensor:
+    """A copy of the positions and velocities, one row each."""
+    return torch.stack([getattr(st, k) for k in MOVING])
+
+
 class Rollout(torch.autograd.Function):
     @staticmethod
     def forward(ctx, v_pref_x, v_pref_y, tau, state0: orca.State, params, steps: int, ckpt: int):
@@ -28,24 +42,29 @@ class Rollout(torch.autograd.Function):
         p = dataclasses.replace(params, time_horizon=float(tau.detach().reshape(()).item()),
                                 pref_is_goal=0)
         ctx.tau_device = tau.device
-        n = state0.n
-        st = state0.clone()
-        st.pref_x = v_pref_x.detach().contiguous().clone()
-        st.pref_y = v_pref_y.detach().contiguous().clone()
-        nxt = st.clone()
-        ws = orca.Workspace(n)
+        # only positions and velocities change from step to step: they live in
+        # one tensor of four rows per state, everything else is shared
+        base = dataclasses.replace(state0.clone(), pref_x=v_pref_x.detach().contiguous().clone(),
+                                   pref_y=v_pref_y.detach().contiguous().clone())
+        prm = orca.make_params(p)
+        rows = _rows(base)
+        here, there = (rows, _at(base, rows)), None
+        other = torch.empty_like(rows)
+        there = (other, _at(base, other))
+        ws = orca.Workspace(state0.n)
         ckpts = []
         for t in range(steps):
             if t % ckpt == 0:
-                ckpts.append(tuple(getattr(st, k).clone() for k in ("px", "py", "vx", "vy")))
-            orca.step(st, p, ws, out=nxt)
-            st, nxt = nxt, st
-        ctx.p = p
+                ckpts.append(here[0].clone())
+            orca.step(here[1], prm, ws, out=there[1])
+            here, there = there, here
+        ctx.p = prm
         ctx.steps = steps
         ctx.ckpt = ckpt
         ctx.ckpts = ckpts
-        ctx.base = st.clone()  # pref/radius/speed/class arrays for the replays
-        return st.px.clone(), st.py.clone()
+        ctx.end = here[0].clone()
+        ctx.base = base  # pref/radius/speed/class arrays for the replays
+        return here[0][0].clone(), here[0][1].clone()
 
     @staticmethod
     def backward(ctx, g_px, g_py):
@@ -68,25 +87,19 @@ class Rollout(torch.autograd.Function):
         # to the forward trajectory.  Mismatches are counted on the device and
         # checked once at the end.
         mismatch = torch.zeros((), dtype=torch.int64, device=dev)
-        ends = [tuple(getattr(base, k) for k in ("px", "py", "vx", "vy"))]
+        # the states of a segment after its checkpoint
+        seq = torch.empty((min(ckpt, max(steps, 1)), 4, n), dtype=torch.float32, device=dev)
+        after = [_at(base, rows) for rows in seq]
         for seg in range(n_seg - 1, -1, -1):
             t0 = seg * ckpt
-            t1 = min(t0 + ckpt, steps)
-            st = base.clone()
-            for k, v in zip(("px", "py", "vx", "vy"), ctx.ckpts[seg]):
-                getattr(st, k).copy_(v)
-            states = []
-            nxt = st.clone()
-            for t in range(t0, t1):
-                states.append(st.clone())
-                orca.step(st, p, ws, out=nxt)
-                st, nxt = nxt, st
-            want = ends[0] if seg == n_seg - 1 else ctx.ckpts[seg + 1]
-            for k, v in zip(("px", "py", "vx", "vy"), want):
-                mismatch += (getattr(st, k) != v).sum()
-            for t in range(t1 - 1, t0 - 1, -1):
-                orca.step_backward(states[t - t0], p, wsb, gpx, gpy, gvx, gvy, g_prx, g_pry,
-                                   g_tau, out=(gpx, gpy, gvx, gvy))
+            m = min(ckpt, steps - t0)
+            states = [_at(base, ctx.ckpts[seg])] + after[:m]
+            for k in range(m):
+                orca.step(states[k], p, ws, out=states[k + 1])
+            mismatch += (seq[m - 1] != (ctx.end if seg == n_seg - 1 else ctx.ckpts[seg + 1])).sum()
+            for k in range(m - 1, -1, -1):
+                orca.step_backward(states[k], p, wsb, gpx, gpy, gvx, gvy, g_prx, g_pry, g_tau,
+                                   out=(gpx, gpy, gvx, gvy))
         if int(mismatch.item()) != 0:
             raise RuntimeError("rollout backward: a replayed segment left the forward trajectory "
                                f"({int(mismatch.item())} differing values)")
