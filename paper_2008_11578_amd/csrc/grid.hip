@@ -177,6 +177,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const uint32_t *__restric
 }
 
 // (5) scatter into cell order: position = start[cell] + rank.
+// What bounds it is the writes: two small records per agent to scattered
+// positions, lines of which a block of another XCD also writes parts.  Each XCD
+// therefore takes a contiguous range of agents (xcd_tile): where callers hold
+// neighbours together, as the scenes of a batch are, its L2 then has the whole
+// line before it writes it back (512 scenes, 8.4M agents: 201 -> 140 us, the whole step 3.17 -> 3.11 ms; 1M
+// agents in random order: 10.5 us either way).
 __global__ __launch_bounds__(kBlock) void k_scatter(orca_agents_in in, int n,
                                                     const uint32_t *__restrict__ cell,
                                                     const uint32_t *__restrict__ rank,
@@ -184,7 +190,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(orca_agents_in in, int n,
                                                     float2 *__restrict__ s0,
                                                     float4 *__restrict__ s1)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+    const int i = xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     if (i >= n) return;
     const uint32_t pos = start[cell[i]] + rank[i];
     if (pos >= (uint32_t)n) return;  // cannot happen for a consistent histogram
