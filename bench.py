@@ -402,7 +402,7 @@ def capture_loop(step_fn, a, b, steps):
 def bench_batched(steps: int, cpu: bool = True):
     """512 uneven scenes (about 5.6M agents) per step: the autotuned batched
     step captured as a `steps`-step graph, against 512 sequential single-scene
-    steps captured as a graph.  The persistent step kernel's duration comes
+    steps captured as a graph.  The step kernel's duration comes
     from HIP events around it over eager steps after the graph; its roofline
     takes the oracle's work counters on the states opening and closing the
     timed graph; the oracle's batched step is timed beside it."""

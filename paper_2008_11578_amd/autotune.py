@@ -1,7 +1,7 @@
 """Autotuner for the ORCA step: picks the grid cell size (as a fraction of
 the neighbour distance) and, for batches, the launch form of the step kernel
-(persistent with per-XCD tile queues, or one workgroup per tile), the lanes
-per workgroup and the compiled neighbour-list capacity, by timing real steps
+(one workgroup per 64 agents, or of a given size), the lanes per
+workgroup and the compiled neighbour-list capacity, by timing real steps
 on the caller's state.
 
 Results are cached in a JSON file keyed by device architecture, form, agent

@@ -181,8 +181,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const uint32_t *__restric
 // positions, lines of which a block of another XCD also writes parts.  Each XCD
 // therefore takes a contiguous range of agents (xcd_tile): where callers hold
 // neighbours together, as the scenes of a batch are, its L2 then has the whole
-// line before it writes it back (512 scenes, 8.4M agents: 201 -> 140 us, the whole step 3.17 -> 3.11 ms; 1M
-// agents in random order: 10.5 us either way).
+// line before it writes it back (512 scenes, 5.6M agents: 201 -> 140 us,
+// the whole step 3.17 -> 3.11 ms; 1M agents in random order: 10.5 us either way).
 __global__ __launch_bounds__(kBlock) void k_scatter(orca_agents_in in, int n,
                                                     const uint32_t *__restrict__ cell,
                                                     const uint32_t *__restrict__ rank,

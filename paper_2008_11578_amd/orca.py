@@ -380,7 +380,7 @@ class Batch:
         self.has_accel = int(any(make_params(p).accel[c] > 0 or make_params(p).turn[c] > 0
                                  for p in scene_params for c in range(2)))
         self.mode = int(mode)
-        self.block = int(block)    # lanes per workgroup (64, 128, 256; 0 = 128)
+        self.block = int(block)    # lanes per workgroup in mode 1 (64, 128, 256; 0 = 64)
         self.k_tile = int(k_tile)  # compiled neighbour capacity (0 = smallest >= k)
         self.error = torch.zeros(1, dtype=torch.int32, device=device)
 
