@@ -162,14 +162,16 @@ def make_params(p) -> OrcaParams:
         cell = p.get("cell_size", 0.0)
         acc, turn = p.get("accel"), p.get("turn")
     else:
-        g = p.__getattribute__
+        g = lambda k: getattr(p, k)
         cell = p.cell_size
         acc, turn = getattr(p, "accel", None), getattr(p, "turn", None)
     out = OrcaParams(g("dt"), g("time_horizon"), g("neighbor_dist"), cell, int(g("max_neighbors")),
                      int(g("pref_is_goal")))
     out.par_eps = g("par_eps")
     # element by element: ctypes builds an array from a tuple far more slowly
-    for row, given in zip(out.f, g("f")):
+    f = g("f")
+    for a in range(2):
+        row, given = out.f[a], f[a]
         row[0], row[1] = float(given[0]), float(given[1])
     if acc is not None:
         a = out.accel

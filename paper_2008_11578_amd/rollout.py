@@ -88,7 +88,8 @@ class Rollout(torch.autograd.Function):
         # checked once at the end.
         mismatch = torch.zeros((), dtype=torch.int64, device=dev)
         # the states of a segment after its checkpoint
-        seq = torch.empty((min(ckpt, max(steps, 1)), 4, n), dtype=torch.float32, device=dev)
+        seq = torch.empty((min(ckpt, max(steps, 1)), *ctx.end.shape), dtype=torch.float32,
+                          device=dev)
         after = [_at(base, rows) for rows in seq]
         for seg in range(n_seg - 1, -1, -1):
             t0 = seg * ckpt

@@ -277,3 +277,24 @@ def test_small_crowd_grid_lists_match_oracle(n, cell):
         nbr, cnt = gpu_neighbors(s, p)
         ref = oracle.step(s, p, want_neighbors=True)
         np.testing.assert_array_equal(nbr, ref["nbr"])
+
+
+def test_rollout_of_a_state_held_in_columns():
+    """A state's arrays may have any shape of n elements: positions in columns
+    give the trajectory and gradients of flat ones, and keep their shape."""
+    import torch
+    from paper_2008_11578_amd import orca, rollout
+    sc = scenarios.c5_rollout(n=300, side=30.0)
+    got = []
+    for shape in ((300,), (300, 1)):
+        st = orca.State.from_arrays(sc.arrays())
+        prx, pry = st.pref_x.clone().requires_grad_(), st.pref_y.clone().requires_grad_()
+        for k in FIELDS:
+            setattr(st, k, getattr(st, k).reshape(shape))
+        tau = torch.tensor(2.0, device="cuda", requires_grad=True)
+        px, py = rollout.rollout(prx, pry, tau, st, sc.params, 7, 3)
+        assert px.shape == shape and py.shape == shape
+        (px.square().mean() + py.square().mean()).backward()
+        got.append((px.detach().reshape(-1), py.detach().reshape(-1), prx.grad, pry.grad, tau.grad))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
