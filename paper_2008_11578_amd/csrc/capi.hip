@@ -250,8 +250,9 @@ int orca_build_grid(const orca_agents_in *in, int32_t n, const orca_params *para
     const Work w = bind(L, ws);
     if (launch_grid_build(*in, n, *params, L, w, stream) != hipSuccess) return ORCA_EHIP;
     if (nbr || nbr_count) {
-        if ((n <= (params->max_neighbors > 24 ? kGroupListMaxLarge : kGroupListMax) ? launch_list_group(n, *params, w, nbr, nbr_count, stream)
-                            : launch_knn_export(*in, n, *params, L, w, nbr, nbr_count, stream)) !=
+        const int most = params->max_neighbors > 24 ? kGroupListMaxLarge : kGroupListMax;
+        if ((n <= most ? launch_list_group(n, *params, w, nbr, nbr_count, stream)
+                       : launch_knn_export(*in, n, *params, L, w, nbr, nbr_count, stream)) !=
             hipSuccess)
             return ORCA_EHIP;
     }
@@ -283,8 +284,9 @@ int step_impl(const orca_agents_in *in, const orca_agents_out *out, int32_t n,
         return ORCA_EHIP;
     if (events && events->step_begin && hipEventRecord(events->step_begin, stream) != hipSuccess)
         return ORCA_EHIP;
-    if ((n <= (has_hard_lines(*params) ? kGroupStepMaxHard : kGroupStepMax) ? launch_step_group(*in, *out, n, *params, w, whole, nbr, nbr_count, stream)
-                        : launch_step(*in, *out, n, *params, L, w, nbr, nbr_count, stream)) !=
+    const int most = has_hard_lines(*params) ? kGroupStepMaxHard : kGroupStepMax;
+    if ((n <= most ? launch_step_group(*in, *out, n, *params, w, whole, nbr, nbr_count, stream)
+                   : launch_step(*in, *out, n, *params, L, w, nbr, nbr_count, stream)) !=
         hipSuccess)
         return ORCA_EHIP;
     if (events && events->step_end && hipEventRecord(events->step_end, stream) != hipSuccess)
