@@ -249,14 +249,20 @@ __global__ __launch_bounds__(kScanThreads) void k_spawn_grid(
         // a positive size even when everything is a point at rest; larger where
         // the box would need more cells (or one cell, by its size, for all)
         double c = fmax(d * (1.0 + 1e-6), fmax(1e-3, fmax(w, h) * 1e-6));
-        for (int it = 0; it < 200 && (floor(w / c) + 1.0) * (floor(h / c) + 1.0) > kCandCells; ++it)
+        // the cell counts as they are used below: at the limit a quotient here
+        // and a product there can round to either side of a whole number
+        double inv = 1.0 / c, fx = floor(w * inv) + 1.0, fy = floor(h * inv) + 1.0;
+        while (fx * fy > (double)kCandCells) {
             c *= 1.125;
+            inv = 1.0 / c;
+            fx = floor(w * inv) + 1.0;
+            fy = floor(h * inv) + 1.0;
+        }
         gs.x0 = finite ? (double)b.x : 0.0;
         gs.y0 = finite ? (double)b.y : 0.0;
-        gs.inv = finite ? 1.0 / c : 0.0;
-        gs.nx = (int)(floor(w * gs.inv) + 1.0);
-        gs.ny = (int)(floor(h * gs.inv) + 1.0);
-        if ((double)gs.nx * (double)gs.ny > (double)kCandCells) gs.nx = gs.ny = 1;
+        gs.inv = finite ? inv : 0.0;
+        gs.nx = (int)fx;
+        gs.ny = (int)fy;
         *grid = gs;
     }
     __syncthreads();
