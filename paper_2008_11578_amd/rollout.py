@@ -23,13 +23,15 @@ MOVING = ("px", "py", "vx", "vy")
 
 def _at(base: orca.State, rows: torch.Tensor) -> orca.State:
     """`base` with the positions and velocities in the four rows of `rows`
-    (views; everything else is shared)."""
-    return dataclasses.replace(base, **dict(zip(MOVING, rows)))
+    (views, each in the shape of the array it stands for; everything else is
+    shared)."""
+    return dataclasses.replace(base, **{k: row.view(getattr(base, k).shape)
+                                        for k, row in zip(MOVING, rows)})
 
 
 def _rows(st: orca.State) -> torch.Tensor:
     """A copy of the positions and velocities, one row each."""
-    return torch.stack([getattr(st, k) for k in MOVING])
+    return torch.stack([getattr(st, k).reshape(-1) for k in MOVING])
 
 
 class Rollout(torch.autograd.Function):
@@ -47,12 +49,12 @@ class Rollout(torch.autograd.Function):
         base = dataclasses.replace(state0.clone(), pref_x=v_pref_x.detach().contiguous().clone(),
                                    pref_y=v_pref_y.detach().contiguous().clone())
         prm = orca.make_params(p)
-        rows = _rows(base)
-        here, there = (rows, _at(base, rows)), None
-        other = torch.empty_like(rows)
-        there = (other, _at(base, other))
         ws = orca.Workspace(state0.n)
         ckpts = []
+        here = there = (None, base)
+        if steps > 0:
+            base.agents_in()  # the arrays as they were given, before they become rows
+            here, there = ((r, _at(base, r)) for r in (_rows(base), _rows(base)))
         for t in range(steps):
             if t % ckpt == 0:
                 ckpts.append(here[0].clone())
@@ -62,9 +64,9 @@ class Rollout(torch.autograd.Function):
         ctx.steps = steps
         ctx.ckpt = ckpt
         ctx.ckpts = ckpts
-        ctx.end = here[0].clone()
+        ctx.end = here[0]
         ctx.base = base  # pref/radius/speed/class arrays for the replays
-        return here[0][0].clone(), here[0][1].clone()
+        return here[1].px.clone(), here[1].py.clone()
 
     @staticmethod
     def backward(ctx, g_px, g_py):
@@ -88,8 +90,7 @@ class Rollout(torch.autograd.Function):
         # checked once at the end.
         mismatch = torch.zeros((), dtype=torch.int64, device=dev)
         # the states of a segment after its checkpoint
-        seq = torch.empty((min(ckpt, max(steps, 1)), *ctx.end.shape), dtype=torch.float32,
-                          device=dev)
+        seq = torch.empty((min(ckpt, steps) if n_seg else 0, 4, n), dtype=torch.float32, device=dev)
         after = [_at(base, rows) for rows in seq]
         for seg in range(n_seg - 1, -1, -1):
             t0 = seg * ckpt
