@@ -519,8 +519,10 @@ __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a
     });
 }
 
+// (four wavefronts per SIMD up to K 10, as the LDS allows: one register too many
+// without the bound)
 template <int K, int BLOCK, bool ACC>
-__global__ __launch_bounds__(BLOCK) void k_adjoint(AdjArgs a)
+__global__ __launch_bounds__(BLOCK, K <= 10 && !ACC ? 4 : 1) void k_adjoint(AdjArgs a)
 {
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;

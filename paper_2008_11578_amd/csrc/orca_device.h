@@ -1500,6 +1500,11 @@ __device__ __forceinline__ void group_lp3(const LdsLines<BLOCK, ACC> &ls, int c,
 // (419 us by the walk alone), 512 scenes at 32, 40 and groups alone 3.68, 3.57
 // and 3.56 ms, 200,003 capped at 24 to 48 253, 238, 211 and 212 us; small
 // crowds are the same down to 32 and lose at 24 (4,999 mixed: 92 and 112 us).
+// Short lists in kernels with hard lines or a recorded active set are walked in any
+// case: groups take the registers of a wavefront per SIMD there (1M agents, kernel
+// in us, groups / walk: hard lines k 4 431 / 356, k 8 664 / 561, k 10 716 / 637,
+// but k 12 724 / 746; adjoint k 4 378 / 350, k 10 662 / 459, k 12 702 / 556, with
+// hard lines 660 / 463, 998 / 777, 1077 / 817).
 template <bool REC, int K, int BLOCK, bool ACC>
 __device__ __forceinline__ void wave_lp3(const LdsLines<BLOCK, ACC> &ls, int tid, bool need, int m,
                                          int fail, float vmax, float tx, float ty, float eps,
@@ -1508,9 +1513,10 @@ __device__ __forceinline__ void wave_lp3(const LdsLines<BLOCK, ACC> &ls, int tid
     constexpr int G = ACC ? 8 : 4;
     constexpr int NL = (K + (ACC ? kAccLines + kTurnLines : 0) + G - 1) / G;
     constexpr int kGroups = kWave / G;
+    constexpr bool kWalk = K <= (REC ? 12 : 10) && (REC || ACC);
     const uint64_t needm = __ballot(need);
     const int nf = __popcll(needm);
-    if (nf > (ACC ? 48 : 40)) {
+    if (kWalk || nf > (ACC ? 48 : 40)) {
         if (need) lp3<REC, BLOCK, ACC>(ls, m, fail, vmax, tx, ty, eps, vx, vy, rec);
         return;
     }

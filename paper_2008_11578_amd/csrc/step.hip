@@ -29,9 +29,17 @@ using dev::buf_idx;
 using dev::KnnShape;
 using dev::knn_select;
 
+// Wavefronts per SIMD the registers leave room for, where the lines' LDS leaves
+// room for as many (4 up to K 10): without the bound LP3 by groups takes more than
+// 128 registers and the fourth wavefront does not fit (1M agents, kernel in us
+// without / with: k 10 346 / 302 at 0.3 /m^2, 451 / 400 at 1.0).  At k 12, which
+// has room for three and a quarter, 457 / 479.
+template <int K, bool EXPORT>
+constexpr int kStepWaves = K <= 10 && !EXPORT ? 4 : 1;
+
 // EXPORT: the same step, also writing the neighbour lists it used.
 template <int K, int BLOCK, bool ACC, bool EXPORT>
-__global__ __launch_bounds__(BLOCK) void k_step(StepArgs a, dev::SceneP p)
+__global__ __launch_bounds__(BLOCK, (kStepWaves<K, EXPORT>)) void k_step(StepArgs a, dev::SceneP p)
 {
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;
