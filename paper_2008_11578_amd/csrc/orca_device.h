@@ -80,9 +80,9 @@ __device__ __forceinline__ double nb_key(float xi, float yi, float xj, float yj)
 // Exact k-nearest selection.
 //
 // Candidates are taken row by row from the cell stencil; each row is clipped
-// to the chord of the neighbour circle at the row's nearest y (FP64, with a
-// margin of 1e-6 cell on every bound, far above the rounding of the cell
-// coordinates), so every agent with key < R_n^2 is visited.
+// to the chord of the neighbour circle at the row's nearest y (FP32, of a circle
+// widened far beyond its rounding, see CellDisc), so every agent with
+// key < R_n^2 is visited.
 //
 // Pass 1 counts the in-range candidates of the lane in kBins bins of equal
 // area (bin = floor(key * kBins / R_n^2), monotone in the key); a group of
@@ -98,10 +98,14 @@ __device__ __forceinline__ double nb_key(float xi, float yi, float xj, float yj)
 // of the FP64 keys (rounding is monotone); equal FP32 keys among the entries
 // that decide the result are resolved by an insertion pass that recomputes
 // the FP64 keys and then compares the caller indices.
-// A lane whose counts could overflow (> 255 in range) or whose candidates do
-// not fit the buffer selects by repeated minimum instead (exact, slower).
+// Where the bins hold more than the buffer, or the counts could overflow (> 255
+// in range), a smaller circle is counted.  What kRecounts circles do not settle
+// (agents at one distance) is selected by repeated minimum, exact and far slower:
+// one such lane holds the whole call (131,072 agents, 2 /m^2, k 20, R_n 5 m, the
+// first call on a workspace: 1950 us when all these lanes took it, 390 now).
 // ---------------------------------------------------------------------------
 constexpr int kBins = 16;
+constexpr int kRecounts = 3;
 
 template <int K>
 struct KnnShape {
@@ -515,7 +519,8 @@ __device__ __forceinline__ void sort_entries(const float2 *__restrict__ s0,
 // Collects into the lane's buffer a set that holds its K nearest within R_n
 // (or all, when there are fewer) and its own agent; returns the number of
 // entries, or 0 when no such set fits the buffer, and the squared radius r2c
-// that bounds their keys.  rg2 (<= R_n^2) is a guess of a squared radius that
+// that bounds their keys (then a circle that holds K at least).  rg2
+// (<= R_n^2) is a guess of a squared radius that
 // holds at least K candidates; with `kept` (from the previous step) it is
 // expected to hold little more.  A circle that holds fewer than K is widened
 // to the whole neighbour circle, so the result never depends on the guess.
@@ -563,17 +568,22 @@ __device__ __forceinline__ uint32_t knn_collect(const GridMeta &g,
         if (n <= (uint32_t)K) r2c = g.rn2;  // too few: count them all
     }
     // pass 1: per-bin counts of the keys below r2c in kBins equal-area bins,
-    // and the candidates themselves while they fit the buffer.
+    // and the candidates themselves while they fit the buffer; again with
+    // another circle where that does not tell the nearest apart.
     double bscale;
     // Counts per bin: 4-bit counters of one group of candidates in `nib`
     // (a group adds at most kScanUnroll <= 15 to a bin), widened after each
     // group into byte counters, even bins in `hev` (byte k: bin 2k) and odd
-    // bins in `hod` (byte k: bin 2k + 1); bytes cannot overflow either, since
-    // a lane with more than 255 candidates takes the exact fallback.
+    // bins in `hod` (byte k: bin 2k + 1), which hold up to 255 candidates.
     static_assert(kScanUnroll <= 15, "a group must fit the 4-bit counters");
     uint64_t hev, hod, nib;
-    uint32_t total;
-    for (;;) {
+    uint32_t total, take;
+    int bstar;
+    // circles known to hold too few, and more than needed (rounded outwards)
+    float few = 0.0f, many = 0.0f;
+    auto outer = [](double r2) { return (float)r2 * 1.000001f; };
+    auto between = [&] { return fmin((double)(sqrtf(few) * sqrtf(many)), g.rn2); };
+    for (int tries = 0;; ++tries) {
         bscale = (double)kBins / r2c;
         hev = 0;
         hod = 0;
@@ -605,29 +615,43 @@ __device__ __forceinline__ uint32_t knn_collect(const GridMeta &g,
                 hod += (nib >> 4) & 0x0F0F0F0F0F0F0F0Full;
                 nib = 0;
             });
-        if (total > (uint32_t)K || !(r2c < g.rn2)) break;
-        r2c = g.rn2;  // the guessed circle holds fewer than K: count them all
+        if (total <= (uint32_t)K && r2c < g.rn2) {
+            few = (float)r2c;  // the guessed circle holds fewer than K: count them all
+            r2c = many > 0.0f ? between() : g.rn2;
+        } else if (total > 255u) {
+            many = outer(r2c);  // next a circle of 64, by its share
+            r2c = few > 0.0f ? between() : r2c * (64.0 / (double)total);
+        } else {
+            // threshold bin b*: the first bin at which the cumulative count
+            // reaches K others
+            uint32_t cum = 0;
+            take = total;
+            bstar = kBins - 1;
+            bool found = false;
+#pragma unroll
+            for (int b = 0; b < kBins; ++b) {
+                cum += (uint32_t)((((b & 1) ? hod : hev) >> ((b >> 1) * 8)) & 0xffull);
+                if (!found && cum > (uint32_t)K) {
+                    found = true;
+                    bstar = b;
+                    take = cum;
+                }
+            }
+            if (take <= (uint32_t)kCap) break;
+            // the bins are too wide: the circle up to b*, or into the last bin
+            const double bin = r2c / (double)kBins;
+            few = (float)((double)bstar * bin);
+            many = outer(r2c);
+            r2c = bstar + 1 < kBins ? (double)(bstar + 1) * bin * (1.0 + 1e-9)
+                                    : between();
+        }
+        if (tries == kRecounts) {
+            r2c = many > 0.0f ? fmin((double)many, g.rn2) : g.rn2;
+            return 0;
+        }
     }
     // every candidate of the circle is in the buffer, below its last slot
     const bool captured = total <= (uint32_t)(kCap - 1);
-
-    // threshold bin b*: the first bin at which the cumulative count reaches K
-    // others
-    uint32_t cum = 0, take = 0;
-    int bstar = kBins - 1;
-    bool found = false;
-#pragma unroll
-    for (int b = 0; b < kBins; ++b) {
-        cum += (uint32_t)((((b & 1) ? hod : hev) >> ((b >> 1) * 8)) & 0xffull);
-        if (!found && cum > (uint32_t)K) {
-            found = true;
-            bstar = b;
-            take = cum;
-        }
-    }
-    if (!found) take = total;
-
-    if (total > 255u || take > (uint32_t)kCap) return 0;
     // the circle that holds bins <= b* (with a relative margin far above the
     // rounding of key * bscale)
     const bool last = bstar + 1 >= kBins;
@@ -687,8 +711,8 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
         if (keep) *keep = fminf(next, g.rn);
         return (int)min(take - 1u, (uint32_t)K);
     }
-    // fallback: repeated minimum over all candidates, strictly above the last pick
-    const CellDisc disc = cell_disc(g, xd, yd, g.rn2);
+    // fallback: repeated minimum over that circle, strictly above the last pick
+    const CellDisc disc = cell_disc(g, xd, yd, r2c);
     int ya, yb;
     row_span(g, disc, ya, yb);
     double lk = -1.0;
@@ -707,7 +731,7 @@ __device__ int knn_select(const GridMeta &g, const uint32_t *__restrict__ start,
                 const double key = nb_key(xi, yi, c.x, c.y);
                 const bool above = key > lk || (key == lk && j > lj);
                 const bool below = key < bk || (key == bk && j < bj);
-                if (key < g.rn2 && t != spos && above && below) {
+                if (key < r2c && t != spos && above && below) {
                     bk = key;
                     bj = j;
                     bt = t;
