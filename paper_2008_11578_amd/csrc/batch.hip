@@ -141,22 +141,35 @@ __device__ __forceinline__ void batch_agent(const BatchArgs &a, int s, int first
 
 // The step: one 64-agent tile per wavefront, XCD-aware order.
 template <int K, int BLOCK, bool ACC>
-__global__ __launch_bounds__(BLOCK) void k_step_batched_flat(BatchArgs a)
+__global__ __launch_bounds__(BLOCK) void k_step_batched_flat(BatchArgs a, int chunk)
 {
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;
-    const int s0 = xcd_tile(blockIdx.x, gridDim.x) * BLOCK;
+    const int s0 = xcd_chunk_tile(blockIdx.x, gridDim.x, chunk) * BLOCK;
     batch_agent<K, BLOCK, ACC>(a, s0 + tid, scene_of(a.off, a.S, s0), lines, tid);
 }
+
+// Tiles that an XCD takes in one piece: the scenes of a batch can be far from
+// alike, and with an eighth of the whole in one piece the XCD that has the dense
+// ones ends last (kernel in us, in eighths / in chunks: 64 scenes of 16,384 agents,
+// the first eight dense 912 / 321, dense ones spread over it 326 / 432, by how late
+// the last of them starts; 6 scenes, 1M agents, all vehicles in the first, k 32
+// 1473 / 1013; 512 scenes of all sizes 2628 / 2671; the same at 8 to 1024 tiles).  At
+// least eight chunks for each XCD.
+constexpr int kChunkMax = 64;
 
 template <int K, int BLOCK>
 hipError_t launch_step_batched_b(const BatchArgs &a, bool acc, hipStream_t stream)
 {
-    const dim3 nb((a.n + BLOCK - 1) / BLOCK);
+    const int nb = (a.n + BLOCK - 1) / BLOCK;
+    const int share = nb / (8 * kXcds);
+    const int chunk = share < 1 ? 1 : (share > kChunkMax ? kChunkMax : share);
     if (acc)
-        hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, true>), nb, dim3(BLOCK), 0, stream, a);
+        hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, true>), dim3(nb), dim3(BLOCK), 0, stream,
+                           a, chunk);
     else
-        hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, false>), nb, dim3(BLOCK), 0, stream, a);
+        hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, false>), dim3(nb), dim3(BLOCK), 0, stream,
+                           a, chunk);
     return hipGetLastError();
 }
 

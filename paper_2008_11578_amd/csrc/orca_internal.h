@@ -106,6 +106,19 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
     return x * q + (x < r ? x : r) + b / kXcds;
 }
 
+// The same with the tiles dealt to the XCDs in chunks, for work that is uneven
+// from one end of the tiles to the other (see launch_step_batched_b).  Each round of
+// eight chunks starts at another XCD, so that work that recurs every so many
+// tiles does not fall to the same one.
+__device__ __forceinline__ int xcd_chunk_tile(int b, int nb, int chunk)
+{
+    const int whole = nb / (kXcds * chunk) * (kXcds * chunk);
+    if (b >= whole) return whole + xcd_tile(b - whole, nb - whole);
+    const int l = b / kXcds, round = l / chunk;
+    const int x = (b + round + round / kXcds + round / (kXcds * kXcds)) % kXcds;
+    return (round * kXcds + x) * chunk + l % chunk;
+}
+
 // Rank of this lane's agent in cell c, counted into count[c]: neighbouring lanes
 // of one cell (a caller whose order follows the places) count together, by the
 // first of them.  Called by all lanes that have an agent, in index order.
