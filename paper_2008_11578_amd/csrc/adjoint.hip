@@ -566,62 +566,186 @@ __global__ __launch_bounds__(kWave) void k_adjoint_group(AdjArgs a, float rn)
     adjoint_vjp(a, f, [&](int q) { return lds.nbr[who][q]; });
 }
 
-// The smallest edge of target j above `last` (edge index + 1, 0 for none),
-// among all c of them.
-__device__ __forceinline__ uint32_t next_edge(const AdjointBufs &b, int j, uint32_t last)
+// Targets of more edges than a list holds are ordered by their own lane up to
+// kHubLane, in its column of the wavefront's LDS, up to kHubWave by the wavefront
+// there, and beyond as linked lists in place.
+// (a column of 32 and not of 16 or 24: a vehicle among pedestrians has about k
+// edges, and vehicles lie together in many orders; 5,000 agents, 50 of them with
+// discs of 2.5 m, k 20: 202 us at 16, 100 at 24 and 32; k 32 260 at 24, 171 at 32)
+constexpr int kHubLane = 32;
+constexpr int kHubWave = kHubLane * kWave / 2;
+
+// Two chains (edge index + 1, ended by 0), each ascending, into one.
+__device__ uint32_t merge_chains(uint32_t *__restrict__ next, uint32_t x, uint32_t y)
 {
-    uint32_t best = ~0u;
-    for (int q = 0; q < kEdgeSlots; ++q) {
-        const uint32_t e = b.e_list[(int64_t)j * kEdgeSlots + q];
-        if (e >= last && e < best) best = e;
+    if (!x || !y) return x ? x : y;
+    uint32_t head = 0, last = 0;
+    while (x && y) {
+        const uint32_t take = x < y ? x : y;
+        (x < y ? x : y) = next[take - 1u];
+        if (last)
+            next[last - 1u] = take;
+        else
+            head = take;
+        last = take;
     }
-    for (uint32_t h = b.e_head[j]; h; h = b.e_next[h - 1u])
-        if (h - 1u >= last && h - 1u < best) best = h - 1u;
-    return best;
+    next[last - 1u] = x ? x : y;
+    return head;
+}
+
+// A chain of m edges beyond the LDS (agents at one place, which all look at the
+// same few) and the target's list, as one ascending chain: every lane orders a
+// 64th of it, one edge after another into chains of doubling lengths (`bins`, the
+// lane's column), and the lanes' chains are merged pair by pair.
+__device__ uint32_t sort_chain(const AdjointBufs &b, int64_t j, uint32_t m, uint32_t *bins, int lane)
+{
+    uint32_t *next = b.e_next;
+    const uint32_t rest = m - (uint32_t)kEdgeSlots, share = (rest + kWave - 1) / kWave;
+    uint32_t first = 0, h = b.e_head[j];
+    for (uint32_t at = 0; at < rest && h; ++at) {
+        if (at == (uint32_t)lane * share) first = h;
+        h = next[h - 1u];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    for (int k = 0; k < kHubLane; ++k) bins[k * kWave] = 0u;
+    const uint32_t from = (uint32_t)lane * share;
+    uint32_t left = from < rest ? min(share, rest - from) : 0u;
+    uint32_t mine = lane < kEdgeSlots ? b.e_list[j * kEdgeSlots + lane] + 1u : 0u;
+    while (mine || left) {
+        uint32_t chain = mine;
+        if (!chain) {
+            chain = first;
+            first = next[chain - 1u];
+            --left;
+        }
+        mine = 0u;
+        next[chain - 1u] = 0u;
+        for (int k = 0;; ++k) {
+            const uint32_t have = bins[k * kWave];
+            bins[k * kWave] = 0u;
+            chain = merge_chains(next, have, chain);
+            if (!have || k == kHubLane - 1) {
+                bins[k * kWave] = chain;
+                break;
+            }
+        }
+    }
+    uint32_t chain = 0;
+    for (int k = 0; k < kHubLane; ++k) chain = merge_chains(next, bins[k * kWave], chain);
+    for (int o = 1; o < kWave; o <<= 1) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        const uint32_t other = (uint32_t)__shfl_down((int)chain, o, kWave);
+        if (lane % (2 * o) == 0) chain = merge_chains(next, chain, other);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    return (uint32_t)__shfl((int)chain, 0, kWave);
+}
+
+// The sum of the m > kHubLane edges of target j, by a wavefront, in increasing edge
+// index.  `lds`: the wavefront's.
+__device__ float4 hub_sum(const AdjointBufs &b, int64_t j, uint32_t m, uint32_t *lds, int lane)
+{
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    auto add = [&](const float4 &v) {
+        s.x += v.x;
+        s.y += v.y;
+        s.z += v.z;
+        s.w += v.w;
+    };
+    dev::lane_order<kWave>();  // the lanes' own columns are read
+    if (m > (uint32_t)kHubWave) {
+        for (uint32_t h = sort_chain(b, j, m, lds + lane, lane); h; h = b.e_next[h - 1u])
+            add(b.e_val[h - 1u]);
+        return s;
+    }
+    uint32_t *sorted = lds + kHubWave;
+    if (lane < kEdgeSlots) lds[lane] = b.e_list[j * kEdgeSlots + lane];
+    uint32_t h = b.e_head[j];
+    for (uint32_t q = kEdgeSlots; q < m && h; ++q) {
+        if (lane == 0) lds[q] = h - 1u;
+        h = b.e_next[h - 1u];
+    }
+    dev::lane_order<kWave>();
+    for (uint32_t q = lane; q < m; q += kWave) {
+        const uint32_t e = lds[q];
+        uint32_t rank = 0;
+#pragma unroll 4
+        for (uint32_t r = 0; r < m; ++r) rank += lds[r] < e ? 1u : 0u;
+        sorted[rank] = e;
+    }
+    dev::lane_order<kWave>();
+    for (uint32_t q = 0; q < m; q += kWave) {
+        const float4 v = b.e_val[sorted[min(q + (uint32_t)lane, m - 1u)]];
+        auto lane_of = [](float x, int r) {
+            return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), r));
+        };
+        for (int r = 0; r < min((int)(m - q), kWave); ++r)
+            add(make_float4(lane_of(v.x, r), lane_of(v.y, r), lane_of(v.z, r), lane_of(v.w, r)));
+    }
+    return s;
 }
 
 // Each target sums its edges in increasing edge index (= source agent, slot):
-// those of its list ordered in registers, or picked one by one when there are
-// more.  TAU: the block's tau contributions too (a fixed order: lanes, then
-// wavefronts).
+// those of its list ordered in registers, more of them as above.  (One walk over
+// the chain for each edge summed cost a lane c (c - 8) dependent loads for c edges:
+// 600 agents at one place among 5,000, k 10: 4640 us a call, 540 so.)  TAU: the block's
+// tau contributions too (a fixed order: lanes, then wavefronts).
 template <bool TAU>
 __global__ __launch_bounds__(kBlock) void k_edge_gather(int n, AdjointBufs b, float *gpx0, float *gpy0,
                                                         float *gvx0, float *gvy0)
 {
+    __shared__ uint32_t order[kBlock / kWave][kHubLane * kWave];
+    const int lane = threadIdx.x % kWave;
+    uint32_t *lds = order[threadIdx.x / kWave];
     const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j < n) {
-        const uint32_t c = b.e_cnt[j];
-        float sx = 0.0f, sy = 0.0f, tx = 0.0f, ty = 0.0f;
-        auto add = [&](const float4 &v) {
-            sx += v.x;
-            sy += v.y;
-            tx += v.z;
-            ty += v.w;
-        };
+    const uint32_t c = j < n ? b.e_cnt[j] : 0u;
+    float sx = 0.0f, sy = 0.0f, tx = 0.0f, ty = 0.0f;
+    auto add = [&](const float4 &v) {
+        sx += v.x;
+        sy += v.y;
+        tx += v.z;
+        ty += v.w;
+    };
+    if (c <= (uint32_t)kHubLane) {
+        uint32_t e[kEdgeSlots];
+        static_assert(kEdgeSlots == 8, "two loads and a network of eight");
+        const uint4 *l = (const uint4 *)(b.e_list + (int64_t)min(j, n - 1) * kEdgeSlots);
+        const uint4 p = l[0], q = c > 4u ? l[1] : make_uint4(~0u, ~0u, ~0u, ~0u);
+        e[0] = c > 0u ? p.x : ~0u;
+        e[1] = c > 1u ? p.y : ~0u;
+        e[2] = c > 2u ? p.z : ~0u;
+        e[3] = c > 3u ? p.w : ~0u;
+        e[4] = c > 4u ? q.x : ~0u;
+        e[5] = c > 5u ? q.y : ~0u;
+        e[6] = c > 6u ? q.z : ~0u;
+        e[7] = c > 7u ? q.w : ~0u;
+        dev::sort_network<kEdgeSlots>(e);
         if (c <= (uint32_t)kEdgeSlots) {
-            uint32_t e[kEdgeSlots];
-            static_assert(kEdgeSlots == 8, "two loads and a network of eight");
-            const uint4 *l = (const uint4 *)(b.e_list + (int64_t)j * kEdgeSlots);
-            const uint4 p = l[0], q = c > 4u ? l[1] : make_uint4(~0u, ~0u, ~0u, ~0u);
-            e[0] = c > 0u ? p.x : ~0u;
-            e[1] = c > 1u ? p.y : ~0u;
-            e[2] = c > 2u ? p.z : ~0u;
-            e[3] = c > 3u ? p.w : ~0u;
-            e[4] = c > 4u ? q.x : ~0u;
-            e[5] = c > 5u ? q.y : ~0u;
-            e[6] = c > 6u ? q.z : ~0u;
-            e[7] = c > 7u ? q.w : ~0u;
-            dev::sort_network<kEdgeSlots>(e);
 #pragma unroll
             for (int k = 0; k < kEdgeSlots; ++k)
                 if ((uint32_t)k < c) add(b.e_val[e[k]]);
         } else {
-            for (uint32_t k = 0, last = 0; k < c; ++k) {
-                const uint32_t e = next_edge(b, j, last);
-                add(b.e_val[e]);
-                last = e + 1u;
+            uint32_t *col = lds + lane;
+#pragma unroll
+            for (int k = 0; k < kEdgeSlots; ++k) col[k * kWave] = e[k];
+            uint32_t h = b.e_head[j];
+            for (int k = kEdgeSlots; k < (int)c && h; ++k) {
+                int at = k;
+                for (; at > 0 && col[(at - 1) * kWave] > h - 1u; --at)
+                    col[at * kWave] = col[(at - 1) * kWave];
+                col[at * kWave] = h - 1u;
+                h = b.e_next[h - 1u];
             }
+            for (uint32_t k = 0; k < c; ++k) add(b.e_val[col[k * kWave]]);
         }
+    }
+    for (uint64_t hubs = __ballot(c > (uint32_t)kHubLane); hubs; hubs &= hubs - 1) {
+        const int who = __ffsll((long long)hubs) - 1;
+        const float4 v = hub_sum(b, (int64_t)(j - lane + who), (uint32_t)__shfl((int)c, who, kWave),
+                                 lds, lane);
+        if (lane == who) add(v);
+    }
+    if (j < n) {
         gpx0[j] += sx;
         gpy0[j] += sy;
         gvx0[j] += tx;
