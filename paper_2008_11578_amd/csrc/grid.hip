@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_count(const float *__restrict__
                                                        const float *__restrict__ py, int n,
                                                        const float4 *__restrict__ partial,
                                                        int n_partial, float rn, float cs_req,
-                                                       int max_cells,
+                                                       int max_cells, int few_cells,
                                                        GridMeta *__restrict__ meta,
                                                        uint32_t *__restrict__ cell,
                                                        uint32_t *__restrict__ rank,
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_count(const float *__restrict__
         b = block_bbox<kBlock>(b);
         if (threadIdx.x == 0) {
             GridMeta h;
-            grid_geometry(b, rn, cs_req, max_cells, h);
+            grid_geometry(b, rn, cs_req, max_cells, h, few_cells);
             h.cell_base = 0;
             h.agent_base = 0;
             h.n = n;
@@ -197,51 +197,137 @@ __global__ __launch_bounds__(kBlock) void k_scatter(orca_agents_in in, int n,
     write_record(in, i, pos, s0, s1);
 }
 
-// (4 + 5) for a small crowd: every block scans the whole histogram (at most
-// kSmallCells cells) into LDS and scatters its agents; block 0 stores the starts
-// for the kernels after this one.  Two launches fewer: a crowd of this size
-// spends its time on launches.  (16,384 agents: grid 19 -> 13 us.)
-constexpr int kSmallCells = 8192;
+// (4 + 5) for a small crowd, which spends its time on launches: two fewer.  Every
+// block has the whole histogram to go through, so blocks are as large as they
+// can be, and each loads its share at once.
+//   up to kTable cells: scanned into a table in LDS, an agent reads its start there;
+//   more: summed by runs of kSub cells (16 lanes a run), the sums scanned in LDS;
+//         an agent's start is its run's prefix and what the run holds before its
+//         cell.
+// The starts are also stored for the kernels after this one, each block a part of
+// them.  Whole builds in us, five launches / this: 16,384 agents in 2,304 cells 19.1
+// / 14.2, 20,000 in 28,390 cells 28.1 / 23.6, 32,768 in them 21.5 / 23.9.  The
+// geometry therefore asks for kTable cells where larger ones cost nothing (the
+// group kernels take a row's candidates 16 at a time).  (With kTable as the limit a
+// crowd spread wide had far larger cells than it asked for: 30,000 agents, one of
+// them 7 km away, 2^20 cells allowed, lists 61 us in five launches, 206 with the
+// limit, 42 now.)
+constexpr int kSmallBlock = 1024;
+constexpr int kTable = 8 * kSmallBlock;
+constexpr int kSub = 32;
+constexpr int kSmallCells = 131072 + kSub;  // workspaces of up to 65,536 agents by default
+constexpr int kSubs = kSmallCells / kSub;
+static_assert(kSubs <= kTable, "run sums take the table's place");
 
-__global__ __launch_bounds__(kBlock) void k_scan_scatter(orca_agents_in in, int n,
-                                                         const uint32_t *__restrict__ cell,
-                                                         const uint32_t *__restrict__ rank,
-                                                         const uint32_t *__restrict__ count,
-                                                         const GridMeta *__restrict__ meta,
-                                                         uint32_t *__restrict__ start,
-                                                         float2 *__restrict__ s0,
-                                                         float4 *__restrict__ s1)
+__global__ __launch_bounds__(kSmallBlock) void k_scan_scatter(orca_agents_in in, int n,
+                                                              const uint32_t *__restrict__ cell,
+                                                              const uint32_t *__restrict__ rank,
+                                                              const uint32_t *__restrict__ count,
+                                                              const GridMeta *__restrict__ meta,
+                                                              uint32_t *__restrict__ start,
+                                                              float2 *__restrict__ s0,
+                                                              float4 *__restrict__ s1)
 {
-    __shared__ uint32_t first[kSmallCells];
+    __shared__ uint32_t table[kTable];
     const int n_cells = min(meta->n_cells, kSmallCells);
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    const uint32_t mine = i < n ? cell[i] : 0u, r = i < n ? rank[i] : 0u;
-    uint32_t before = 0;
-    for (int base = 0; base < n_cells; base += kScanTile) {
-        uint32_t v[kPer], s = 0, tot;
+    const int tid = threadIdx.x;
+    const int i = blockIdx.x * kSmallBlock + tid;
+    const uint32_t mine = i < n ? min(cell[i], (uint32_t)n_cells - 1u) : 0u;
+    uint32_t pos = i < n ? rank[i] : 0u;
+    // (the count's region is a multiple of a run long; past the cells in use it is
+    // not read into a sum)
+    const uint4 *four = (const uint4 *)count;
+    const int last = (n_cells - 1) / 4;
+    auto cells4 = [&](int c) {  // counts of cells c .. c + 3, 0 past the last one
+        uint4 v = four[min(c / 4, last)];
+        v.x = c < n_cells ? v.x : 0u;
+        v.y = c + 1 < n_cells ? v.y : 0u;
+        v.z = c + 2 < n_cells ? v.z : 0u;
+        v.w = c + 3 < n_cells ? v.w : 0u;
+        return v;
+    };
+    uint32_t tot;
+    if (n_cells <= kTable) {
+        const int c0 = tid * 8;
+        const uint4 a = cells4(c0), b = cells4(c0 + 4);
+        const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        uint32_t s = 0;
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int c = base + threadIdx.x * kPer + k;
-            v[k] = c < n_cells ? count[c] : 0u;
-            s += v[k];
-        }
-        uint32_t run = before + block_excl_scan<kBlock>(s, &tot);
+        for (int k = 0; k < 8; ++k) s += v[k];
+        uint32_t run = block_excl_scan<kSmallBlock>(s, &tot);
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int c = base + threadIdx.x * kPer + k;
-            if (c < n_cells) {
-                first[c] = run;
-                if (blockIdx.x == 0) start[c] = run;
+        for (int k = 0; k < 8; ++k) {
+            if (c0 + k < n_cells) {
+                table[c0 + k] = run;
+                if (blockIdx.x == 0) start[c0 + k] = run;
             }
             run += v[k];
         }
-        before += tot;
+        __syncthreads();
+        pos += table[mine];
+    } else {
+        const int n_sub = (n_cells + kSub - 1) / kSub;
+        constexpr int kLanes = kSub / 4, kGroups = kSmallBlock / kLanes, kLoads = 16;
+        for (int q0 = tid / kLanes; q0 < n_sub; q0 += kLoads * kGroups) {
+            uint4 v[kLoads];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u)
+                v[u] = cells4((q0 + u * kGroups) * kSub + tid % kLanes * 4);
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                uint32_t t = v[u].x + v[u].y + v[u].z + v[u].w;
+#pragma unroll
+                for (int o = kLanes / 2; o > 0; o >>= 1) t += (uint32_t)__shfl_xor((int)t, o, kLanes);
+                if (tid % kLanes == 0 && q0 + u * kGroups < n_sub) table[q0 + u * kGroups] = t;
+            }
+        }
+        __syncthreads();
+        constexpr int kPerThread = (kSubs + kSmallBlock - 1) / kSmallBlock;
+        uint32_t v[kPerThread], s = 0;
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            const int q = tid * kPerThread + k;
+            v[k] = q < n_sub ? table[q] : 0u;
+            s += v[k];
+        }
+        uint32_t run = block_excl_scan<kSmallBlock>(s, &tot);
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            const int q = tid * kPerThread + k;
+            if (q < n_sub) table[q] = run;
+            run += v[k];
+        }
+        __syncthreads();
+        for (int q = blockIdx.x * (kSmallBlock / kSub) + tid / kSub; q < n_sub;
+             q += gridDim.x * (kSmallBlock / kSub)) {
+            const int c = q * kSub + tid % kSub;
+            uint32_t before = c < n_cells ? count[c] : 0u;
+            const uint32_t have = before;
+#pragma unroll
+            for (int o = 1; o < kSub; o <<= 1) {
+                const uint32_t t = (uint32_t)__shfl_up((int)before, o, kSub);
+                before += tid % kSub >= o ? t : 0u;
+            }
+            if (c < n_cells) start[c] = table[q] + before - have;
+        }
+        if (i < n) {
+            const int in_run = (int)mine % kSub, c0 = (int)mine - in_run;
+            pos += table[c0 / kSub];
+            for (int q0 = 0; q0 < in_run; q0 += 16) {
+                uint4 h[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) h[u] = cells4(c0 + q0 + 4 * u);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int q = q0 + 4 * u;
+                    pos += (q < in_run ? h[u].x : 0u) + (q + 1 < in_run ? h[u].y : 0u) +
+                           (q + 2 < in_run ? h[u].z : 0u) + (q + 3 < in_run ? h[u].w : 0u);
+                }
+            }
+        }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) start[n_cells] = (uint32_t)n;
-    __syncthreads();
-    if (i >= n) return;
-    const uint32_t pos = first[min(mine, (uint32_t)n_cells - 1u)] + r;
-    if (pos >= (uint32_t)n) return;  // cannot happen for a consistent histogram
+    if (blockIdx.x == 0 && tid == 0) start[n_cells] = (uint32_t)n;
+    if (i >= n || pos >= (uint32_t)n) return;  // the latter cannot happen for a consistent histogram
     write_record(in, i, pos, s0, s1);
 }
 
@@ -256,9 +342,11 @@ __global__ void k_fill_zero(uint4 *p, size_t n16)
 
 namespace {
 
-// (1) to (3), with at most max_cells cells.
+// (1) to (3), with at most max_cells cells (few_cells: see grid_geometry; of crowds
+// whose geometry is formed in (3)).
 void launch_count(const orca_agents_in &in, int n, float rn, float cell_size, int max_cells,
-                  const Work &w, hipStream_t stream, uint32_t *clear, int64_t clear_len)
+                  int few_cells, const Work &w, hipStream_t stream, uint32_t *clear,
+                  int64_t clear_len)
 {
     const int nb = (int)((n + kBlock - 1) / kBlock);
     const int nbb = nb < kBboxBlocks ? nb : kBboxBlocks;
@@ -269,7 +357,7 @@ void launch_count(const orca_agents_in &in, int n, float rn, float cell_size, in
         hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kBlock), 0, stream, w.partial, nbb, rn,
                            cell_size, max_cells, n, w.meta);
     hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, stream, in.px, in.py, n,
-                       fused ? w.partial : nullptr, nbb, rn, cell_size, max_cells, w.meta, w.cell,
+                       fused ? w.partial : nullptr, nbb, rn, cell_size, max_cells, few_cells, w.meta, w.cell,
                        w.rank, w.count);
 }
 }  // namespace
@@ -279,16 +367,15 @@ hipError_t launch_grid_build(const orca_agents_in &in, int n, const orca_params 
                              int64_t clear_len)
 {
     const int nb = (int)((n + kBlock - 1) / kBlock);
-    if (nb > kFusedParts)
+    // (a workspace that allows more cells is used as it asks: how many the crowd
+    // needs is known on the device only)
+    if (nb > kFusedParts || L.max_cells > kSmallCells)
         return launch_grid_build_rn(in, n, p.neighbor_dist, p.cell_size, L, w, stream, clear,
                                     clear_len);
-    // a crowd this small is stepped by groups of lanes, which take a row's
-    // candidates 16 at a time: cells finer than kSmallCells give would not help
-    // (the cells change no result)
-    const int max_cells = L.max_cells < kSmallCells ? (int)L.max_cells : kSmallCells;
-    launch_count(in, n, p.neighbor_dist, p.cell_size, max_cells, w, stream, clear, clear_len);
-    hipLaunchKernelGGL(k_scan_scatter, dim3(nb), dim3(kBlock), 0, stream, in, n, w.cell, w.rank,
-                       w.count, w.meta, w.start, w.s0, w.s1);
+    launch_count(in, n, p.neighbor_dist, p.cell_size, (int)L.max_cells, kTable, w, stream, clear,
+                 clear_len);
+    hipLaunchKernelGGL(k_scan_scatter, dim3((n + kSmallBlock - 1) / kSmallBlock), dim3(kSmallBlock), 0,
+                       stream, in, n, w.cell, w.rank, w.count, w.meta, w.start, w.s0, w.s1);
     return hipGetLastError();
 }
 
@@ -296,7 +383,7 @@ hipError_t launch_grid_build_rn(const orca_agents_in &in, int n, float rn, float
                                 const Layout &L, const Work &w, hipStream_t stream, uint32_t *clear,
                                 int64_t clear_len)
 {
-    launch_count(in, n, rn, cell_size, (int)L.max_cells, w, stream, clear, clear_len);
+    launch_count(in, n, rn, cell_size, (int)L.max_cells, 0, w, stream, clear, clear_len);
     return launch_scan_scatter(in, n, L, w, w.meta, stream);
 }
 

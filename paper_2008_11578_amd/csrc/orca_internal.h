@@ -213,9 +213,12 @@ __device__ float4 block_bbox(float4 b)
 //        margin far above the rounding of the FP64 cell coordinates
 //   the cell size grows (and m is re-derived) until nx * ny <= max_cells;
 //   non-finite boxes (NaN/Inf positions) collapse to a single cell.
+// few_cells > 0 asks for so few cells where that costs nothing: those finer than
+// R_n in any case, others up to kStretch R_n (see k_scan_scatter).
 // Fills every field except cell_base, agent_base, n and seg_end.
+constexpr double kStretch = 1.6;
 __device__ __forceinline__ void grid_geometry(float4 b, float rn, float cs_req, int max_cells,
-                                              GridMeta &g)
+                                              GridMeta &g, int few_cells = 0)
 {
     const bool finite = isfinite(b.x) && isfinite(b.y) && isfinite(b.z) && isfinite(b.w);
     const double w = finite ? (double)b.z - (double)b.x : 0.0;
@@ -223,13 +226,23 @@ __device__ __forceinline__ void grid_geometry(float4 b, float rn, float cs_req, 
     double c0 = cs_req > 0.0f ? (double)cs_req : (double)rn;
     int m = 1;
     double cs = c0, fx = 0.0, fy = 0.0;
-    for (int it = 0; it < 200; ++it) {
-        m = (int)ceil((double)rn / c0 - 1e-6);
+    auto cells_of = [&](double c) {
+        m = (int)ceil((double)rn / c - 1e-6);
         if (m < 1) m = 1;
-        cs = fmax(c0, (double)rn / m) * (1.0 + 1e-5);
+        cs = fmax(c, (double)rn / m) * (1.0 + 1e-5);
         fx = floor(w / cs) + 1.0;
         fy = floor(h / cs) + 1.0;
-        if (fx * fy <= (double)max_cells) break;
+        return fx * fy;
+    };
+    if (few_cells > 0) {
+        double c = c0;
+        for (int it = 0; it < 64 && c <= kStretch * (double)rn && !(cells_of(c) <= (double)few_cells);
+             ++it)
+            c *= 1.25;
+        c0 = c <= kStretch * (double)rn ? c : fmax(c0, (double)rn);
+    }
+    for (int it = 0; it < 200; ++it) {
+        if (cells_of(c0) <= (double)max_cells) break;
         c0 *= 1.25;
     }
     if (!(fx * fy <= (double)max_cells) || !(cs > 0.0)) {

@@ -1,0 +1,66 @@
+"""The grid of a crowd of up to 32,768 agents, scanned and scattered in one kernel."""
+import numpy as np
+import pytest
+
+from paper_2008_11578_amd import scenarios
+
+pytestmark = pytest.mark.gpu
+
+
+def _cell(ws):
+    """(cell size, cells) of the last grid: the workspace begins with its origin
+    (2 floats), the cell size, the neighbour distance and the cells per axis."""
+    import torch
+    head = ws.buf[:24].cpu()
+    return float(head.view(torch.float32)[2]), int(head.view(torch.int32)[4:6].prod())
+
+
+def _spread(n, k, seed=3):
+    """Eight groups and one agent far away."""
+    p = scenarios.Params(neighbor_dist=5.0, max_neighbors=k)
+    sc = scenarios.random_state(n, float(np.sqrt(n / 4.0)), seed=seed, params=p)
+    rng = np.random.default_rng(seed)
+    at, group = rng.uniform(0.0, 600.0, (8, 2)), rng.integers(0, 8, n)
+    sc.px = (sc.px + at[group, 0]).astype(np.float32)
+    sc.py = (sc.py + at[group, 1]).astype(np.float32)
+    sc.px[n // 2] = sc.py[n // 2] = 900.0
+    return sc, p
+
+
+@pytest.mark.parametrize("n,max_cells", [(20000, 0), (32768, 0), (32768, 65536), (2100, 40000),
+                                         (30000, 1 << 20), (9000, 131072), (9000, 132000)])
+def test_cells_are_as_large_as_asked_where_they_fit(n, max_cells):
+    """The workspace bounds the cells, and the cell size grows only where the
+    crowd's box needs more than that; the lists are the oracle's either way."""
+    import oracle
+    import torch
+    from paper_2008_11578_amd import orca
+    sc, p = _spread(n, 10)
+    ws = orca.Workspace(n, max_cells=max_cells)
+    nbr, cnt = orca.build_grid(orca.State.from_arrays(sc), p, ws)
+    torch.cuda.synchronize()
+    size, cells = _cell(ws)
+    assert 20000 < cells <= 40000
+    np.testing.assert_allclose(size, 5.0 * (1.0 + 1e-5), rtol=1e-6)
+    np.testing.assert_array_equal(nbr.cpu().numpy(), oracle.step(sc, p, want_neighbors=True)["nbr"])
+
+
+@pytest.mark.parametrize("nx", [1, 63, 64, 65, 255, 4096, 4161, 65535, 65536])
+@pytest.mark.parametrize("n", [2049, 32768])
+def test_cell_counts_about_whole_runs(n, nx):
+    """A crowd on a line in as many cells as a run of the scan, more, fewer, and as
+    many as the workspace allows: lists equal the oracle's."""
+    import oracle
+    import torch
+    from paper_2008_11578_amd import orca
+    p = scenarios.Params(neighbor_dist=1.0, max_neighbors=6)
+    sc = scenarios.random_state(n, 1.0, seed=nx, params=p)
+    rng = np.random.default_rng(nx)
+    x = rng.uniform(0.0, nx * (1.0 + 1e-5) - 0.5, n)
+    x[0], x[1] = 0.0, nx * (1.0 + 1e-5) - 0.5
+    sc.px, sc.py = x.astype(np.float32), np.zeros(n, np.float32)
+    ws = orca.Workspace(n, max_cells=65536)
+    nbr, cnt = orca.build_grid(orca.State.from_arrays(sc), p, ws)
+    torch.cuda.synchronize()
+    assert _cell(ws)[1] == nx
+    np.testing.assert_array_equal(nbr.cpu().numpy(), oracle.step(sc, p, want_neighbors=True)["nbr"])
