@@ -152,18 +152,23 @@ __global__ __launch_bounds__(BLOCK) void k_step_batched_flat(BatchArgs a, int ch
 // Tiles that an XCD takes in one piece: the scenes of a batch can be far from
 // alike, and with an eighth of the whole in one piece the XCD that has the dense
 // ones ends last (kernel in us, in eighths / in chunks: 64 scenes of 16,384 agents,
-// the first eight dense 912 / 321, dense ones spread over it 326 / 432, by how late
+// the first eight dense 912 / 320, dense ones spread over it 326 / 430, by how late
 // the last of them starts; 6 scenes, 1M agents, all vehicles in the first, k 32
-// 1473 / 1013; 512 scenes of all sizes 2628 / 2671; the same at 8 to 1024 tiles).  At
-// least eight chunks for each XCD.
-constexpr int kChunkMax = 64;
+// 1473 / 1030).  Where all scenes are alike an eighth in one piece finds more of
+// what the scatter wrote in its own L2, so the chunks are as large as eight for
+// each XCD allow (8 scenes, 1M agents, 0.3 /m^2: 431 / 438 us a call, 512 scenes of
+// all sizes 2628 / 2640), and batches whose tiles are all under way at once keep the
+// eighths (8 scenes, 131,072 agents, 0.02 /m^2: 45 / 51).
+constexpr int kChunkMax = 1024;
+constexpr int kChunkAgents = 262144;  // batches of more agents
+
 
 template <int K, int BLOCK>
 hipError_t launch_step_batched_b(const BatchArgs &a, bool acc, hipStream_t stream)
 {
     const int nb = (a.n + BLOCK - 1) / BLOCK;
-    const int share = nb / (8 * kXcds);
-    const int chunk = share < 1 ? 1 : (share > kChunkMax ? kChunkMax : share);
+    int chunk = nb;  // eighths: no whole round of chunks
+    if (a.n > kChunkAgents) chunk = nb / (8 * kXcds) < kChunkMax ? nb / (8 * kXcds) : kChunkMax;
     if (acc)
         hipLaunchKernelGGL((k_step_batched_flat<K, BLOCK, true>), dim3(nb), dim3(BLOCK), 0, stream,
                            a, chunk);

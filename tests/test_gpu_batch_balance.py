@@ -46,7 +46,8 @@ def test_order_of_dense_scenes_does_not_set_the_time():
 
 
 @pytest.mark.parametrize("sizes", [[98305], [49152, 49153 + 64 * 8 - 1], [100000, 1, 37000],
-                                   [64 * 128 * 8 * 2, 64 * 100 + 1], [64 * 8 * 130 * 8 + 63]])
+                                   [64 * 128 * 8 * 2, 64 * 100 + 1], [262144, 1], [262080, 64],
+                                   [64 * 8 * 130 * 8 + 63]])
 @pytest.mark.parametrize("block", [64, 128, 256])
 def test_every_tile_is_stepped_once(sizes, block):
     """Tile counts on, below and above whole rounds of chunks, in each workgroup
