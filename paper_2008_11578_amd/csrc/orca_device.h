@@ -128,13 +128,16 @@ struct SortNet {
 // parts: counted and scanned again there, 430 us per step over steps 10-110 of
 // the 1M crossing.  By number, with kMore at 2, 3, 4 and 5: 382, 363, 362 and
 // 363 us.)
+// (Of the shortest lists two places are the half already: k 4, 66,560 agents at 0.5
+// /m^2, a lane per agent, 62 us at 4, 51 at 2 and 50 at 1.)
 constexpr int kKeptMore = 4;
 template <int K>
 struct KeptShape {
     static constexpr int kFit = SortNet<K>::N < KnnShape<K>::kCap ? SortNet<K>::N
                                                                   : KnnShape<K>::kCap - 1;
     static constexpr int kRoom = (kFit - K - 1) / 2;
-    static constexpr int kMore = kRoom < kKeptMore ? kRoom : kKeptMore;
+    static constexpr int kWant = K <= 4 ? kKeptMore / 2 : kKeptMore;
+    static constexpr int kMore = kRoom < kWant ? kRoom : kWant;
 };
 
 // Hard lines of a vehicle's own motion limits: the acceleration octagon (see
@@ -1528,7 +1531,8 @@ __device__ __forceinline__ void group_lp3(const LdsLines<BLOCK, ACC> &ls, int c,
 // case: groups take the registers of a wavefront per SIMD there (1M agents, kernel
 // in us, groups / walk: hard lines k 4 431 / 356, k 8 664 / 561, k 10 716 / 637,
 // but k 12 724 / 746; adjoint k 4 378 / 350, k 10 662 / 459, k 12 702 / 556, with
-// hard lines 660 / 463, 998 / 777, 1077 / 817).
+// hard lines 660 / 463, 998 / 777, 1077 / 817); so are lists of up to 4 in all
+// kernels (66,560 agents at 0.5 /m^2, whole call 65 / 62 us).
 template <bool REC, int K, int BLOCK, bool ACC>
 __device__ __forceinline__ void wave_lp3(const LdsLines<BLOCK, ACC> &ls, int tid, bool need, int m,
                                          int fail, float vmax, float tx, float ty, float eps,
@@ -1537,7 +1541,7 @@ __device__ __forceinline__ void wave_lp3(const LdsLines<BLOCK, ACC> &ls, int tid
     constexpr int G = ACC ? 8 : 4;
     constexpr int NL = (K + (ACC ? kAccLines + kTurnLines : 0) + G - 1) / G;
     constexpr int kGroups = kWave / G;
-    constexpr bool kWalk = K <= (REC ? 12 : 10) && (REC || ACC);
+    constexpr bool kWalk = K <= 4 || (K <= (REC ? 12 : 10) && (REC || ACC));
     const uint64_t needm = __ballot(need);
     const int nf = __popcll(needm);
     if (kWalk || nf > (ACC ? 48 : 40)) {
