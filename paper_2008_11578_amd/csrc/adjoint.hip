@@ -849,7 +849,7 @@ hipError_t launch_adjoint(const orca_agents_in &in, int n, const orca_params &pr
     const int k = prm.max_neighbors;
     if (ev && ev->step_begin && hipEventRecord(ev->step_begin, stream) != hipSuccess)
         return hipErrorInvalidValue;
-    if (n <= (has_hard_lines(prm) ? kGroupAdjointMaxHard : kGroupAdjointMax))
+    if (n <= group_adjoint_max(prm))
         launch_adjoint_group(a, n <= kWholeMax, prm.neighbor_dist, stream);
     else if (k <= 4)
         launch_adjoint_k<4>(a, stream);

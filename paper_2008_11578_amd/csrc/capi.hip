@@ -284,10 +284,9 @@ int step_impl(const orca_agents_in *in, const orca_agents_out *out, int32_t n,
         return ORCA_EHIP;
     if (events && events->step_begin && hipEventRecord(events->step_begin, stream) != hipSuccess)
         return ORCA_EHIP;
-    const int most = has_hard_lines(*params) ? kGroupStepMaxHard : kGroupStepMax;
-    if ((n <= most ? launch_step_group(*in, *out, n, *params, w, whole, nbr, nbr_count, stream)
-                   : launch_step(*in, *out, n, *params, L, w, nbr, nbr_count, stream)) !=
-        hipSuccess)
+    if ((n <= group_step_max(*params)
+             ? launch_step_group(*in, *out, n, *params, w, whole, nbr, nbr_count, stream)
+             : launch_step(*in, *out, n, *params, L, w, nbr, nbr_count, stream)) != hipSuccess)
         return ORCA_EHIP;
     if (events && events->step_end && hipEventRecord(events->step_end, stream) != hipSuccess)
         return ORCA_EHIP;

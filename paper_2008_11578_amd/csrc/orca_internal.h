@@ -357,30 +357,50 @@ hipError_t launch_step(const orca_agents_in &in, const orca_agents_out &out, int
                        int32_t *cnt, hipStream_t stream);
 
 // Small crowds: a group of lanes per agent, over the grid or (whole) over the
-// copies that launch_pack makes in caller order.  The largest crowd that takes
-// the form, by what it costs beside a lane per agent (whole calls in us, group /
-// lane): a lane per agent is one wavefront per SIMD up to 65,536 agents and
-// takes a wavefront's latency however few they are; a group of 16 does the
-// same work in more instructions.
-//   step          66,560 mixed 82 / 88, k 10 67 / 68, dense 94 / 96; 100,000
-//                 104 / 105, 85 / 76, 115 / 102
-//   hard lines    100,000 129 / 149, 150,000 168 / 176, 200,000 211 / 191
-//   adjoint       50,000 103 / 115 (k 10), 136 / 134 (dense), 72,000 124 / 117,
-//                 167 / 151; hard lines 72,000 193 / 200, 100,000 237 / 209
-//   lists         50,000 45 / 61 (k 16), 72,000 54 / 47; k 32 (a network of 64)
-//                 200,000 146 / 158, 300,000 203 / 217
+// copies that launch_pack makes in caller order.  A lane per agent is one wavefront
+// per SIMD up to 65,536 agents and takes a wavefront's latency however few they are;
+// a group of 16 does the same work in more instructions, the fewer the more work
+// an agent has.  The largest crowd that takes the form, by whole calls in us, group /
+// lane, R_n 5 m (density and k decide; the density is not known where the form is
+// chosen):
+//   step          50,000: 0.05 /m^2, k 10 56 / 52; 0.25, k 10 71 / 92; 1.0, k 10 81 / 129;
+//                 66,560: 61 / 54, 84 / 97, 99 / 131, but 51 / 43 at 0.01; 100,000 (k 20,
+//                 2 /m^2) 308 / 279
+//   k up to 4     16,384: 0.02 33 / 34, 0.5 34 / 37; 32,769: 41 / 36, 50 / 46
+//   hard lines    98,304: 0.05, k 20 105 / 96; 0.35, k 16 151 / 181; 131,072: 131 / 95, 186
+//                 / 230, 0.01, k 10 110 / 77
+//                 k up to 4: 66,560 0.02 73 / 79, 0.5 102 / 103; 98,304 93 / 83, 132 / 112
+//   adjoint       32,769: 0.05, k 10 66 / 72, 1.0 106 / 147; 50,000 74 / 73, 165 / 152
+//   hard lines    66,560: 0.05, k 10 122 / 114, 0.25 158 / 176, 2 /m^2, k 20 199 / 272
+//                 k up to 4: 66,560 0.02 113 / 93, 0.5 156 / 122
+//   lists         32,769: 0.05, k 8 35 / 33, 1.0, k 10 39 / 58; 50,000: 0.05, k 8 38 / 33, 0.35,
+//                 k 16 45 / 41; k 32 (a network of 64) 200,000 146 / 158, 300,000 203 / 217
 //   batched step  see launch_batched
 // Without a grid, each agent scanning the whole crowd: 1,500 agents 31 / 34, 2,500
-// 40 / 35 (256 agents: 23 us, bound by the host).
+// 40 / 35 (256 agents: 15 us, bound by the host).
 constexpr int kGroup = 16;  // lanes per agent
 constexpr int kWholeMax = 2048;
-constexpr int kGroupStepMax = 72000, kGroupStepMaxHard = 131072;
+constexpr int kGroupStepMax = 72000, kGroupStepMaxHard = 98304;
 constexpr int kGroupAdjointMax = 49152, kGroupAdjointMaxHard = 72000;
-constexpr int kGroupListMax = 65536, kGroupListMaxLarge = 262144;
+constexpr int kBriefList = 4;  // lists so short that a lane has little to do
+constexpr int kGroupStepMaxBrief = 16384, kGroupStepMaxBriefHard = 72000;
+constexpr int kGroupAdjointMaxBriefHard = 49152;
+constexpr int kGroupListMax = 49152, kGroupListMaxLarge = 262144;
 constexpr int kGroupBatchMax = 98304;
 inline bool has_hard_lines(const orca_params &p)
 {
     return p.accel[0] > 0.0f || p.accel[1] > 0.0f || p.turn[0] > 0.0f || p.turn[1] > 0.0f;
+}
+inline int group_step_max(const orca_params &p)
+{
+    const bool brief = p.max_neighbors <= kBriefList;
+    if (has_hard_lines(p)) return brief ? kGroupStepMaxBriefHard : kGroupStepMaxHard;
+    return brief ? kGroupStepMaxBrief : kGroupStepMax;
+}
+inline int group_adjoint_max(const orca_params &p)
+{
+    if (!has_hard_lines(p)) return kGroupAdjointMax;
+    return p.max_neighbors <= kBriefList ? kGroupAdjointMaxBriefHard : kGroupAdjointMaxHard;
 }
 // What a scan of the whole crowd needs of a grid.
 __device__ __forceinline__ GridMeta whole_crowd(int n, float rn)
@@ -398,7 +418,7 @@ hipError_t launch_step_group(const orca_agents_in &in, const orca_agents_out &ou
                              const orca_params &prm, const Work &w, bool whole, int32_t *nbr,
                              int32_t *cnt, hipStream_t stream);
 
-// The flat batched step by groups of lanes.
+// Neighbour lists by groups of lanes; the batched step by groups of lanes.
 hipError_t launch_list_group(int n, const orca_params &prm, const Work &w, int32_t *nbr,
                              int32_t *cnt, hipStream_t stream);
 hipError_t launch_batched_group(const BatchArgs &a, int k_max, bool acc, hipStream_t stream);
