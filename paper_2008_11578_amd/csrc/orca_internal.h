@@ -234,14 +234,18 @@ __device__ __forceinline__ void grid_geometry(float4 b, float rn, float cs_req, 
         fy = floor(h / cs) + 1.0;
         return fx * fy;
     };
+    bool few = false;
     if (few_cells > 0) {
         double c = c0;
-        for (int it = 0; it < 64 && c <= kStretch * (double)rn && !(cells_of(c) <= (double)few_cells);
-             ++it)
+        for (int it = 0; it < 64 && c <= kStretch * (double)rn; ++it) {
+            few = cells_of(c) <= (double)few_cells;
+            if (few) break;
             c *= 1.25;
-        c0 = c <= kStretch * (double)rn ? c : fmax(c0, (double)rn);
+        }
+        few = few && few_cells <= max_cells;
+        if (!few) c0 = fmax(c0, (double)rn);
     }
-    for (int it = 0; it < 200; ++it) {
+    for (int it = 0; it < 200 && !few; ++it) {
         if (cells_of(c0) <= (double)max_cells) break;
         c0 *= 1.25;
     }
