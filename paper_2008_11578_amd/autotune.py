@@ -2,11 +2,14 @@
 the neighbour distance) and, for batches, the launch form of the step kernel
 (one workgroup per 64 agents, or of a given size), the lanes per
 workgroup and the compiled neighbour-list capacity, by timing real steps
-on the caller's state.
+on the caller's state.  Only configurations that differ in what runs are
+timed against each other: small crowds and batches are stepped by groups of
+lanes, which have one launch shape and two capacities, and the smallest
+crowds without a grid.
 
 Results are cached in a JSON file keyed by device architecture, form, agent
-count bucket (powers of two), density bucket (half-octaves of agents/m^2) and
-neighbour cap; the cache path is $ORCA_AUTOTUNE_CACHE or
+count bucket (powers of two), density bucket (half-octaves of agents/m^2),
+neighbour cap and generation of the kernels; the cache path is $ORCA_AUTOTUNE_CACHE or
 ~/.cache/orca_mi355x/autotune.json.  Timing uses HIP events on the current
 stream; the caller's state is never modified (steps write to a scratch copy).
 """
@@ -24,6 +27,10 @@ from . import orca
 
 FACTORS = (1.0, 0.5, 1.0 / 3.0, 0.25, 0.2)
 MODES = (0, 1)
+KERNELS = 2          # raised when the kernels change so that old choices say nothing
+WHOLE_MAX = 2048     # crowds stepped without a grid (the library's kWholeMax)
+GROUP_BATCH_MAX = 98304  # batches stepped by groups of lanes (kGroupBatchMax)
+GROUP_CAPACITIES = (16, 32)  # neighbour capacities of the group kernels
 
 
 def cache_path() -> str:
@@ -71,7 +78,7 @@ def _density(state: orca.State) -> float:
 def cache_key(form: str, n: int, density: float, k: int) -> str:
     nb = int(round(math.log2(max(n, 1))))
     db = round(2.0 * math.log2(max(density, 1e-6))) / 2.0
-    return f"{_arch()}|{form}|n2^{nb}|d2^{db}|k{k}"
+    return f"{_arch()}|v{KERNELS}|{form}|n2^{nb}|d2^{db}|k{k}"
 
 
 def _time_ms(fn, reps: int) -> float:
@@ -92,14 +99,14 @@ def tune_plain(state: orca.State, params, ws: orca.Workspace,
                use_cache: bool = True) -> dict:
     """Best cell size for orca_step on this state.  Returns
     {"cell_size": cs, "factor": f, "ms": t, "timings": {f: t}}."""
-    key = cache_key("plain", state.n, _density(state), int(params.max_neighbors))
+    key = cache_key("whole" if state.n <= WHOLE_MAX else "plain", state.n, _density(state), int(params.max_neighbors))
     if use_cache:
         hit = _load().get(key)
         if hit is not None:
             return dict(hit, cell_size=hit["factor"] * params.neighbor_dist, cached=True)
     out = state.clone()
     timings = {}
-    for f in factors:
+    for f in factors[:1] if state.n <= WHOLE_MAX else factors:
         p = dataclasses.replace(params, cell_size=f * params.neighbor_dist)
         timings[f] = _time_ms(lambda: orca.step(state, p, ws, out=out), reps)
     best = min(timings, key=timings.get)
@@ -120,11 +127,14 @@ def tune_batched(state: orca.State, scene_off, scene_params: List, ws: orca.Work
     """Best (cell-size factor, launch form, lanes per workgroup, neighbour
     tile) for orca_step_batched, by coordinate search in that order, each
     stage timing its candidates with the choices made so far (the tile: the
-    smallest compiled capacity holding k and the next two).  Returns
-    {"factor", "mode", "block", "k_tile", "ms", "timings", "params" (tuned
-    per-scene list)}."""
+    smallest compiled capacity holding k and the next two).  Launch form and
+    lanes are one stage (mode 0 always has 64 lanes) and only there for batches
+    that have a choice.  Returns {"factor", "mode", "block", "k_tile", "ms",
+    "timings", "params" (tuned per-scene list)}."""
     k = max(int(p.max_neighbors) for p in scene_params)
-    key = cache_key(f"batched{len(scene_params)}", state.n, _density(state), k)
+    modes = tuple(modes)
+    group = state.n <= GROUP_BATCH_MAX
+    key = cache_key(f"batched{len(scene_params)}{'g' if group else ''}", state.n, _density(state), k)
     hit = _load().get(key) if use_cache else None
     if hit is None:
         out = state.clone()
@@ -137,13 +147,20 @@ def tune_batched(state: orca.State, scene_off, scene_params: List, ws: orca.Work
             timings[f"{f:.4f}/{m}/{b}/{kt}"] = t
             return t
 
-        best = {"factor": factors[0], "mode": 0, "block": 128, "k_tile": 0}
-        f = min(factors, key=lambda f: run(f, best["mode"], best["block"], best["k_tile"]))
-        best["factor"] = f
-        best["mode"] = min(modes, key=lambda m: run(f, m, best["block"], best["k_tile"]))
-        best["block"] = min(blocks, key=lambda b: run(f, best["mode"], b, best["k_tile"]))
+        # what a (mode, block) comes to: its lanes, and nothing in a group kernel
+        shapes = {}
+        for m in modes:
+            for blk in blocks:
+                shapes.setdefault(0 if group else (blk if m == 1 else 64), (m, blk))
         tiles = [t for t in K_TILES if t >= k][:3]
-        best["k_tile"] = min(tiles, key=lambda kt: run(f, best["mode"], best["block"], kt))
+        if group:
+            tiles = tiles[:1] + [c for c in GROUP_CAPACITIES if k <= 16 < c]
+        m, blk = next(iter(shapes.values()))
+        f = min(factors, key=lambda f: run(f, m, blk, 0))
+        if len(shapes) > 1:
+            m, blk = min(shapes.values(), key=lambda s: run(f, *s, 0))
+        kt = min(tiles, key=lambda t: run(f, m, blk, t))
+        best = {"factor": f, "mode": m, "block": blk, "k_tile": kt}
         best["ms"] = timings[f"{f:.4f}/{best['mode']}/{best['block']}/{best['k_tile']}"]
         hit = dict(best, timings=timings)
         _store(key, hit)
