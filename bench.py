@@ -79,6 +79,31 @@ def source_hash(files=("step.hip", "orca_device.h", "orca_internal.h")) -> str:
     return h.hexdigest()[:16]
 
 
+CAPACITIES = (4, 8, 10, 12, 16, 20, 24, 32)  # neighbour capacities compiled into the kernels
+
+
+def kernel_name(form: str, n: int, params, k_tile: int = 0) -> str:
+    """The kernel that the library runs for `form` (step, adjoint or batch) and n
+    agents: small crowds are stepped by groups of lanes, in two capacities
+    (the lines are read from the library's header)."""
+    with open(os.path.join(ROOT, "paper_2008_11578_amd", "csrc", "orca_internal.h")) as fh:
+        line = {k: int(v) for k, v in re.findall(r"\b(k\w+) = (\d+)\b", fh.read())}
+    k = k_tile or params.max_neighbors
+    hard = any(params.accel) or any(params.turn)
+    brief = params.max_neighbors <= line["kBriefList"]
+    if form == "step":
+        most = line["kGroupStepMax" + ("Brief" if brief else "") + ("Hard" if hard else "")]
+    elif form == "adjoint":
+        most = line["kGroupAdjointMax" + ("BriefHard" if brief and hard else "Hard" if hard else "")]
+    else:
+        most = line["kGroupBatchMax"]
+    lane, group = {"step": ("k_step", "k_step_group"), "adjoint": ("k_adjoint", "k_adjoint_group"),
+                   "batch": ("k_step_batched_flat", "k_step_batched_group")}[form]
+    if n <= most:
+        return f"{group}<{16 if k <= 16 else 32}>"
+    return f"{lane}<{min(c for c in CAPACITIES if c >= k)}>"
+
+
 def traffic_from_profile(kernel_hash: str):
     """HBM bytes per launch of the step kernel from the committed rocprofv3
     counter summary, or None when missing or taken on other kernel source."""
@@ -325,7 +350,7 @@ def bench_config_leg(name, sc, params, steps, cpu_1t_steps, cpu=True):
     if cpu:
         ops, nbr, lp3 = oracle_ops([r["start"], r["end"]], params)
         leg["roofline"] = alu_roofline(ops, r["k_ms"], n, STEP_BYTES_PER_AGENT,
-                                       f"k_step<{params.max_neighbors}>",
+                                       kernel_name("step", n, params),
                                        mean_neighbors=nbr, oracle_lp3_share=lp3)
         rate, el, th = oracle_rate(r["start"], params, n, steps)
         rate1, el1, _ = oracle_rate(r["start"], params, n, cpu_1t_steps, threads=1)
@@ -491,9 +516,9 @@ def bench_batched(steps: int, cpu: bool = True):
         for snap in (snap_start, snap_end):
             w = oracle.step_batched(snap, sc.scene_off, prm, want_work=True)["work"]
             ops.append(algorithmic_ops(w))
-        k_max = max(p.max_neighbors for p in prm)
         out["roofline"] = alu_roofline(float(np.mean(ops)), k_ms, n, STEP_BYTES_PER_AGENT,
-                                       f"k_step_batched<{tuned['k_tile'] or k_max}>")
+                                       kernel_name("batch", n, max(prm, key=lambda p: p.max_neighbors),
+                                                   tuned["k_tile"]))
         full = oracle_threads()
         oracle.set_threads(full)
         reps = 3
@@ -827,7 +852,7 @@ def bench_adjoint(reps: int = 3, cpu: bool = True):
             ops.append(algorithmic_ops(w) + ADJ_OPS_PER_NEIGHBOR * float(w[:, 2].sum())
                        + ADJ_OPS_PER_AGENT * n)
         out["roofline"] = alu_roofline(float(np.mean(ops)), k_ms, n, ADJ_BYTES_PER_AGENT,
-                                       f"k_adjoint<{p.max_neighbors}>")
+                                       kernel_name("adjoint", n, p))
         st = {k: np.array(getattr(sc, k), dtype=np.uint8 if k == "cls" else np.float64)
               for k in ("px", "py", "vx", "vy", "pref_x", "pref_y", "radius", "max_speed", "cls")}
         full = oracle_threads()
@@ -974,7 +999,7 @@ def main(argv=None):
     if ops_per_launch is not None:
         kh = source_hash()
         roof = alu_roofline(ops_per_launch, k_ms, n, STEP_BYTES_PER_AGENT,
-                            f"k_step<{params.max_neighbors}>", source_hash=kh)
+                            kernel_name("step", n, params), source_hash=kh)
         traffic = traffic_from_profile(kh)
         if traffic:
             roof.update(traffic=traffic["bytes"], traffic_raw_fetch_kib=traffic["fetch_kib"],
