@@ -25,7 +25,6 @@ struct GridMeta {
     int nx, ny;        // cells per axis
     int m;             // stencil radius in cells: in-range pairs are <= m cells apart
     int n_cells;       // nx * ny
-    double cs_d;       // cs in double (the value inv_cs was derived from)
     double inv_cs;     // 1 / cs, for the FP64 cell coordinates
     double rn2;        // rn * rn in double (exact)
     int cell_base;     // first global cell id of this scene (batched form)
@@ -265,7 +264,6 @@ __device__ __forceinline__ void grid_geometry(float4 b, float rn, float cs_req, 
     g.ny = (int)fy;
     g.m = m;
     g.n_cells = g.nx * g.ny;
-    g.cs_d = cs;
     g.inv_cs = 1.0 / cs;
     g.rn2 = (double)rn * (double)rn;
 }
