@@ -127,16 +127,17 @@ struct SortNet {
 // the K-th distance, two speed steps, holds 32 and more in a crossing's dense
 // parts: counted and scanned again there, 430 us per step over steps 10-110 of
 // the 1M crossing.  By number, with kMore at 2, 3, 4 and 5: 382, 363, 362 and
-// 363 us.)
-// (Of the shortest lists two places are the half already: k 4, 66,560 agents at 0.5
-// /m^2, a lane per agent, 62 us at 4, 51 at 2 and 50 at 1.)
+// 363 us.)  Where the buffer is small for K, three sevenths of its room: more fill
+// it too often, fewer are too few too often (262,144 agents walking, us per step, at
+// kMore 2, 3 and 4: k 10 154, 142, 148 at 1.0 /m^2; k 12 151, 139, 136; k 8 156, 158 and 3
+// the most, standing 133 and 149; k 4 115, 108, 109, standing 85, 92, 93).
 constexpr int kKeptMore = 4;
 template <int K>
 struct KeptShape {
     static constexpr int kFit = SortNet<K>::N < KnnShape<K>::kCap ? SortNet<K>::N
                                                                   : KnnShape<K>::kCap - 1;
-    static constexpr int kRoom = (kFit - K - 1) / 2;
-    static constexpr int kWant = K <= 4 ? kKeptMore / 2 : kKeptMore;
+    static constexpr int kRoom = (kFit - K - 1) * 3 / 7;
+    static constexpr int kWant = K <= kBriefList ? kKeptMore - 1 : kKeptMore;
     static constexpr int kMore = kRoom < kWant ? kRoom : kWant;
 };
 
@@ -568,7 +569,13 @@ __device__ __forceinline__ uint32_t knn_collect(const GridMeta &g,
                 }
             });
         if (n <= kFit && (n > (uint32_t)K || !(r2c < g.rn2))) return n;
-        if (n <= (uint32_t)K) r2c = g.rn2;  // too few: count them all
+        // too few: a circle that should hold about half as many again as is
+        // wanted, and still all of them in the buffer; all of R_n after that
+        // (to R_n at once, a crowd that moves paid for it every step: 262,144
+        // agents walking at 1.5 /m^2, k 8, 654 us a step, 158 so)
+        constexpr int kWanted = 3 * (K + 1 + KeptShape<K>::kMore) / 2;
+        constexpr int kNext = kWanted < kCap - 3 ? kWanted : kCap - 3;
+        if (n <= (uint32_t)K) r2c = fmin(r2c * ((double)kNext / (double)max(n, 1u)), g.rn2);
     }
     // pass 1: per-bin counts of the keys below r2c in kBins equal-area bins,
     // and the candidates themselves while they fit the buffer; again with
