@@ -452,7 +452,7 @@ __device__ __forceinline__ void adjoint_vjp(const AdjArgs &a, const AdjAgent<BLO
     a.b.tau_part[i] = taub;
 }
 
-template <int K, int BLOCK, bool ACC>
+template <int K, int BLOCK, bool ACC, bool WALK>
 __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a, const GridMeta &g,
                                               float4 *lines, int tid)
 {
@@ -507,7 +507,7 @@ __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a
         fail = f.nh;
         f.rec.kind = dev::kCentre;
     }
-    dev::wave_lp3<true, K, BLOCK, ACC>(f.src, tid, live && fail < mt, mt, fail, f.vmax, f.prx, f.pry,
+    dev::wave_lp3<true, K, BLOCK, ACC, WALK>(f.src, tid, live && fail < mt, mt, fail, f.vmax, f.prx, f.pry,
                                        p.eps, f.vx, f.vy, &f.rec);
     if (!live) return;
     adjoint_vjp(a, f, [&](int qn) {
@@ -521,15 +521,15 @@ __device__ __forceinline__ void adjoint_agent(bool live, int s, const AdjArgs &a
 
 // (four wavefronts per SIMD up to K 10, as the LDS allows: one register too many
 // without the bound)
-template <int K, int BLOCK, bool ACC>
-__global__ __launch_bounds__(BLOCK, K <= 10 && !ACC ? 4 : 1) void k_adjoint(AdjArgs a)
+template <int K, int BLOCK, bool ACC, bool WALK>
+__global__ __launch_bounds__(BLOCK, K <= 10 && !ACC && WALK ? 4 : 1) void k_adjoint(AdjArgs a)
 {
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;
     const int s = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + tid;
     const GridMeta g = *a.meta;
     // every lane of the last wavefront takes part (LP3 is solved by quads)
-    adjoint_agent<K, BLOCK, ACC>(s < a.n, min(s, a.n - 1), a, g, lines, tid);
+    adjoint_agent<K, BLOCK, ACC, WALK>(s < a.n, min(s, a.n - 1), a, g, lines, tid);
 }
 
 // The same for a small crowd: a group of lanes per agent (orca_group.h), the
@@ -781,16 +781,25 @@ __global__ __launch_bounds__(kBlock) void k_tau_final(const double *__restrict__
     if (threadIdx.x == 0) *g_tau += (float)red[0];
 }
 
+template <int K, bool ACC>
+void launch_adjoint_v(const AdjArgs &a, hipStream_t stream)
+{
+    const int nb = (a.n + kAdjBlock - 1) / kAdjBlock;
+    if (K <= 12 && a.n > kWalkAgents)
+        hipLaunchKernelGGL((k_adjoint<K, kAdjBlock, ACC, K <= 12>), dim3(nb), dim3(kAdjBlock), 0, stream,
+                           a);
+    else
+        hipLaunchKernelGGL((k_adjoint<K, kAdjBlock, ACC, K <= kBriefList>), dim3(nb), dim3(kAdjBlock), 0,
+                           stream, a);
+}
+
 template <int K>
 void launch_adjoint_k(const AdjArgs &a, hipStream_t stream)
 {
-    const int nb = (a.n + kAdjBlock - 1) / kAdjBlock;
     if (a.p.acc0 > 0.0f || a.p.acc1 > 0.0f || a.p.turn0 > 0.0f || a.p.turn1 > 0.0f)
-        hipLaunchKernelGGL((k_adjoint<K, kAdjBlock, true>), dim3(nb), dim3(kAdjBlock), 0, stream,
-                           a);
+        launch_adjoint_v<K, true>(a, stream);
     else
-        hipLaunchKernelGGL((k_adjoint<K, kAdjBlock, false>), dim3(nb), dim3(kAdjBlock), 0, stream,
-                           a);
+        launch_adjoint_v<K, false>(a, stream);
 }
 
 template <int K, bool ACC>

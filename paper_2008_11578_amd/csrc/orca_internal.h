@@ -389,6 +389,9 @@ constexpr int kGroupStepMaxBrief = 16384, kGroupStepMaxBriefHard = 72000;
 constexpr int kGroupAdjointMaxBriefHard = 49152;
 constexpr int kGroupListMax = 49152, kGroupListMaxLarge = 262144;
 constexpr int kGroupBatchMax = 98304;
+// Crowds of more agents, two wavefronts per SIMD, walk LP3 by the lane where the lists
+// are short (see wave_lp3).
+constexpr int kWalkAgents = 131072;
 inline bool has_hard_lines(const orca_params &p)
 {
     return p.accel[0] > 0.0f || p.accel[1] > 0.0f || p.turn[0] > 0.0f || p.turn[1] > 0.0f;

@@ -46,8 +46,9 @@ def kernels():
 
 
 @pytest.mark.parametrize("form,waves", [
-    (r"6k_stepILi(4|8|10)ELi64ELb.ELb0", 4), (r"9k_adjointILi(4|8|10)ELi64ELb0", 4),
-    (r"9k_adjointILi(4|8|10|12)ELi64", 3), (r"19k_step_batched_flatILi(4|8|10)ELi64", 3)])
+    (r"6k_stepILi(4|8|10)ELi64ELb0ELb0", 4), (r"6k_stepILi(4|8|10)ELi64ELb1ELb0ELb1", 4),
+    (r"9k_adjointILi(4|8|10)ELi64ELb0ELb1", 4), (r"9k_adjointILi(4|8|10|12)ELi64ELb.ELb1", 3),
+    (r"19k_step_batched_flatILi(4|8|10)ELi64", 3)])
 def test_registers_leave_room_for_the_wavefronts_the_lds_does(kernels, form, waves):
     some = {n: k for n, k in kernels.items() if re.search(form, n)}
     assert some
