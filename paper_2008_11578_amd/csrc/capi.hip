@@ -250,8 +250,7 @@ int orca_build_grid(const orca_agents_in *in, int32_t n, const orca_params *para
     const Work w = bind(L, ws);
     if (launch_grid_build(*in, n, *params, L, w, stream) != hipSuccess) return ORCA_EHIP;
     if (nbr || nbr_count) {
-        const int most = params->max_neighbors > 24 ? kGroupListMaxLarge : kGroupListMax;
-        if ((n <= most ? launch_list_group(n, *params, w, nbr, nbr_count, stream)
+        if ((n <= group_list_max(*params) ? launch_list_group(n, *params, w, nbr, nbr_count, stream)
                        : launch_knn_export(*in, n, *params, L, w, nbr, nbr_count, stream)) !=
             hipSuccess)
             return ORCA_EHIP;

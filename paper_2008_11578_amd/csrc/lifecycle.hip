@@ -633,15 +633,29 @@ __global__ __launch_bounds__(kBlock) void k_overlap(const GridMeta *__restrict__
         const GridMeta g = *meta;
         const float2 me = s0[s];
         const double r = (double)s1[s].w;
-        dev::scan_disc(g, start, s0, (double)me.x, (double)me.y, g.rn2,
-                       [&](const float2 &a, uint32_t k, bool valid) {
-                           const double d2 = dev::nb_key(me.x, me.y, a.x, a.y);
-                           if (valid && d2 < g.rn2 && k != (uint32_t)s) {
-                               const double rr = r + (double)s1[k].w;
-                               cnt += d2 < rr * rr ? 1u : 0u;
-                               gap = fmin(gap, sqrt(d2) - rr);
-                           }
-                       });
+        // the radii of a group's agents in range are asked for together
+        dev::scan_disc_groups(
+            g, start, s0, (double)me.x, (double)me.y, g.rn2,
+            [&](const float2 (&a)[dev::kScanUnroll], uint32_t t0, uint32_t e) {
+                double d2[dev::kScanUnroll];
+                float other[dev::kScanUnroll];
+                bool in[dev::kScanUnroll];
+#pragma unroll
+                for (int q = 0; q < dev::kScanUnroll; ++q) {
+                    d2[q] = dev::nb_key(me.x, me.y, a[q].x, a[q].y);
+                    in[q] = t0 + q < e && d2[q] < g.rn2 && t0 + q != (uint32_t)s;
+                    other[q] = 0.0f;
+                    if (in[q]) other[q] = s1[t0 + q].w;
+                }
+#pragma unroll
+                for (int q = 0; q < dev::kScanUnroll; ++q) {
+                    if (in[q]) {
+                        const double rr = r + (double)other[q];
+                        cnt += d2[q] < rr * rr ? 1u : 0u;
+                        gap = fmin(gap, sqrt(d2[q]) - rr);
+                    }
+                }
+            });
     }
     __shared__ double sg[kBlock / kWave];
     __shared__ uint32_t sp[kBlock / kWave], sa[kBlock / kWave];
@@ -779,7 +793,7 @@ hipError_t launch_overlap_stats(const orca_agents_in &in, int n, float reach, do
     OverlapPart *part = (OverlapPart *)extra;
     const int nb = (n + kBlock - 1) / kBlock;
     if (n > 0) {
-        const hipError_t e = launch_grid_build_rn(in, n, reach, 0.0f, L, w, stream);
+        const hipError_t e = launch_grid_build_rn(in, n, reach, 0.0f, L, w, stream, nullptr, 0, true);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_overlap, dim3(nb), dim3(kBlock), 0, stream, w.meta, w.start, w.s0,
                            w.s1, n, part);

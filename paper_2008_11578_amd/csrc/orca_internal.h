@@ -295,10 +295,11 @@ hipError_t launch_grid_build(const orca_agents_in &in, int n, const orca_params 
                              const Layout &L, const Work &w, hipStream_t stream,
                              uint32_t *clear = nullptr, int64_t clear_len = 0);
 
-// The same for a neighbour distance and a cell size.
+// The same for a neighbour distance and a cell size; fine: a short distance, which
+// takes many cells for the agents there are.
 hipError_t launch_grid_build_rn(const orca_agents_in &in, int n, float rn, float cell_size,
                                 const Layout &L, const Work &w, hipStream_t stream,
-                                uint32_t *clear = nullptr, int64_t clear_len = 0);
+                                uint32_t *clear = nullptr, int64_t clear_len = 0, bool fine = false);
 
 // Histogram scan and scatter into cell order; scan_meta supplies the number
 // of cells (n_cells) and of agents (n) of the whole cell space.
@@ -375,8 +376,9 @@ hipError_t launch_step(const orca_agents_in &in, const orca_agents_out &out, int
 //   adjoint       32,769: 0.05, k 10 66 / 72, 1.0 106 / 147; 50,000 74 / 73, 165 / 152
 //   hard lines    66,560: 0.05, k 10 122 / 114, 0.25 158 / 176, 2 /m^2, k 20 199 / 272
 //                 k up to 4: 66,560 0.02 113 / 93, 0.5 156 / 122
-//   lists         32,769: 0.05, k 8 35 / 33, 1.0, k 10 39 / 58; 50,000: 0.05, k 8 38 / 33, 0.35,
-//                 k 16 45 / 41; k 32 (a network of 64) 200,000 146 / 158, 300,000 203 / 217
+//   lists         50,000: 0.05, k 8 38 / 33, 0.35, k 16 45 / 41, 1.0, k 10 46 / 66, one agent 7
+//                 km away 75 / 188; k 32 (a network of 64) 200,000 146 / 158, 300,000 203 / 217
+//                 k up to 4: 50,000 0.02 37 / 33, 0.5 40 / 36
 //   batched step  see launch_batched
 // Without a grid, each agent scanning the whole crowd: 1,500 agents 31 / 34, 2,500
 // 40 / 35 (256 agents: 15 us, bound by the host).
@@ -387,7 +389,7 @@ constexpr int kGroupAdjointMax = 49152, kGroupAdjointMaxHard = 72000;
 constexpr int kBriefList = 4;  // lists so short that a lane has little to do
 constexpr int kGroupStepMaxBrief = 16384, kGroupStepMaxBriefHard = 72000;
 constexpr int kGroupAdjointMaxBriefHard = 49152;
-constexpr int kGroupListMax = 49152, kGroupListMaxLarge = 262144;
+constexpr int kGroupListMax = 65536, kGroupListMaxLarge = 262144, kGroupListMaxBrief = 49152;
 constexpr int kGroupBatchMax = 98304;
 // Crowds of more agents, two wavefronts per SIMD, walk LP3 by the lane where the lists
 // are short (see wave_lp3).
@@ -406,6 +408,12 @@ inline int group_adjoint_max(const orca_params &p)
 {
     if (!has_hard_lines(p)) return kGroupAdjointMax;
     return p.max_neighbors <= kBriefList ? kGroupAdjointMaxBriefHard : kGroupAdjointMaxHard;
+}
+inline int group_list_max(const orca_params &p)
+{
+    return p.max_neighbors <= kBriefList ? kGroupListMaxBrief
+           : p.max_neighbors > 24        ? kGroupListMaxLarge
+                                         : kGroupListMax;
 }
 // What a scan of the whole crowd needs of a grid.
 __device__ __forceinline__ GridMeta whole_crowd(int n, float rn)

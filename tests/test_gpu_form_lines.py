@@ -47,8 +47,8 @@ def _took(what, n, density, k, caps):
     ("step", 16384, 4, False), ("step", 72000, 4, False), ("step", 72000, 10, False),
     ("step", 72000, 4, True), ("step", 98304, 16, True), ("step", 131072, 4, True),
     ("step", 131072, 20, True), ("adjoint", 49152, 10, False), ("adjoint", 49152, 4, True),
-    ("adjoint", 72000, 4, True), ("lists", 49152, 10, False),
-    ("step", 131072, 8, True), ("adjoint", 131072, 10, False)])
+    ("adjoint", 72000, 4, True), ("lists", 65536, 10, False),
+    ("lists", 49152, 4, False), ("step", 131072, 8, True), ("adjoint", 131072, 10, False)])
 def test_both_sides_of_a_line_take_about_as_long(what, line, k, caps):
     for density in (0.05, 0.3):
         below, above = (_took(what, n, density, k, caps) for n in (line, line + 1))
