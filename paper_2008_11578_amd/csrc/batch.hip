@@ -135,7 +135,7 @@ __device__ __forceinline__ void batch_agent(const BatchArgs &a, int s, int first
     const int sc = scene_from(a.off, a.S, first, s);
     const GridMeta g = a.meta[sc];
     const dev::SceneP p = dev::scene_params(a.prm[sc]);
-    dev::step_agent<K, BLOCK, ACC, false, K <= kBriefList>(live, s, g, p, a.in, a.out, a.start, a.s0, a.s1, lines, tid,
+    dev::step_agent<K, BLOCK, ACC>(live, s, g, p, a.in, a.out, a.start, a.s0, a.s1, lines, tid,
                                    a.guess);
 }
 

@@ -1534,15 +1534,13 @@ __device__ __forceinline__ void group_lp3(const LdsLines<BLOCK, ACC> &ls, int c,
 // (419 us by the walk alone), 512 scenes at 32, 40 and groups alone 3.68, 3.57
 // and 3.56 ms, 200,003 capped at 24 to 48 253, 238, 211 and 212 us; small
 // crowds are the same down to 32 and lose at 24 (4,999 mixed: 92 and 112 us).
-// WALK: the lanes in any case.  Groups take the registers of a wavefront or two per
-// SIMD from the kernels with hard lines or a recorded active set and short lists,
-// which large crowds feel and small ones do not (whole calls in us, groups / walk,
-// at 0.05 and 0.45 /m^2: adjoint k 10 131,072 agents 83 / 85, 151 / 148, 200,000 121 / 101,
-// 227 / 180, 1M 497 / 468, 765 / 592; with hard lines k 8 131,072 113 / 139, 193 / 188,
-// 200,000 169 / 166, 306 / 262, 1M 592 / 514, 1107 / 816; step with hard lines k 8 131,072
-// 92 / 119, 163 / 171, 262,144 139 / 151, 265 / 238, 1M 385 / 386, 745 / 646, but k 12 1M
-// 724 / 746): the step up to k 10, the adjoint up to 12, above kWalkAgents.  Lists of up
-// to kBriefList are walked by all kernels (66,560 agents at 0.5 /m^2 65 / 62 us).
+// WALK: the lanes in any case.  Groups that record the active set take the registers
+// of a wavefront or two per SIMD, which large crowds feel and small ones do not (whole
+// adjoints in us, groups / walk, at 0.05 and 0.45 /m^2: k 10 131,072 agents 83 / 85, 151 /
+// 148, 200,000 121 / 101, 227 / 180, 1M 497 / 468, 765 / 592; with hard lines k 8 131,072 113 /
+// 139, 193 / 188, 200,000 169 / 166, 306 / 262, 1M 592 / 514, 1107 / 816): the adjoint up to k
+// 12, above kWalkAgents.  Lists of up to kBriefList are walked by all kernels without hard
+// lines (step, 66,560 agents at 0.5 /m^2, 65 / 62 us).
 template <bool REC, int K, int BLOCK, bool ACC, bool WALK>
 __device__ __forceinline__ void wave_lp3(const LdsLines<BLOCK, ACC> &ls, int tid, bool need, int m,
                                          int fail, float vmax, float tx, float ty, float eps,
@@ -1696,7 +1694,7 @@ __device__ __forceinline__ void desired_velocity(const SceneP &p, float xi, floa
 // cnt[i] (either nullable); the step itself is unchanged.  All 64 lanes of a
 // wavefront call it; one that is not `live` repeats an agent of another lane
 // and writes nothing (its lanes serve LP3).
-template <int K, int BLOCK, bool ACC = false, bool EXPORT = false, bool WALK = false>
+template <int K, int BLOCK, bool ACC = false, bool EXPORT = false>
 __device__ __forceinline__ void step_agent(bool live, int s, const GridMeta &g, const SceneP &p,
                                            const orca_agents_in &in, const orca_agents_out &out,
                                            const uint32_t *__restrict__ start,
@@ -1759,7 +1757,7 @@ __device__ __forceinline__ void step_agent(bool live, int s, const GridMeta &g, 
         st = 1;
     }
     const bool infeasible = fail < mt;
-    wave_lp3<false, K, BLOCK, ACC, WALK>(src, tid, live && infeasible, mt, fail, vmax, prx, pry, p.eps,
+    wave_lp3<false, K, BLOCK, ACC, (!ACC && K <= kBriefList)>(src, tid, live && infeasible, mt, fail, vmax, prx, pry, p.eps,
                                    vx, vy, nullptr);
     if (infeasible) st = 1;
     if (!live) return;

@@ -391,8 +391,8 @@ constexpr int kGroupStepMaxBrief = 16384, kGroupStepMaxBriefHard = 72000;
 constexpr int kGroupAdjointMaxBriefHard = 49152;
 constexpr int kGroupListMax = 65536, kGroupListMaxLarge = 262144, kGroupListMaxBrief = 49152;
 constexpr int kGroupBatchMax = 98304;
-// Crowds of more agents, two wavefronts per SIMD, walk LP3 by the lane where the lists
-// are short (see wave_lp3).
+// The adjoint of more agents, two wavefronts per SIMD, walks LP3 by the lane where the
+// lists are short (see wave_lp3).
 constexpr int kWalkAgents = 131072;
 inline bool has_hard_lines(const orca_params &p)
 {

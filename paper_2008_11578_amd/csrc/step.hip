@@ -32,20 +32,22 @@ using dev::knn_select;
 // Wavefronts per SIMD the registers leave room for, where the lines' LDS leaves
 // room for as many (4 up to K 10): without the bound LP3 by groups takes more than
 // 128 registers and the fourth wavefront does not fit (1M agents, kernel in us
-// without / with: k 10 346 / 302 at 0.3 /m^2, 451 / 400 at 1.0).  At k 12, which
-// has room for three and a quarter, 457 / 479.
-template <int K, bool ACC, bool EXPORT, bool WALK>
-constexpr int kStepWaves = K <= 10 && !EXPORT && (!ACC || WALK) ? 4 : 1;
+// without / with: k 10 346 / 302 at 0.3 /m^2, 451 / 400 at 1.0; with hard lines, whose 17
+// registers too many go to scratch memory, whole steps of walking crowds k 8 692 / 573,
+// k 10 566 / 515, of jammed ones k 8 745 / 623).  At k 12, which has room for three and a
+// quarter, 457 / 479.
+template <int K, bool EXPORT>
+constexpr int kStepWaves = K <= 10 && !EXPORT ? 4 : 1;
 
 // EXPORT: the same step, also writing the neighbour lists it used.
-template <int K, int BLOCK, bool ACC, bool EXPORT, bool WALK>
-__global__ __launch_bounds__(BLOCK, (kStepWaves<K, ACC, EXPORT, WALK>)) void k_step(StepArgs a, dev::SceneP p)
+template <int K, int BLOCK, bool ACC, bool EXPORT>
+__global__ __launch_bounds__(BLOCK, (kStepWaves<K, EXPORT>)) void k_step(StepArgs a, dev::SceneP p)
 {
     __shared__ float4 lines[dev::KnnShape<K>::kSlots * BLOCK];
     const int tid = threadIdx.x;
     const int s = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + tid;
     const GridMeta g = *a.meta;
-    dev::step_agent<K, BLOCK, ACC, EXPORT, WALK>(s < a.n, min(s, a.n - 1), g, p, a.in, a.out, a.start,
+    dev::step_agent<K, BLOCK, ACC, EXPORT>(s < a.n, min(s, a.n - 1), g, p, a.in, a.out, a.start,
                                            a.s0, a.s1, lines, tid, a.guess, a.nbr, a.cnt, a.k);
 }
 
@@ -104,22 +106,18 @@ void launch_step_k(const StepArgs &a, hipStream_t stream)
     const bool acc = has_hard_lines(a.prm);
     const bool exp = a.nbr || a.cnt;
     const dev::SceneP p = dev::scene_params(a.prm);
-    constexpr bool kBrief = K <= kBriefList;
     if (acc && exp)
-        hipLaunchKernelGGL((k_step<K, kStepBlock, true, true, kBrief>), dim3(nb), dim3(kStepBlock), 0,
-                           stream, a, p);
-    else if (acc && K <= 10 && a.n > kWalkAgents)
-        hipLaunchKernelGGL((k_step<K, kStepBlock, true, false, K <= 10>), dim3(nb), dim3(kStepBlock), 0,
+        hipLaunchKernelGGL((k_step<K, kStepBlock, true, true>), dim3(nb), dim3(kStepBlock), 0,
                            stream, a, p);
     else if (acc)
-        hipLaunchKernelGGL((k_step<K, kStepBlock, true, false, kBrief>), dim3(nb), dim3(kStepBlock), 0,
+        hipLaunchKernelGGL((k_step<K, kStepBlock, true, false>), dim3(nb), dim3(kStepBlock), 0,
                            stream, a, p);
     else if (exp)
-        hipLaunchKernelGGL((k_step<K, kStepBlock, false, true, kBrief>), dim3(nb), dim3(kStepBlock), 0,
+        hipLaunchKernelGGL((k_step<K, kStepBlock, false, true>), dim3(nb), dim3(kStepBlock), 0,
                            stream, a, p);
     else
-        hipLaunchKernelGGL((k_step<K, kStepBlock, false, false, kBrief>), dim3(nb), dim3(kStepBlock),
-                           0, stream, a, p);
+        hipLaunchKernelGGL((k_step<K, kStepBlock, false, false>), dim3(nb), dim3(kStepBlock), 0,
+                           stream, a, p);
 }
 
 template <int K>
