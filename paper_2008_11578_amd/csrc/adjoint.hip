@@ -567,13 +567,18 @@ __global__ __launch_bounds__(kWave) void k_adjoint_group(AdjArgs a, float rn)
 }
 
 // Targets of more edges than a list holds are ordered by their own lane up to
-// kHubLane, in its column of the wavefront's LDS, up to kHubWave by the wavefront
-// there, and beyond as linked lists in place.
-// (a column of 32 and not of 16 or 24: a vehicle among pedestrians has about k
+// kHubLane, in a column of the wavefront's LDS (kHubCols lanes at a time), up to
+// kHubWave by the wavefront there, and beyond as linked lists in place.
+// (A column of 32 and not of 16 or 24: a vehicle among pedestrians has about k
 // edges, and vehicles lie together in many orders; 5,000 agents, 50 of them with
-// discs of 2.5 m, k 20: 202 us at 16, 100 at 24 and 32; k 32 260 at 24, 171 at 32)
+// discs of 2.5 m, k 20: 202 us at 16, 100 at 24 and 32; k 32 260 at 24, 171 at 32.
+// A column for every lane held the SIMDs to five wavefronts: 1M crossing 479 us, 472
+// so.)
 constexpr int kHubLane = 32;
-constexpr int kHubWave = kHubLane * kWave / 2;
+constexpr int kHubCols = 32;
+constexpr int kHubWords = kHubLane * kHubCols;  // of a wavefront
+constexpr int kHubWave = kHubWords / 2;
+constexpr int kHubBins = kHubWords / kWave;
 
 // Two chains (edge index + 1, ended by 0), each ascending, into one.
 __device__ uint32_t merge_chains(uint32_t *__restrict__ next, uint32_t x, uint32_t y)
@@ -607,7 +612,7 @@ __device__ uint32_t sort_chain(const AdjointBufs &b, int64_t j, uint32_t m, uint
         h = next[h - 1u];
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    for (int k = 0; k < kHubLane; ++k) bins[k * kWave] = 0u;
+    for (int k = 0; k < kHubBins; ++k) bins[k * kWave] = 0u;
     const uint32_t from = (uint32_t)lane * share;
     uint32_t left = from < rest ? min(share, rest - from) : 0u;
     uint32_t mine = lane < kEdgeSlots ? b.e_list[j * kEdgeSlots + lane] + 1u : 0u;
@@ -624,14 +629,14 @@ __device__ uint32_t sort_chain(const AdjointBufs &b, int64_t j, uint32_t m, uint
             const uint32_t have = bins[k * kWave];
             bins[k * kWave] = 0u;
             chain = merge_chains(next, have, chain);
-            if (!have || k == kHubLane - 1) {
+            if (!have || k == kHubBins - 1) {
                 bins[k * kWave] = chain;
                 break;
             }
         }
     }
     uint32_t chain = 0;
-    for (int k = 0; k < kHubLane; ++k) chain = merge_chains(next, bins[k * kWave], chain);
+    for (int k = 0; k < kHubBins; ++k) chain = merge_chains(next, bins[k * kWave], chain);
     for (int o = 1; o < kWave; o <<= 1) {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         const uint32_t other = (uint32_t)__shfl_down((int)chain, o, kWave);
@@ -694,7 +699,7 @@ template <bool TAU>
 __global__ __launch_bounds__(kBlock) void k_edge_gather(int n, AdjointBufs b, float *gpx0, float *gpy0,
                                                         float *gvx0, float *gvy0)
 {
-    __shared__ uint32_t order[kBlock / kWave][kHubLane * kWave];
+    __shared__ uint32_t order[kBlock / kWave][kHubWords];
     const int lane = threadIdx.x % kWave;
     uint32_t *lds = order[threadIdx.x / kWave];
     const int j = blockIdx.x * kBlock + threadIdx.x;
@@ -706,8 +711,11 @@ __global__ __launch_bounds__(kBlock) void k_edge_gather(int n, AdjointBufs b, fl
         tx += v.z;
         ty += v.w;
     };
+    const bool hub = c > (uint32_t)kEdgeSlots && c <= (uint32_t)kHubLane;
+    const uint64_t own = __ballot(hub);
+    const int rank = __popcll(own & ((1ull << lane) - 1ull));
+    uint32_t e[kEdgeSlots];
     if (c <= (uint32_t)kHubLane) {
-        uint32_t e[kEdgeSlots];
         static_assert(kEdgeSlots == 8, "two loads and a network of eight");
         const uint4 *l = (const uint4 *)(b.e_list + (int64_t)min(j, n - 1) * kEdgeSlots);
         const uint4 p = l[0], q = c > 4u ? l[1] : make_uint4(~0u, ~0u, ~0u, ~0u);
@@ -720,23 +728,27 @@ __global__ __launch_bounds__(kBlock) void k_edge_gather(int n, AdjointBufs b, fl
         e[6] = c > 6u ? q.z : ~0u;
         e[7] = c > 7u ? q.w : ~0u;
         dev::sort_network<kEdgeSlots>(e);
-        if (c <= (uint32_t)kEdgeSlots) {
+        if (!hub) {
 #pragma unroll
             for (int k = 0; k < kEdgeSlots; ++k)
                 if ((uint32_t)k < c) add(b.e_val[e[k]]);
-        } else {
-            uint32_t *col = lds + lane;
+        }
+    }
+    for (int first = 0; first < __popcll(own); first += kHubCols) {
+        dev::lane_order<kWave>();  // the columns of the lanes before are read
+        if (hub && rank >= first && rank < first + kHubCols) {
+            uint32_t *col = lds + (rank - first);
 #pragma unroll
-            for (int k = 0; k < kEdgeSlots; ++k) col[k * kWave] = e[k];
+            for (int k = 0; k < kEdgeSlots; ++k) col[k * kHubCols] = e[k];
             uint32_t h = b.e_head[j];
             for (int k = kEdgeSlots; k < (int)c && h; ++k) {
                 int at = k;
-                for (; at > 0 && col[(at - 1) * kWave] > h - 1u; --at)
-                    col[at * kWave] = col[(at - 1) * kWave];
-                col[at * kWave] = h - 1u;
+                for (; at > 0 && col[(at - 1) * kHubCols] > h - 1u; --at)
+                    col[at * kHubCols] = col[(at - 1) * kHubCols];
+                col[at * kHubCols] = h - 1u;
                 h = b.e_next[h - 1u];
             }
-            for (uint32_t k = 0; k < c; ++k) add(b.e_val[col[k * kWave]]);
+            for (uint32_t k = 0; k < c; ++k) add(b.e_val[col[k * kHubCols]]);
         }
     }
     for (uint64_t hubs = __ballot(c > (uint32_t)kHubLane); hubs; hubs &= hubs - 1) {

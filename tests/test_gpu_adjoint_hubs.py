@@ -87,3 +87,69 @@ def test_thousands_at_one_place_stay_cheap(m):
     print(f"{m} at one place: {best:.2f} ms")
     assert torch.equal(first, again)
     assert best < 25.0 * m / 1000.0
+
+
+@pytest.mark.parametrize("filler", [0, 60000])
+@pytest.mark.parametrize("vehicles,ring", [(70, 14), (64, 20), (33, 12), (30, 38)])
+def test_a_wavefront_of_vehicles_that_everyone_avoids(vehicles, ring, filler):
+    """Vehicles lie together in the caller's order, each in a ring of pedestrians
+    who walk towards it, so most lanes of a wavefront have more terms than a list
+    holds: each vehicle's sum is the FP32 sum of its terms in the order of the
+    sources."""
+    import torch
+    n = vehicles * (ring + 1)
+    p = scenarios.Params(dt=0.1, neighbor_dist=8.0, max_neighbors=16, pref_is_goal=0,
+                         f=((0.5, 1.0), (0.0, 0.5)))
+    rng = np.random.default_rng(ring)
+    side = 0.12 * ring + 0.6  # radius of the ring
+    at = np.stack([np.arange(vehicles) % 9, np.arange(vehicles) // 9], 1) * (2.0 * side + 9.0)
+    ang = 2.0 * np.pi * (np.arange(ring)[None] + rng.uniform(0, 0.3, (vehicles, ring))) / ring
+    out = np.stack([np.cos(ang), np.sin(ang)], 2)
+    arrays = {f: np.zeros(n, np.float32) for f in ("px", "py", "vx", "vy", "pref_x", "pref_y",
+                                                  "radius", "max_speed")}
+    for c, f in enumerate(("px", "py")):
+        arrays[f][:vehicles] = at[:, c]
+        arrays[f][vehicles:] = (at[:, None, c] + side * out[:, :, c]).ravel()
+    for c, (f, g) in enumerate((("vx", "pref_x"), ("vy", "pref_y"))):
+        arrays[f][vehicles:] = arrays[g][vehicles:] = (-1.2 * out[:, :, c]).ravel()
+    arrays["radius"][:] = 0.2
+    arrays["radius"][:vehicles] = side - 0.5
+    arrays["max_speed"][:] = 1.5
+    arrays["cls"] = (np.arange(n) < vehicles).astype(np.uint8)
+    if filler:
+        far = {f: np.zeros(filler, v.dtype) for f, v in arrays.items()}
+        far["px"] = (1000.0 + 20.0 * (np.arange(filler) % 250)).astype(np.float32)
+        far["py"] = (1000.0 + 20.0 * (np.arange(filler) // 250)).astype(np.float32)
+        far["radius"] += np.float32(0.3)
+        far["max_speed"] += np.float32(1.5)
+        arrays = {f: np.concatenate([v, far[f]]) for f, v in arrays.items()}
+
+    class Crowd:
+        pass
+
+    crowd = Crowd()
+    crowd.arrays = lambda: arrays
+    go = _backward(crowd, p)
+    total = n + filler
+    gen = torch.Generator().manual_seed(ring)
+    cot = [torch.zeros(total) for _ in range(4)]
+    for c in cot:
+        c[vehicles:n] = torch.randn(n - vehicles, generator=gen)
+    whole = go([c.cuda() for c in cot])[:, :vehicles].cpu().numpy()
+    one = [torch.zeros(total, device="cuda") for _ in range(4)]
+    terms = []
+    for i in range(vehicles, n):
+        for o, c in zip(one, cot):
+            o[i] = c[i]
+        terms.append(go(one)[:, :vehicles].clone())
+        for o in one:
+            o[i] = 0.0
+    terms = torch.stack(terms).cpu().numpy()
+    sums = np.zeros_like(whole)
+    for t in terms:
+        sums += t
+    count = (np.abs(terms).sum(axis=1) > 0).sum(axis=0)
+    print("terms of each vehicle: %d to %d, %d of %d more than 8" %
+          (count.min(), count.max(), (count > 8).sum(), vehicles))
+    assert (count > min(8, ring - 2)).mean() > 0.7
+    np.testing.assert_array_equal(whole, sums)
