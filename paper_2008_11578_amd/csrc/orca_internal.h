@@ -222,7 +222,7 @@ __device__ __forceinline__ void grid_geometry(float4 b, float rn, float cs_req, 
     const bool finite = isfinite(b.x) && isfinite(b.y) && isfinite(b.z) && isfinite(b.w);
     const double w = finite ? (double)b.z - (double)b.x : 0.0;
     const double h = finite ? (double)b.w - (double)b.y : 0.0;
-    double c0 = cs_req > 0.0f ? (double)cs_req : (double)rn;
+    const double c0 = cs_req > 0.0f ? (double)cs_req : (double)rn;
     int m = 1;
     double cs = c0, fx = 0.0, fy = 0.0;
     auto cells_of = [&](double c) {
@@ -233,20 +233,17 @@ __device__ __forceinline__ void grid_geometry(float4 b, float rn, float cs_req, 
         fy = floor(h / cs) + 1.0;
         return fx * fy;
     };
-    bool few = false;
-    if (few_cells > 0) {
-        double c = c0;
-        for (int it = 0; it < 64 && c <= kStretch * (double)rn; ++it) {
-            few = cells_of(c) <= (double)few_cells;
-            if (few) break;
-            c *= 1.25;
+    bool few = few_cells > 0;
+    double limit = few && few_cells < max_cells ? few_cells : max_cells;
+    double c = c0;
+    for (int it = 0; it < 264; ++it) {
+        if (few && (it == 64 || !(c <= kStretch * (double)rn))) {
+            few = false;
+            limit = max_cells;
+            c = fmax(c0, (double)rn);
         }
-        few = few && few_cells <= max_cells;
-        if (!few) c0 = fmax(c0, (double)rn);
-    }
-    for (int it = 0; it < 200 && !few; ++it) {
-        if (cells_of(c0) <= (double)max_cells) break;
-        c0 *= 1.25;
+        if (cells_of(c) <= limit) break;
+        c *= 1.25;
     }
     if (!(fx * fy <= (double)max_cells) || !(cs > 0.0)) {
         // only for extents beyond ~1e19 cells or non-positive sizes: one

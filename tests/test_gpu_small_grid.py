@@ -64,3 +64,18 @@ def test_cell_counts_about_whole_runs(n, nx):
     torch.cuda.synchronize()
     assert _cell(ws)[1] == nx
     np.testing.assert_array_equal(nbr.cpu().numpy(), oracle.step(sc, p, want_neighbors=True)["nbr"])
+
+
+@pytest.mark.parametrize("n,max_cells", [(2858, 0), (4095, 0), (4096, 0), (2100, 8191), (9000, 0)])
+def test_cells_finer_than_the_neighbour_distance_where_they_fit(n, max_cells):
+    """Also in a workspace that allows fewer cells than the scan's table holds."""
+    import oracle
+    import torch
+    from paper_2008_11578_amd import orca
+    p = scenarios.Params(neighbor_dist=3.0, cell_size=1.5, max_neighbors=10)
+    sc = scenarios.random_state(n, float(np.sqrt(n / 1.6)), seed=n, params=p)
+    ws = orca.Workspace(n, max_cells=max_cells)
+    nbr, cnt = orca.build_grid(orca.State.from_arrays(sc), p, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(_cell(ws)[0], 1.5 * (1.0 + 1e-5), rtol=1e-6)
+    np.testing.assert_array_equal(nbr.cpu().numpy(), oracle.step(sc, p, want_neighbors=True)["nbr"])
