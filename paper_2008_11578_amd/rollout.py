@@ -25,8 +25,11 @@ def _at(base: orca.State, rows: torch.Tensor) -> orca.State:
     """`base` with the positions and velocities in the four rows of `rows`
     (views, each in the shape of the array it stands for; everything else is
     shared)."""
-    return dataclasses.replace(base, **{k: row.view(getattr(base, k).shape)
-                                        for k, row in zip(MOVING, rows)})
+    moving = dict(zip(MOVING, rows.unbind()))
+    for k in MOVING:
+        if getattr(base, k).dim() != 1:
+            moving[k] = moving[k].view(getattr(base, k).shape)
+    return dataclasses.replace(base, **moving)
 
 
 def _rows(st: orca.State) -> torch.Tensor:
@@ -54,7 +57,8 @@ class Rollout(torch.autograd.Function):
         here = there = (None, base)
         if steps > 0:
             base.agents_in()  # the arrays as they were given, before they become rows
-            here, there = ((r, _at(base, r)) for r in (_rows(base), _rows(base)))
+            rows = _rows(base)
+            here, there = ((r, _at(base, r)) for r in (rows, torch.empty_like(rows)))
         for t in range(steps):
             if t % ckpt == 0:
                 ckpts.append(here[0].clone())
@@ -91,7 +95,7 @@ class Rollout(torch.autograd.Function):
         mismatch = torch.zeros((), dtype=torch.int64, device=dev)
         # the states of a segment after its checkpoint
         seq = torch.empty((min(ckpt, steps) if n_seg else 0, 4, n), dtype=torch.float32, device=dev)
-        after = [_at(base, rows) for rows in seq]
+        after = [_at(base, rows) for rows in seq.unbind()]
         for seg in range(n_seg - 1, -1, -1):
             t0 = seg * ckpt
             m = min(ckpt, steps - t0)
