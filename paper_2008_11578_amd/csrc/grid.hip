@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(orca_agents_in in, int n,
 // block has the whole histogram to go through, so blocks are as large as they
 // can be, and each loads its share at once.
 //   up to kTable cells: scanned into a table in LDS, an agent reads its start there;
-//   more: summed by runs of kSub cells (16 lanes a run), the sums scanned in LDS;
+//   more: summed by runs of kSub cells (8 lanes a run), the sums scanned in LDS;
 //         an agent's start is its run's prefix and what the run holds before its
 //         cell.
 // The starts are also stored for the kernels after this one, each block a part of
@@ -360,8 +360,8 @@ void launch_count(const orca_agents_in &in, int n, float rn, float cell_size, in
         hipLaunchKernelGGL(k_grid_setup, dim3(1), dim3(kBlock), 0, stream, w.partial, nbb, rn,
                            cell_size, max_cells, n, w.meta);
     hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, stream, in.px, in.py, n,
-                       fused ? w.partial : nullptr, nbb, rn, cell_size, max_cells, few_cells, w.meta, w.cell,
-                       w.rank, w.count);
+                       fused ? w.partial : nullptr, nbb, rn, cell_size, max_cells, few_cells,
+                       w.meta, w.cell, w.rank, w.count);
 }
 }  // namespace
 

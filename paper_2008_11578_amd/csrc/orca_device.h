@@ -130,7 +130,9 @@ struct SortNet {
 // 363 us.)  Where the buffer is small for K, three sevenths of its room: more fill
 // it too often, fewer are too few too often (262,144 agents walking, us per step, at
 // kMore 2, 3 and 4: k 10 154, 142, 148 at 1.0 /m^2; k 12 151, 139, 136; k 8 156, 158 and 3
-// the most, standing 133 and 149; k 4 115, 108, 109, standing 85, 92, 93).
+// the most, standing 133 and 149; k 4 115, 108, 109, standing 85, 92, 93; lists of
+// those standing, k 10, at 3 and 4: 90.6 and 102.0 at 1.0 /m^2, 83.9 and 82.6 at 0.26,
+// where R_n holds little more).
 constexpr int kKeptMore = 4;
 template <int K>
 struct KeptShape {
